@@ -4,9 +4,10 @@
 // A real ring of n = 2h points goes through one complex DFT of length h
 // (even samples as real part, odd samples as imaginary part) with the usual
 // split/merge step around it.  The length-h DFT is a Stockham autosort
-// mixed-radix FFT (radices 16, 9, 8, 4, 2, 3 and the primes 5 to 23; 17 in
-// FP64) held in LDS, run in place: each pass reads its butterflies into
-// registers, synchronises, then writes.  One larger prime factor (up to 1021:
+// mixed-radix FFT (radices up to 20 and 23; 17 in FP64) held in LDS, run in
+// place: each pass reads its butterflies into registers, synchronises, then
+// writes.  The first pass reads the kernel's input itself and the last writes
+// its output where the radix allows.  One larger prime factor (up to 1021:
 // always up to 191, above that where the plan's cost model prefers it to
 // Bluestein) runs as a general prime pass on the matrix cores (below); other
 // lengths go through Bluestein's chirp convolution at a length L = 2^a 3^b
@@ -138,6 +139,17 @@ __device__ constexpr C2<T> root(int t)
     return C2<T>{T(PrimeRoots<R>::c[u]), T(t <= R / 2 ? -sn : sn)};
 }
 
+// First of the two coprime factors of the composite radices that are formed by
+// the prime-factor map (0: the radix is formed otherwise).
+__host__ __device__ constexpr int pfa_factor(int R)
+{
+    return R == 6 || R == 10 || R == 14 || R == 18 ? 2
+           : R == 12 || R == 20                   ? 4
+           : R == 15                              ? 3
+           : R == 24                              ? 8
+                                                  : 0;
+}
+
 // Forward radix-R DFT of v in registers.
 template <typename T, int R>
 __device__ inline void dft_reg(C2<T> *v)
@@ -225,6 +237,29 @@ __device__ inline void dft_reg(C2<T> *v)
 #pragma unroll
             for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = t[k2];
         }
+    } else if constexpr (pfa_factor(R) > 0) {
+        // R = A B with A and B coprime, by the prime-factor map: inputs
+        // n = (a B + b A) mod R, A- and B-point DFTs with no twiddles between
+        // them, output k at (k mod A, k mod B)
+        constexpr int A = pfa_factor(R), B = R / A;
+        C2<T> y[A][B];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) y[a][b] = v[(a * B + b * A) % R];
+            dft_reg<T, B>(y[a]);
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            C2<T> t[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) t[a] = y[a][b];
+            dft_reg<T, A>(t);
+#pragma unroll
+            for (int a = 0; a < A; ++a) y[a][b] = t[a];
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[k] = y[k % A][k % B];
     } else {
         // odd R: pair r with R - r
         constexpr int H = (R - 1) / 2;
@@ -283,9 +318,10 @@ __device__ inline PassDesc uniform(PassDesc d)
 
 
 // The table reads behind the twiddle powers of one butterfly: w = W[t1]
-// (w = exp(-2 pi i k / (Ns R))) and, for radix 9 and 16, w^3 or w^4.
+// (w = exp(-2 pi i k / (Ns R))) and, for radix 9, w^3, for the radices from
+// 10 to 24, w^4.
 template <int R>
-constexpr int twiddle_step2() { return R == 9 ? 3 : R == 16 ? 4 : 0; }
+constexpr int twiddle_step2() { return R == 9 ? 3 : R >= 10 && R != 23 ? 4 : 0; }
 
 // Powers w^r (r = 1 .. R-1) from w and the second table value, by products
 // at most three deep; tw[0] is unused.
@@ -301,16 +337,19 @@ __device__ inline void twiddle_powers(C2<T> *tw, C2<T> w1, C2<T> w2nd)
         for (int a = 3; a <= 6; a += 3)
 #pragma unroll
             for (int b = 1; b <= 2; ++b) tw[a + b] = cmul(tw[a], tw[b]);
-    } else if constexpr (R == 16) {
+    } else if constexpr (twiddle_step2<R>() == 4) {
         tw[2] = cmul(tw[1], tw[1]);
         tw[3] = cmul(tw[1], tw[2]);
         tw[4] = w2nd;
         tw[8] = cmul(w2nd, w2nd);
-        tw[12] = cmul(w2nd, tw[8]);
+        if constexpr (R > 12) tw[12] = cmul(w2nd, tw[8]);
+        if constexpr (R > 16) tw[16] = cmul(tw[8], tw[8]);
+        if constexpr (R > 20) tw[20] = cmul(tw[16], w2nd);
 #pragma unroll
-        for (int a = 4; a <= 12; a += 4)
+        for (int a = 4; a < R; a += 4)
 #pragma unroll
-            for (int b = 1; b <= 3; ++b) tw[a + b] = cmul(tw[a], tw[b]);
+            for (int b = 1; b <= 3; ++b)
+                if (a + b < R) tw[a + b] = cmul(tw[a], tw[b]);
     } else {
         if constexpr (R > 2) tw[2] = cmul(tw[1], tw[1]);
         if constexpr (R > 3) tw[3] = cmul(tw[1], tw[2]);
@@ -457,11 +496,326 @@ __device__ inline void stockham_pass(int buf_off, int lbufp, int nf, const PassD
     stockham_pass_impl<T, R, CAP, BHAT>(buf_off, lbufp, nf, pd, (GlobalC2<T> *)Wg, (GlobalC2<T> *)bhat);
 }
 
-// Radices above the register butterflies run as the general prime pass.
-template <typename T>
-__host__ __device__ constexpr bool is_gp_radix(int R)
+// Twiddles (for Ns > 1) and radix-R butterfly of v, from the twiddle table
+// values w1 and w2 of the butterfly.
+template <typename T, int R>
+__device__ inline void twiddled_dft(C2<T> *v, int Ns, C2<T> w1, C2<T> w2)
 {
-    return R > (sizeof(T) == 4 ? 23 : 17);
+    if (Ns > 1) {
+        C2<T> tw[R];
+        twiddle_powers<T, R>(tw, w1, w2);
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[r] = cmul(v[r], tw[r]);
+    }
+    dft_reg<T, R>(v);
+}
+
+// The first and last passes of a ring's FFT join the kernels' global reads and
+// writes: a pass of its own costs every value an LDS write, an LDS read, two
+// barriers and the index arithmetic of a separate loop.  Measured on 64 rings
+// of 5120 points (half-length 10 x 16 x 16), 411 fields: c2r 2.64 -> 2.22 and
+// r2c 2.65 -> 1.99 ps per grid point; all of O1280 (most of it prime passes,
+// which only the last pass helps) 12.34 -> 11.50 and 12.28 -> 11.33 ms.  What
+// remains on such a ring is half memory traffic (6 bytes a point, 1.2 ps at the
+// copy rate) and half vector instructions (94 per complex value).  None of
+// these passes needs its butterflies held over a barrier (they read or write
+// LDS, not both), so a thread takes its butterflies in runs of NB, whose loads
+// are issued together.
+
+template <typename T>
+using GlobalReal = __attribute__((address_space(1))) T;
+template <typename T>
+using GlobalOut = __attribute__((address_space(1))) C2<T>;
+template <typename T>
+__device__ inline C2<T> ldg(GlobalC2<T> *p)
+{
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    const V2 w = *(const __attribute__((address_space(1))) V2 *)p;
+    return C2<T>{w.x, w.y};
+}
+template <typename T>
+__device__ inline void stg(GlobalOut<T> *p, C2<T> v)
+{
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    *(__attribute__((address_space(1))) V2 *)p = V2{v.x, v.y};
+}
+
+// Values the fused passes share: the block's fields and, on the grid side,
+// its first field's grid row of the ring (field f at grid + f npts) and the
+// chirp of a Bluestein ring; on the Fourier side, its first field's column of
+// the ring's Fourier rows ((m, f) at four[m nfld + f]) and e^{-2 pi i m / n}.
+template <typename T>
+struct GridSide {
+    int lbufp, nf, h;
+    unsigned npts;
+    GlobalReal<T> *grid;
+    GlobalC2<T> *chirp;
+};
+template <typename T>
+struct FourSide {
+    int lbufp, nf, h, M;
+    unsigned nfld, mg_nf;
+    GlobalOut<T> *four;
+    GlobalC2<T> *post;
+};
+template <typename P>
+__device__ inline P *uni(P *p)
+{
+    const uint64_t x = (uint64_t)(uintptr_t)p;
+    return (P *)(uintptr_t)(((uint64_t)uni((unsigned)(x >> 32)) << 32) | uni((unsigned)x));
+}
+
+// First pass of the r2c FFT (Ns = 1): butterfly j of field f reads
+// z_i = g_{2i} + i g_{2i+1}, i = j + r nbf, from the grid row (consecutive
+// lanes take consecutive i) and writes LDS.  BLUE: times the chirp, zero for
+// i >= h.
+template <typename T, int R, bool BLUE>
+__device__ __attribute__((noinline)) void pass_from_grid(GridSide<T> g, PassDesc pd)
+{
+    constexpr int NB = R >= 16 ? 1 : 16 / R;
+    constexpr unsigned CB = sizeof(C2<T>);
+    pd = uniform(pd);
+    const int lbufp = uni(g.lbufp), nf = uni(g.nf), h = uni(g.h), nbf = pd.nbf, total = nf * nbf;
+    const unsigned npts = uni(g.npts);
+    GlobalReal<T> *grid = uni(g.grid);
+    GlobalC2<T> *chirp = uni(g.chirp);
+    for (int e0 = threadIdx.x; e0 < total; e0 += NB * kFftThreads) {
+        C2<T> v[NB][R];
+        int at[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int e = e0 + b * kFftThreads;
+            at[b] = -1;
+            if (e < total) {
+                const int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
+                at[b] = f * lbufp + j * R;
+                GlobalC2<T> *src = (GlobalC2<T> *)(grid + (uint64_t)(unsigned)f * npts);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const unsigned i = (unsigned)(j + r * nbf);
+                    v[b][r] = C2<T>{T(0), T(0)};
+                    if (!BLUE || i < (unsigned)h) v[b][r] = ldg<T>(src + i);
+                }
+                if constexpr (BLUE) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const unsigned i = (unsigned)(j + r * nbf);
+                        if (i < (unsigned)h) v[b][r] = cmul(v[b][r], ldg<T>(chirp + i));
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (at[b] < 0) continue;
+            dft_reg<T, R>(v[b]);
+            const unsigned a0 = (unsigned)at[b] * CB;
+#pragma unroll
+            for (int r = 0; r < R; ++r) stb<T>(a0 + r * CB, v[b][r]);
+        }
+    }
+    __syncthreads();
+}
+
+// Last pass of the c2r FFT (Ns = nbf): z = conj(DFT), its real parts the even
+// samples and its imaginary parts the odd ones, straight to the grid row.
+// BLUE: the first h outputs of Bluestein's second FFT, conjugated and times
+// the chirp.
+template <typename T, int R, bool BLUE>
+__device__ __attribute__((noinline)) void pass_to_grid(GridSide<T> g, PassDesc pd, GlobalC2<T> *W, T scale)
+{
+    constexpr int NB = R >= 8 || BLUE ? 1 : 8 / R;
+    constexpr int C2ND = twiddle_step2<R>();
+    constexpr unsigned CB = sizeof(C2<T>);
+    pd = uniform(pd);
+    const int lbufp = uni(g.lbufp), nf = uni(g.nf), h = uni(g.h), nbf = pd.nbf, total = nf * nbf;
+    const unsigned npts = uni(g.npts), srd = nbf * CB;
+    GlobalReal<T> *grid = uni(g.grid);
+    GlobalC2<T> *chirp = uni(g.chirp);
+    for (int e0 = threadIdx.x; e0 < total; e0 += NB * kFftThreads) {
+        C2<T> v[NB][R], w1[NB], w2[NB];
+        int ff[NB], jj[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int e = e0 + b * kFftThreads;
+            ff[b] = -1;
+            if (e < total) {
+                const int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
+                ff[b] = f;
+                jj[b] = j;
+                if (nbf > 1) {
+                    w1[b] = ldg<T>(W + (unsigned)j);
+                    if constexpr (C2ND > 0) w2[b] = ldg<T>(W + (unsigned)(C2ND * j));
+                }
+                const unsigned a0 = (unsigned)(f * lbufp + j) * CB;
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (ff[b] < 0) continue;
+            twiddled_dft<T, R>(v[b], nbf, w1[b], w2[b]);
+            GlobalOut<T> *dst = (GlobalOut<T> *)(grid + (uint64_t)(unsigned)ff[b] * npts);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned i = (unsigned)(jj[b] + r * nbf);
+                if constexpr (BLUE) {
+                    // four chirp values in registers at a time
+                    if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+                    if (i < (unsigned)h) {
+                        const C2<T> z = cmul(ldg<T>(chirp + i), cconj(v[b][r]));
+                        stg<T>(dst + i, C2<T>{scale * z.x, -scale * z.y});
+                    }
+                } else {
+                    stg<T>(dst + i, C2<T>{scale * v[b][r].x, -scale * v[b][r].y});
+                }
+            }
+        }
+    }
+}
+
+// Merge step of the c2r transform for the pair (m, h - m): from y0 = Y_m and
+// y1 = Y_{h-m} (the latter zero for m = 0) and pst = e^{-2 pi i m / n},
+//   Z'_m = (Y_m + conj Y_{h-m}) + i e^{2 pi i m / n} (Y_m - conj Y_{h-m})
+// and its mirror; y0 and y1 become conj Z'_m and conj Z'_{h-m}.
+template <typename T>
+__device__ inline void merge_pair(C2<T> &y0, C2<T> &y1, C2<T> pst)
+{
+    const C2<T> A = {y0.x + y1.x, y0.y - y1.y}, B = {y0.x - y1.x, y0.y + y1.y};
+    const C2<T> t = cmul(cconj(pst), B);
+    y0 = {A.x - t.y, -A.y - t.x};
+    y1 = {A.x + t.y, A.y - t.x};
+}
+
+// First pass of the c2r FFT (Ns = 1) with the merge step: a thread takes the
+// butterflies u and nbf - u of one field, whose inputs are each other's
+// mirrors (h - (u + r nbf) = (nbf - u) + (R - 1 - r) nbf), so that every
+// Fourier value is read once and merged in registers.  Consecutive lanes take
+// consecutive fields of a row (the runs in memory).  y0_fac: factor of Y_0.
+template <typename T, int R>
+__device__ __attribute__((noinline)) void pass_from_four(FourSide<T> g, PassDesc pd, T y0_fac)
+{
+    constexpr int NB = R >= 8 ? 1 : 8 / R;
+    constexpr unsigned CB = sizeof(C2<T>);
+    pd = uniform(pd);
+    const int lbufp = uni(g.lbufp), nf = uni(g.nf), M = uni(g.M), nbf = pd.nbf, total = nf * (nbf / 2 + 1);
+    const unsigned nfld = uni(g.nfld), mg_nf = uni(g.mg_nf);
+    GlobalC2<T> *four = (GlobalC2<T> *)uni(g.four), *post = uni(g.post);
+    for (int e0 = threadIdx.x; e0 < total; e0 += NB * kFftThreads) {
+        C2<T> ya[NB][R], yb[NB][R], ps[NB][R];
+        int uu[NB], ff[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int e = e0 + b * kFftThreads;
+            uu[b] = -1;
+            if (e < total) {
+                const int u = udiv(e, mg_nf), f = e - u * nf;
+                uu[b] = u;
+                ff[b] = f;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int m = u + r * nbf, q = nbf - u + r * nbf;
+                    ya[b][r] = C2<T>{T(0), T(0)};
+                    yb[b][r] = C2<T>{T(0), T(0)};
+                    if (m <= M) ya[b][r] = ldg<T>(four + ((unsigned)m * nfld + (unsigned)f));
+                    if (q <= M) yb[b][r] = ldg<T>(four + ((unsigned)q * nfld + (unsigned)f));
+                    ps[b][r] = ldg<T>(post + (unsigned)m);
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int u = uu[b];
+            if (u < 0) continue;
+            if (u == 0) ya[b][0] = C2<T>{ya[b][0].x * y0_fac, T(0)};
+#pragma unroll
+            for (int r = 0; r < R; ++r) merge_pair(ya[b][r], yb[b][R - 1 - r], ps[b][r]);
+            dft_reg<T, R>(ya[b]);
+            const unsigned a0 = (unsigned)(ff[b] * lbufp + u * R) * CB;
+#pragma unroll
+            for (int r = 0; r < R; ++r) stb<T>(a0 + r * CB, ya[b][r]);
+            if (u > 0 && 2 * u < nbf) {
+                dft_reg<T, R>(yb[b]);
+                const unsigned a1 = (unsigned)(ff[b] * lbufp + (nbf - u) * R) * CB;
+#pragma unroll
+                for (int r = 0; r < R; ++r) stb<T>(a1 + r * CB, yb[b][r]);
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// One Fourier value of the r2c transform to its row, and its magnitude to the
+// field's maximum (smax: LDS words per field, or null).
+typedef __attribute__((address_space(3))) unsigned LdsWord;
+template <typename T>
+__device__ inline void put_four(GlobalOut<T> *four, unsigned nfld, int m, int f, C2<T> y, LdsWord *smax)
+{
+    stg<T>(four + ((unsigned)m * nfld + (unsigned)f), y);
+    if (smax)
+        __hip_atomic_fetch_max(smax + f, __float_as_uint((float)fmax(fabs(y.x), fabs(y.y))), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Last pass of the r2c FFT (Ns = nbf) with the split step
+//   Y_m = (Z_m + conj Z_{h-m}) / 2 - (i/2) e^{-2 pi i m / n} (Z_m - conj Z_{h-m}):
+// a thread takes the butterflies k and nbf - k of one field, whose outputs
+// are each other's mirrors, and writes the kept Y_m (m <= M) to the Fourier
+// rows.  scale0 / scale: half the transform's factor at m = 0 / m > 0.
+template <typename T, int R>
+__device__ __attribute__((noinline)) void pass_to_four(FourSide<T> g, PassDesc pd, GlobalC2<T> *W, T scale0, T scale,
+                                                       LdsWord *smax)
+{
+    constexpr int C2ND = twiddle_step2<R>();
+    constexpr unsigned CB = sizeof(C2<T>);
+    pd = uniform(pd);
+    const int lbufp = uni(g.lbufp), nf = uni(g.nf), M = uni(g.M), h = uni(g.h), nbf = pd.nbf,
+              total = nf * (nbf / 2 + 1);
+    const unsigned nfld = uni(g.nfld), mg_nf = uni(g.mg_nf), srd = nbf * CB;
+    GlobalOut<T> *four = uni(g.four);
+    GlobalC2<T> *post = uni(g.post);
+    for (int e = threadIdx.x; e < total; e += kFftThreads) {
+        const int k = udiv(e, mg_nf), f = e - k * nf, kb = k ? nbf - k : 0;
+        C2<T> va[R], vb[R], ps[R], wa{}, wa2{}, wb{}, wb2{};
+        if (nbf > 1) {
+            wa = ldg<T>(W + (unsigned)k);
+            wb = ldg<T>(W + (unsigned)kb);
+            if constexpr (C2ND > 0) {
+                wa2 = ldg<T>(W + (unsigned)(C2ND * k));
+                wb2 = ldg<T>(W + (unsigned)(C2ND * kb));
+            }
+        }
+        const unsigned a0 = (unsigned)(f * lbufp + k) * CB, a1 = (unsigned)(f * lbufp + kb) * CB;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            va[r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
+            vb[r] = ldb<T>(a1 + __umul24((unsigned)r, srd));
+        }
+        twiddled_dft<T, R>(va, nbf, wa, wa2);
+        __builtin_amdgcn_sched_barrier(0);  // one butterfly's twiddles in registers at a time
+        twiddled_dft<T, R>(vb, nbf, wb, wb2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) ps[r] = ldg<T>(post + (unsigned)(k + r * nbf));
+        // k = 0 mirrors itself: Z_{h - t nbf} = Z_{(R - t) nbf}
+        if (k == 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) vb[r] = va[(r + 1) % R];
+        }
+        const bool mirror = k > 0 && 2 * k < nbf;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int m = k + r * nbf;
+            const C2<T> zm = va[r], zq = vb[R - 1 - r];
+            const C2<T> A = {zm.x + zq.x, zm.y - zq.y}, B = {zm.x - zq.x, zm.y + zq.y};
+            const C2<T> t = cmul(ps[r], B);
+            const T s = m == 0 ? scale0 : scale;
+            if (m <= M) put_four<T>(four, nfld, m, f, C2<T>{s * (A.x + t.y), m == 0 ? T(0) : s * (A.y - t.x)}, smax);
+            if (mirror && h - m <= M)
+                put_four<T>(four, nfld, h - m, f, C2<T>{s * (A.x - t.y), s * (-A.y - t.x)}, smax);
+        }
+    }
 }
 
 // General prime pass (radix p = pd.R, an odd prime, first pass so Ns = 1 and
@@ -643,69 +997,84 @@ __device__ __attribute__((noinline)) void gp_pass(int buf_off, int lbufp, int nf
     __syncthreads();
 }
 
+// Calls fn(std::integral_constant<int, R>) for the radix R of a pass of one
+// kind (the plan checks hold every pass to fft_radix_ok).
+template <int KIND, bool DBL, typename Fn>
+__device__ inline void radix_dispatch(int R, Fn fn)
+{
+#define SHTX_RADIX(X)                                                             \
+    case X:                                                                       \
+        if constexpr (fft_radix_ok(KIND, DBL, X)) fn(std::integral_constant<int, X>{}); \
+        break;
+    switch (R) {
+        SHTX_RADIX(2)
+        SHTX_RADIX(3)
+        SHTX_RADIX(4)
+        SHTX_RADIX(5)
+        SHTX_RADIX(6)
+        SHTX_RADIX(7)
+        SHTX_RADIX(8)
+        SHTX_RADIX(9)
+        SHTX_RADIX(10)
+        SHTX_RADIX(11)
+        SHTX_RADIX(12)
+        SHTX_RADIX(13)
+        SHTX_RADIX(14)
+        SHTX_RADIX(15)
+        SHTX_RADIX(16)
+        SHTX_RADIX(17)
+        SHTX_RADIX(18)
+        SHTX_RADIX(19)
+        SHTX_RADIX(20)
+        SHTX_RADIX(23)
+        SHTX_RADIX(24)
+    }
+#undef SHTX_RADIX
+}
+
 template <typename T, int CAP, bool BHAT>
 __device__ inline void pass_dispatch(int buf_off, int lbufp, int nf, const PassDesc &pd, const C2<T> *W,
                                      const C2<T> *bhat)
 {
     if constexpr (BHAT) {
-        // Bluestein lengths are 2^a 3^b with 9 | L and the radix-9 passes first
-        // (checked on the host), so the filter pass is always radix 9
+        // Bluestein lengths start with a radix-9 pass (checked on the host), so
+        // the filter pass is always radix 9
         stockham_pass<T, 9, CAP, true>(buf_off, lbufp, nf, pd, W, bhat);
         return;
     }
-    if (is_gp_radix<T>(pd.R)) {
+    if (gp_radix(pd.R, sizeof(T) == 8)) {
         gp_pass<T>(buf_off, lbufp, nf, pd, (GlobalC2<T> *)W);
         return;
     }
-    switch (pd.R) {
-    case 2: stockham_pass<T, 2, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 3: stockham_pass<T, 3, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 4: stockham_pass<T, 4, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 5: stockham_pass<T, 5, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 7: stockham_pass<T, 7, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 11: stockham_pass<T, 11, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 13: stockham_pass<T, 13, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 17: stockham_pass<T, 17, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    // FP64 plans stop at radix 17 (larger FP64 butterflies would not fit the
-    // registers); the host never plans the radices below for them
-    case 19:
-        if constexpr (sizeof(T) == 4) stockham_pass<T, 19, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat);
-        break;
-    case 23:
-        if constexpr (sizeof(T) == 4) stockham_pass<T, 23, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat);
-        break;
-
-    case 9: stockham_pass<T, 9, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    case 16: stockham_pass<T, 16, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    default: stockham_pass<T, 8, CAP, BHAT>(buf_off, lbufp, nf, pd, W, bhat); break;
-    }
+    radix_dispatch<kPassLds, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+        stockham_pass<T, decltype(r)::value, CAP, false>(buf_off, lbufp, nf, pd, W, bhat);
+    });
 }
 
-// Length-h forward DFT of the h values at the start of each field slot.
-// Plain: a Stockham FFT of length h.  Bluestein: the input must already be
-// multiplied by the chirp and zero-padded to L; the second FFT's first pass
-// applies the filter (conj(X bhat)) to the first FFT's output, the second FFT
-// leaves conj(conv), and the caller multiplies by the chirp when reading the
-// first h outputs.
+// Passes first .. last - 1 of the length-L FFT of each field slot (the plain
+// FFT, or Bluestein's first), then, for Bluestein, the passes of its second
+// FFT up to last - 1: the input must already be multiplied by the chirp and
+// zero-padded to L; the second FFT's first pass applies the filter
+// (conj(X bhat)) to the first FFT's output, the second FFT leaves conj(conv),
+// and the caller multiplies by the chirp when reading the first h outputs.
 template <typename T, int CAP>
-__device__ void dft_h(int buf_off, const RingDesc &d, const PassDesc *passes, int nf, const C2<T> *W,
-                      const C2<T> *bhat)
+__device__ inline void dft_passes(const RingDesc &d, const PassDesc *ps, int nrad, int first, int last, int nf,
+                                  const C2<T> *W, const C2<T> *bhat)
 {
-    const PassDesc *ps = passes + d.pass_off;
-    for (int s = 0; s < d.nrad; ++s) {
+    const int end1 = d.blue ? nrad : last;
+    for (int s = first; s < end1; ++s) {
         const PassDesc pd = ps[s];
-        pass_dispatch<T, CAP, false>(buf_off, d.lbufp, nf, pd, W, bhat);
+        pass_dispatch<T, CAP, false>(0, d.lbufp, nf, pd, W, bhat);
     }
     if (d.blue)
-        for (int s = 0; s < d.nrad; ++s) {
+        for (int s = 0; s < last; ++s) {
             const PassDesc pd = ps[s];
             if (s == 0)
-                pass_dispatch<T, CAP, true>(buf_off, d.lbufp, nf, pd, W, bhat);
+                pass_dispatch<T, CAP, true>(0, d.lbufp, nf, pd, W, bhat);
             else
-                pass_dispatch<T, CAP, false>(buf_off, d.lbufp, nf, pd, W, bhat);
+                pass_dispatch<T, CAP, false>(0, d.lbufp, nf, pd, W, bhat);
         }
 }
-
 
 // A ring's grid rows can be moved two complex values (four points) at a time
 // with 16-byte accesses: no chirp, even h, and every field's row of the ring
@@ -716,41 +1085,20 @@ __device__ inline bool grid_pairs(const RingDesc &d, int h, unsigned npts, const
     return !d.blue && (h & 1) == 0 && (npts & 3u) == 0 && (reinterpret_cast<uintptr_t>(row0) & 15) == 0;
 }
 
-template <typename T, int CAP>
-__global__ __launch_bounds__(kFftThreads, 2) void k_fft_c2r(FftArgs a)
+// The c2r kernel's reads of the kept coefficients Y_m, Y_{h-m} (m <= M) where
+// its first pass does not take them itself (general prime passes, Bluestein):
+// merged into u = conj(Z') in LDS, for Bluestein times the chirp and
+// zero-padded to L.  Runs over fields are contiguous in memory; each thread
+// issues the loads of kU elements before using any.
+template <typename T>
+__device__ inline void merge_to_lds(const RingDesc &d, const C2<T> *fourb, unsigned nfld, int nf, unsigned mg_nf,
+                                    const C2<T> *post, const C2<T> *chirp, T y0_fac)
 {
     LdsC2<T> *buf = lds_c2<T>();
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const FftItem it = a.items[item];
-    if (it.ring < 0) return;
-    const RingDesc d = a.rings[it.ring];
-    const C2<T> *tw = (const C2<T> *)a.twid;
-    const C2<T> *W = tw + d.tw_off;
-    const C2<T> *post = tw + d.post_off;
-    const C2<T> *chirp = tw + d.chirp_off, *bhat = tw + d.bhat_off;
-    const int nf = it.nf, f0 = it.f0, h = d.h, M = d.M, lbufp = d.lbufp;
-    const C2<T> *four = (const C2<T> *)a.in + d.four_off;
-    const T facpos = a.adjoint ? T(0.5) : T(1);
-    const unsigned mg_nf = div_magic(nf);
-    const int buf_off = 0;
-
-    // 1. read the kept coefficients Y_m, Y_{h-m} (m <= M) and merge them into
-    //    the length-h sequence u = conj(Z'), Z'_m = (Y_m + conj Y_{h-m})
-    //    + i e^{2 pi i m / n} (Y_m - conj Y_{h-m}); Bluestein: times the chirp
-    //    and zero-padded to L.  Runs over fields are contiguous in memory.
-    //    Each thread issues the loads of kU elements before using any.
-    auto zprime = [&](C2<T> a1, C2<T> a2, C2<T> pst, C2<T> chp) {
-        C2<T> A = cadd(a1, cconj(a2)), B = csub(a1, cconj(a2));
-        C2<T> t = cmul(cconj(pst), B);
-        C2<T> z = {A.x - t.y, A.y + t.x};
-        C2<T> u = cconj(z);
-        return d.blue ? cmul(u, chp) : u;
-    };
+    const int h = d.h, M = d.M, lbufp = d.lbufp;
     const int hp = h / 2 + 1, nmerge = nf * hp;
-    const unsigned nfld = (unsigned)a.nfld;
-    const C2<T> *fourb = four + f0;  // (m, f) at fourb[m nfld + f]
     for (int e0 = threadIdx.x; e0 < nmerge; e0 += kU * kFftThreads) {
-        C2<T> ym[kU], yh[kU], pm[kU], ph[kU], cm[kU], ch[kU];
+        C2<T> ym[kU], yh[kU], pm[kU], cm[kU];
         int mm[kU], ff[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -766,30 +1114,25 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_c2r(FftArgs a)
             // 32-bit unsigned element offsets from the block's base pointers
             if (ok && m <= M) ym[u] = fourb[(unsigned)m * nfld + (unsigned)f];
             if (ok && h - m <= M) yh[u] = fourb[(unsigned)(h - m) * nfld + (unsigned)f];
-            // e^{-2 pi i (h - m) / n} = -conj(e^{-2 pi i m / n}); the chirp at h - m
-            // is the chirp at m times (-1)^h (m > 0)
             pm[u] = post[(unsigned)m];
-            ph[u] = C2<T>{-pm[u].x, pm[u].y};
             cm[u] = zero;
-            ch[u] = zero;
-            if (d.blue) {
-                cm[u] = chirp[(unsigned)m];
-                ch[u] = (m > 0 && (h & 1)) ? C2<T>{-cm[u].x, -cm[u].y} : cm[u];
-            }
+            if (d.blue) cm[u] = chirp[(unsigned)m];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int m = mm[u];
             if (m < 0) continue;
             C2<T> y0 = ym[u], y1 = yh[u];
-            if (m == 0)
-                y0.y = T(0);
-            else
-                y0 = {y0.x * facpos, y0.y * facpos};
-            y1 = {y1.x * facpos, y1.y * facpos};
+            if (m == 0) y0 = {y0.x * y0_fac, T(0)};
+            merge_pair(y0, y1, pm[u]);
+            if (d.blue) {
+                // the chirp at h - m is the chirp at m times (-1)^h (m > 0)
+                y0 = cmul(y0, cm[u]);
+                y1 = cmul(y1, (h & 1) ? C2<T>{-cm[u].x, -cm[u].y} : cm[u]);
+            }
             LdsC2<T> *sl = buf + ff[u] * lbufp;
-            if (m != 0 && m != h - m) stc(sl + (h - m), zprime(y1, y0, ph[u], ch[u]));
-            stc(sl + m, zprime(y0, y1, pm[u], cm[u]));
+            if (m != 0 && m != h - m) stc(sl + (h - m), y1);
+            stc(sl + m, y0);
         }
     }
     if (d.blue) {
@@ -801,12 +1144,53 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_c2r(FftArgs a)
         }
     }
     __syncthreads();
-    // 2. forward DFT of length h
-    dft_h<T, CAP>(buf_off, d, a.passes, nf, W, bhat);
-    // 3. z = conj(DFT(u)): even samples Re z, odd samples Im z
-    const T scale = a.adjoint ? T(d.w / (2.0 * d.n)) : T(1);
-    const unsigned npts = (unsigned)a.npts;
-    T *gridb = (T *)a.out + (uint64_t)f0 * npts + d.grid_off;  // field f at gridb + f npts
+}
+
+template <typename T, int CAP>
+__global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r(FftArgs a)
+{
+    LdsC2<T> *buf = lds_c2<T>();
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    const FftItem it = a.items[item];
+    if (it.ring < 0) return;
+    const RingDesc d = a.rings[it.ring];
+    const C2<T> *tw = (const C2<T> *)a.twid;
+    const C2<T> *W = tw + d.tw_off;
+    const C2<T> *post = tw + d.post_off;
+    const C2<T> *chirp = tw + d.chirp_off, *bhat = tw + d.bhat_off;
+    const int nf = it.nf, f0 = it.f0, h = d.h, M = d.M, lbufp = d.lbufp;
+    const unsigned nfld = (unsigned)a.nfld, npts = (unsigned)a.npts;
+    const C2<T> *fourb = (const C2<T> *)a.in + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
+    T *gridb = (T *)a.out + (uint64_t)f0 * npts + d.grid_off;    // field f at gridb + f npts
+    const unsigned mg_nf = div_magic(nf);
+    // the adjoint's Y_m = F_m / c_m: Y_0 doubled, the halves in the scale
+    const T y0_fac = a.adjoint ? T(2) : T(1);
+    const T scale = a.adjoint ? T(d.w / (4.0 * d.n)) : T(1);
+    const PassDesc *ps = a.passes + d.pass_off;
+    if (d.fuse_in) {
+        const FourSide<T> fs{lbufp, nf, h, M, nfld, mg_nf, (GlobalOut<T> *)fourb, (GlobalC2<T> *)post};
+        const PassDesc pd = ps[0];
+        radix_dispatch<kPassFromFour, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+            pass_from_four<T, decltype(r)::value>(fs, pd, y0_fac);
+        });
+    } else {
+        merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, y0_fac);
+    }
+    // forward DFT of length h; z = conj(DFT(u)): even samples Re z, odd samples Im z
+    dft_passes<T, CAP>(d, ps, d.nrad, d.fuse_in, d.nrad - d.fuse_out, nf, W, bhat);
+    if (d.fuse_out) {
+        const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
+        const PassDesc pd = ps[d.nrad - 1];
+        radix_dispatch<kPassToGrid, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+            constexpr int R = decltype(r)::value;
+            if constexpr (blue_last_radix(R)) {
+                if (d.blue) return pass_to_grid<T, R, true>(gs, pd, (GlobalC2<T> *)W, scale);
+            }
+            pass_to_grid<T, R, false>(gs, pd, (GlobalC2<T> *)W, scale);
+        });
+        return;
+    }
+
     // single precision, no chirp, even h and 16-byte aligned rows: two complex
     // values (four grid points) per element with one 16-byte store
     if (sizeof(T) == 4 && grid_pairs(d, h, npts, gridb)) {
@@ -849,7 +1233,7 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_c2r(FftArgs a)
 }
 
 template <typename T, int CAP>
-__global__ __launch_bounds__(kFftThreads, 2) void k_fft_r2c(FftArgs a)
+__global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c(FftArgs a)
 {
     LdsC2<T> *buf = lds_c2<T>();
     const int item = xcd_remap(blockIdx.x, gridDim.x);
@@ -863,19 +1247,28 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_r2c(FftArgs a)
     const int nf = it.nf, f0 = it.f0, h = d.h, M = d.M, lbufp = d.lbufp;
     const unsigned npts = (unsigned)a.npts;
     const T *gridb = (const T *)a.in + (uint64_t)f0 * npts + d.grid_off;  // field f at gridb + f npts
-    const int buf_off = 0;
-    __attribute__((address_space(3))) unsigned *smax =
-        (__attribute__((address_space(3))) unsigned *)((LdsByte *)fft_smem + a.fmax_lds);
+    LdsWord *smax = a.fmax ? (LdsWord *)((LdsByte *)fft_smem + a.fmax_lds) : nullptr;
     if (a.fmax)
-        for (int f = threadIdx.x; f < nf; f += kFftThreads) smax[f] = 0u;  // ordered by the barrier below
+        for (int f = threadIdx.x; f < nf; f += kFftThreads) smax[f] = 0u;  // ordered by the first pass's barrier
 
     // 1. z_k = g_{2k} + i g_{2k+1}; Bluestein: times the chirp, zero-padded to L
+    const PassDesc *ps = a.passes + d.pass_off_r;
+    if (d.fuse_in_r) {
+        const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
+        const PassDesc pd = ps[0];
+        if (d.blue)
+            pass_from_grid<T, 9, true>(gs, pd);  // Bluestein lengths start with radix 9
+        else
+            radix_dispatch<kPassFromGrid, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+                pass_from_grid<T, decltype(r)::value, false>(gs, pd);
+            });
+    }
     const int span = d.blue ? d.L : h;
     const unsigned mg_span = div_magic(span);
     // single precision, no chirp, even h and 16-byte aligned rows: four grid
     // points (two complex values) per element with one 16-byte load
     const bool pairs = sizeof(T) == 4 && grid_pairs(d, h, npts, gridb);
-    if (pairs) {
+    if (!d.fuse_in_r && pairs) {
         typedef T V4 __attribute__((ext_vector_type(4)));
         const int hh = h / 2;
         const unsigned mg_hh = div_magic(hh);
@@ -899,7 +1292,7 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_r2c(FftArgs a)
             }
         }
     }
-    for (int e0 = pairs ? nf * span : threadIdx.x; e0 < nf * span; e0 += kU * kFftThreads) {
+    for (int e0 = d.fuse_in_r || pairs ? nf * span : threadIdx.x; e0 < nf * span; e0 += kU * kFftThreads) {
         C2<T> z[kU], cp[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -922,14 +1315,22 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_r2c(FftArgs a)
             stc(buf + f * lbufp + k, d.blue ? cmul(z[u], cp[u]) : z[u]);
         }
     }
-    __syncthreads();
-    dft_h<T, CAP>(buf_off, d, a.passes, nf, W, bhat);
+    if (!d.fuse_in_r) __syncthreads();
+    dft_passes<T, CAP>(d, ps, d.nrad_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, W, bhat);
     // 2. split: Y_m = (Z_m + conj Z_{h-m}) / 2 - (i/2) e^{-2 pi i m / n} (Z_m - conj Z_{h-m})
     const T scale = a.adjoint ? T(1) : T(1.0 / d.n);
     C2<T> *fourb = (C2<T> *)a.out + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
     const unsigned nfld = (unsigned)a.nfld;
     const unsigned mg_nf = div_magic(nf);
-    const int nout = nf * (M + 1);
+    if (d.fuse_out_r) {
+        const FourSide<T> fs{lbufp, nf, h, M, nfld, mg_nf, (GlobalOut<T> *)fourb, (GlobalC2<T> *)post};
+        const PassDesc pd = ps[d.nrad_r - 1];
+        const T s0 = T(0.5) * scale, s1 = a.adjoint ? scale : s0;
+        radix_dispatch<kPassToFour, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+            pass_to_four<T, decltype(r)::value>(fs, pd, (GlobalC2<T> *)W, s0, s1, smax);
+        });
+    }
+    const int nout = d.fuse_out_r ? 0 : nf * (M + 1);
     for (int e0 = threadIdx.x; e0 < nout; e0 += kU * kFftThreads) {
         C2<T> pm[kU], cm[kU], ch[kU];
 #pragma unroll
@@ -959,10 +1360,7 @@ __global__ __launch_bounds__(kFftThreads, 2) void k_fft_r2c(FftArgs a)
             C2<T> y = {T(0.5) * (A.x + t.y), T(0.5) * (A.y - t.x)};
             T fac = (a.adjoint && m > 0) ? T(2) : T(1);
             y = {y.x * scale * fac, m == 0 ? T(0) : y.y * scale * fac};
-            fourb[(unsigned)m * nfld + (unsigned)f] = y;
-            if (a.fmax)
-                __hip_atomic_fetch_max(smax + f, __float_as_uint((float)fmax(fabs(y.x), fabs(y.y))),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            put_four<T>((GlobalOut<T> *)fourb, nfld, m, f, y, smax);
         }
     }
     if (a.fmax) {
@@ -994,45 +1392,56 @@ bool check_fft(const Plan &p, int cap)
         // the kernels index a field's grid row and a ring's Fourier rows with
         // 32-bit unsigned element offsets
         if (p.npts >= (int64_t(1) << 32) || (int64_t)(d.M + 1) * p.nfld >= (int64_t(1) << 32)) SHTX_FFT_FAIL;
-        if (d.pass_off < 0 || d.pass_off + d.nrad > (int)p.passes.size() || d.nrad < 1) SHTX_FFT_FAIL;
-        // the second Bluestein FFT applies the filter in a radix-9 first pass
-        if (d.blue && p.passes[d.pass_off].R != 9) SHTX_FFT_FAIL;
-        int prod = 1, extra = 0;
-        for (int s = 0; s < d.nrad; ++s) {
-            const PassDesc &pd = p.passes[d.pass_off + s];
-            const int R = pd.R;
-            const int code = (int)((d.radcode >> (5 * s)) & 31u);
-            if (R < 2 || d.L % R) SHTX_FFT_FAIL;
-            if (is_gp_radix<T>(R)) {
-                // a general prime pass: the first pass only, an odd prime up to
-                // kGpMaxPrime, at most kGpUnits output units per wave
-                if (s != 0 || code != 0 || R > kGpMaxPrime || R % 2 == 0 || d.blue) SHTX_FFT_FAIL;
-                for (int q = 3; q * q <= R; q += 2)
-                    if (R % q == 0) SHTX_FFT_FAIL;
-                if ((int64_t)gp_row_tiles(R) * gp_col_tiles(d.fb * pd.nbf) >
-                    (int64_t)kGpUnits * (kFftThreads / 64))
-                    SHTX_FFT_FAIL;
-                extra = R;
-            } else {
-                bool ok = R == 4 || R == 8;
-                for (int q : {2, 3, 5, 7, 9, 11, 13, 16, 17}) ok = ok || R == q;
-                ok = ok || ((R == 19 || R == 23) && sizeof(T) == 4);
-                if (!ok || code != R) SHTX_FFT_FAIL;
-                // every butterfly of a block's fields is covered by the pass's rounds
-                if ((int64_t)d.fb * (d.L / R) > (int64_t)fft_rounds(cap, R) * kFftThreads) SHTX_FFT_FAIL;
+        // both directions' pass lists: every pass of a kind with a butterfly for
+        // its radix, and its descriptor exactly that pass
+        int extra = 0;
+        for (int dir = 0; dir < 2; ++dir) {
+            const int off = dir ? d.pass_off_r : d.pass_off, nrad = dir ? d.nrad_r : d.nrad;
+            const int fin = dir ? d.fuse_in_r : d.fuse_in, fout = dir ? d.fuse_out_r : d.fuse_out;
+            if (off < 0 || nrad < 1 || off + nrad > (int)p.passes.size()) SHTX_FFT_FAIL;
+            // fused passes: one pass cannot be both; Bluestein's Fourier side
+            // goes through LDS
+            if ((fin | fout) & ~1 || fin + fout > nrad || (d.blue && (dir ? fout : fin))) SHTX_FFT_FAIL;
+            int prod = 1;
+            for (int s = 0; s < nrad; ++s) {
+                const PassDesc &pd = p.passes[off + s];
+                const int R = pd.R;
+                const bool first = s == 0 && fin, last = s == nrad - 1 && fout;
+                const int kind = first ? (dir ? kPassFromGrid : kPassFromFour)
+                                 : last ? (dir ? kPassToFour : kPassToGrid)
+                                        : kPassLds;
+                if (R < 2 || d.L % R) SHTX_FFT_FAIL;
+                if (gp_radix(R, sizeof(T) == 8)) {
+                    // a general prime pass: the first pass only, an odd prime up to
+                    // kGpMaxPrime, at most kGpUnits output units per wave
+                    if (s != 0 || first || last || R > kGpMaxPrime || R % 2 == 0 || d.blue) SHTX_FFT_FAIL;
+                    for (int q = 3; q * q <= R; q += 2)
+                        if (R % q == 0) SHTX_FFT_FAIL;
+                    if ((int64_t)gp_row_tiles(R) * gp_col_tiles(d.fb * pd.nbf) >
+                        (int64_t)kGpUnits * (kFftThreads / 64))
+                        SHTX_FFT_FAIL;
+                    extra = R;
+                } else {
+                    if (!fft_radix_ok(kind, sizeof(T) == 8, R)) SHTX_FFT_FAIL;
+                    // Bluestein also runs its first and last passes in LDS (at the
+                    // seam of its two FFTs), its first with the filter at radix 9
+                    if (d.blue && last && !blue_last_radix(R)) SHTX_FFT_FAIL;
+                    if (d.blue && (!fft_radix_ok(kPassLds, sizeof(T) == 8, R) || (s == 0 && R != 9))) SHTX_FFT_FAIL;
+                    // every butterfly of a block's fields is covered by the pass's rounds
+                    if ((int64_t)d.fb * (d.L / R) > (int64_t)fft_rounds(cap, R) * kFftThreads) SHTX_FFT_FAIL;
+                }
+                if (pd.Ns != prod || pd.nbf * R != d.L || pd.tstep * prod * R != d.L) SHTX_FFT_FAIL;
+                if (pd.mg_nbf != div_magic(pd.nbf) || pd.mg_ns != div_magic(pd.Ns)) SHTX_FFT_FAIL;
+                // twiddle reads W[c k tstep], k < Ns: c = 1, and 3 for radix 9, 4 for
+                // 10 to 24, 17 for the streamed radix 23
+                const int cmax = R == 23 ? 17 : R == 9 ? 3 : R >= 10 ? 4 : 1;
+                if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= d.L) SHTX_FFT_FAIL;
+                prod *= R;
             }
-            // the pass descriptor must describe exactly this pass
-            if (pd.Ns != prod || pd.nbf * R != d.L || pd.tstep * prod * R != d.L) SHTX_FFT_FAIL;
-            if (pd.mg_nbf != div_magic(pd.nbf) || pd.mg_ns != div_magic(pd.Ns)) SHTX_FFT_FAIL;
-            // twiddle reads W[c k tstep] (c = 1, and 3 or 4 for radix 9 or 16;
-            // 1, 9, 17 for the streamed radix 23), k < Ns
-            const int cmax = R == 16 ? 4 : R == 9 ? 3 : R > 19 ? 17 : 1;
-            if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= d.L) SHTX_FFT_FAIL;
-            prod *= R;
+            if (prod != d.L) SHTX_FFT_FAIL;
         }
         if ((size_t)(d.fb * d.lbufp + extra) * celem > (size_t)p.fft_lds_bytes)
             SHTX_FFT_FAIL;
-        if (prod != d.L) SHTX_FFT_FAIL;
     }
     if (p.prec == SHTX_FP16X3) {
         // the r2c kernel's per-field maxima sit after the block's LDS

@@ -51,10 +51,114 @@ bool is_prime(int n)
     return true;
 }
 
-// Stockham radices for a smooth length: the odd factors first, largest
-// first (the first pass needs no twiddles), with pairs of 3 merged into 9;
-// then the power of two as radix-16 passes and one 8, 4 or 2.
-std::vector<int> radices_for(int L)
+// Cost model of a ring FFT's passes, in vector instructions per complex value
+// (counted from the butterflies' additions and multiply-adds), by which the
+// plan picks a ring length's radices.
+
+// Radix-R butterfly in registers.
+double butterfly_cost(int R)
+{
+    switch (R) {
+    case 2: return 2;
+    case 4: return 4;
+    case 8: return 6.75;
+    case 9: return 11.2;
+    case 16: return 10.2;
+    case 6: case 10: case 14: return 2 + butterfly_cost(R / 2);
+    case 18: return 2 + butterfly_cost(9);
+    case 12: case 20: return 4 + butterfly_cost(R / 4);
+    case 15: return butterfly_cost(3) + butterfly_cost(5);
+    case 24: return butterfly_cost(8) + butterfly_cost(3);
+    }
+    const double H = (R - 1) / 2;  // odd primes, inputs paired
+    return (4 * H * H + 10 * H) / R;
+}
+
+// How often the lanes of a pass's LDS writes meet in a bank pair: the most of
+// 64 consecutive butterflies that fall on one of the 32 pairs, over the two
+// that have to.
+double write_conflicts(int R, int Ns, int nbf)
+{
+    int load[32] = {0}, top = 0, n = std::min(64, nbf);
+    for (int j = 0; j < n; ++j) {
+        const int a = (j / Ns) * Ns * R + j % Ns;
+        top = std::max(top, ++load[a % 32]);
+    }
+    return std::max(1.0, top / 2.0);
+}
+
+// One pass: butterfly and twiddles, per-butterfly index work, and for a pass
+// in LDS its write, its barriers and the conflicts of its writes; a pass that
+// writes to memory needs none of the latter.
+double pass_cost(int R, int Ns, int nbf, bool to_lds)
+{
+    double c = butterfly_cost(R) + 30.0 / R + 4;
+    if (Ns > 1) c += 8.0 * (R - 1) / R;
+    if (to_lds) c += 8 + 3 * (write_conflicts(R, Ns, nbf) - 1);
+    return c;
+}
+
+// The passes of a ring FFT of length L in one direction.
+struct PassPlan {
+    std::vector<int> rad;
+    int fuse_in = 0, fuse_out = 0;
+};
+
+// The cheapest radices for length L after a first pass of radix `lead` (1:
+// none) that ran already, in LDS: every ordered factorisation with a butterfly
+// for each pass's kind, the first pass fused with the kernel's reads and the
+// last with its writes where that radix has such a butterfly.
+PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
+{
+    constexpr double kUnfused = 12;  // a separate loop for the reads or writes
+    const int kin = r2c ? kPassFromGrid : kPassFromFour, kout = r2c ? kPassToFour : kPassToGrid;
+    PassPlan best;
+    double best_cost = 1e300;
+    std::vector<int> cur;
+    auto go = [&](auto &&self, int Ns, double cost, int fuse_in) -> void {
+        if (cost >= best_cost) return;
+        const int left = L / Ns;
+        for (int R = 24; R >= 2; --R) {
+            if (left % R) continue;
+            const int nbf = L / R;
+            const bool last = left == R;
+            cur.push_back(R);
+            auto step = [&](int kind, bool fin, bool fout) {
+                if (!fft_radix_ok(kind, dbl, R)) return;
+                double c = cost + pass_cost(R, Ns, nbf, !fout);
+                if (Ns == 1 && !fin) c += kUnfused;
+                if (last) {
+                    if (!fout) c += kUnfused;
+                    if (c < best_cost) {
+                        best_cost = c;
+                        best.rad = cur;
+                        best.fuse_in = fin || fuse_in;
+                        best.fuse_out = fout;
+                    }
+                } else if ((int)cur.size() < kMaxRadices - 1) {
+                    self(self, Ns * R, c, fin || fuse_in);
+                }
+            };
+            if (Ns == 1 && !last) step(kin, true, false);
+            step(kPassLds, false, false);
+            if (last) step(kout, false, true);
+            cur.pop_back();
+        }
+    };
+    if (lead == L) {
+        best.rad = {lead};
+        return best;
+    }
+    go(go, lead, 0.0, 0);
+    if (lead > 1 && !best.rad.empty()) best.rad.insert(best.rad.begin(), lead);
+    return best;
+}
+
+// Bluestein's radices (both of its FFTs, either direction): radix-9 passes
+// first (the filter pass is a radix-9 one), then a factor 3, the fives and the
+// power of two.  The first pass joins the r2c kernel's reads, the last the c2r
+// kernel's writes.
+PassPlan bluestein_passes(int L, bool r2c, bool dbl)
 {
     std::vector<int> f;
     smooth_factor(L, f);
@@ -71,12 +175,13 @@ std::vector<int> radices_for(int L)
     for (; threes >= 2; threes -= 2) odd.push_back(9);
     if (threes) odd.push_back(3);
     std::sort(odd.rbegin(), odd.rend());
-    std::vector<int> r(odd.begin(), odd.end());
-    for (; twos >= 4; twos -= 4) r.push_back(16);
-    if (twos == 3) r.push_back(8);
-    if (twos == 2) r.push_back(4);
-    if (twos == 1) r.push_back(2);
-    return r;
+    PassPlan p;
+    p.rad.assign(odd.begin(), odd.end());
+    for (; twos >= 4; twos -= 4) p.rad.push_back(16);
+    if (twos) p.rad.push_back(1 << twos);
+    p.fuse_in = r2c && p.rad.size() > 1 && fft_radix_ok(kPassFromGrid, dbl, p.rad.front());
+    p.fuse_out = !r2c && p.rad.size() > 1 && blue_last_radix(p.rad.back());
+    return p;
 }
 
 template <class T>
@@ -197,22 +302,25 @@ int fft_blocking(Plan &p, int cap)
         RingDesc &d = p.rings[j];
         if (d.lbuf > maxcap) return SHTX_EUNSUPPORTED;
         d.fb = std::max(1, std::min(F, cap / d.lbuf));
-        // passes of radix 11 and up run one round of kFftThreads butterflies;
-        // a general prime pass holds at most kGpUnits output units per wave
+        // a general prime pass holds at most kGpUnits output units per wave,
+        // a pass in LDS its rounds of kFftThreads butterflies
         int extra = 0;
-        for (int s = 0; s < d.nrad; ++s) {
-            const PassDesc &q = p.passes[d.pass_off + s];
-            const int R = q.R;
-            int lim;
-            if (R > 23 || (p.prec == SHTX_FP64 && R > 17)) {
-                // units = row tiles x ceil(2 fb nbf / 16)
-                lim = 8 * (kGpUnits * (kFftThreads / 64) / gp_row_tiles(R)) / q.nbf;
-                extra = R;
-            } else {
-                lim = fft_rounds(maxcap, R) * kFftThreads / q.nbf;
+        for (int dir = 0; dir < 2; ++dir) {
+            const int nrad = dir ? d.nrad_r : d.nrad;
+            for (int s = 0; s < nrad; ++s) {
+                const PassDesc &q = p.passes[(dir ? d.pass_off_r : d.pass_off) + s];
+                const int R = q.R;
+                int lim;
+                if (gp_radix(R, p.prec == SHTX_FP64)) {
+                    // units = row tiles x ceil(2 fb nbf / 16)
+                    lim = 8 * (kGpUnits * (kFftThreads / 64) / gp_row_tiles(R)) / q.nbf;
+                    extra = R;
+                } else {
+                    lim = fft_rounds(maxcap, R) * kFftThreads / q.nbf;
+                }
+                if (lim < 1) return SHTX_EUNSUPPORTED;
+                d.fb = std::min(d.fb, lim);
             }
-            if (lim < 1) return SHTX_EUNSUPPORTED;
-            d.fb = std::min(d.fb, lim);
         }
         lds_elems = std::max(lds_elems, d.fb * d.lbufp + extra);
         std::vector<FftItem> g;
@@ -367,8 +475,8 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
     const bool dbl = prec == SHTX_FP64;
     const int cap = dbl ? kFftCapF64 : kFftCapF32;
     struct LenPlan {
-        int L, blue, pass_off;
-        std::vector<int> rad;
+        int L, blue, pass_off[2];  // c2r, r2c
+        PassPlan pass[2];
         int64_t tw, post, chirp, bhat;
     };
     std::map<int, LenPlan> lens;
@@ -418,23 +526,21 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
             lp.blue = 1;
         }
         if (std::max(lp.L, h + 1) > cap) return SHTX_EUNSUPPORTED;
-        if (gp) {
-            lp.rad = radices_for(lp.L / rem);
-            lp.rad.insert(lp.rad.begin(), rem);
-        } else {
-            lp.rad = radices_for(lp.L);
-        }
-        if ((int)lp.rad.size() > kMaxRadices) return SHTX_EUNSUPPORTED;
-        lp.pass_off = (int)p.passes.size();
-        for (int s = 0, Ns = 1; s < (int)lp.rad.size(); Ns *= lp.rad[s], ++s) {
-            PassDesc q{};
-            q.R = lp.rad[s];
-            q.Ns = Ns;
-            q.nbf = lp.L / q.R;
-            q.tstep = lp.L / (Ns * q.R);
-            q.mg_nbf = div_magic(q.nbf);
-            q.mg_ns = div_magic(Ns);
-            p.passes.push_back(q);
+        for (int dir = 0; dir < 2; ++dir) {
+            PassPlan &pp = lp.pass[dir];
+            pp = lp.blue ? bluestein_passes(lp.L, dir == 1, dbl) : plan_passes(lp.L, gp ? rem : 1, dir == 1, dbl);
+            if (pp.rad.empty() || (int)pp.rad.size() > kMaxRadices) return SHTX_EUNSUPPORTED;
+            lp.pass_off[dir] = (int)p.passes.size();
+            for (int s = 0, Ns = 1; s < (int)pp.rad.size(); Ns *= pp.rad[s], ++s) {
+                PassDesc q{};
+                q.R = pp.rad[s];
+                q.Ns = Ns;
+                q.nbf = lp.L / q.R;
+                q.tstep = lp.L / (Ns * q.R);
+                q.mg_nbf = div_magic(q.nbf);
+                q.mg_ns = div_magic(Ns);
+                p.passes.push_back(q);
+            }
         }
         auto push = [&](long double re, long double im) {
             pool.push_back(re);
@@ -480,14 +586,14 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         d.M = p.cutoff[j];
         d.L = lp.L;
         d.blue = lp.blue;
-        d.nrad = (int)lp.rad.size();
-        d.pass_off = lp.pass_off;
-        d.radcode = 0;
-        // code 0 marks a general prime pass (its radix is in the pass descriptor)
-        for (int r = 0; r < d.nrad; ++r) {
-            const bool gp = lp.rad[r] > (prec == SHTX_FP64 ? 17 : 23);
-            d.radcode |= (unsigned long long)(gp ? 0 : lp.rad[r]) << (5 * r);
-        }
+        d.nrad = (int)lp.pass[0].rad.size();
+        d.nrad_r = (int)lp.pass[1].rad.size();
+        d.pass_off = lp.pass_off[0];
+        d.pass_off_r = lp.pass_off[1];
+        d.fuse_in = lp.pass[0].fuse_in;
+        d.fuse_out = lp.pass[0].fuse_out;
+        d.fuse_in_r = lp.pass[1].fuse_in;
+        d.fuse_out_r = lp.pass[1].fuse_out;
         d.lbuf = std::max(d.L, d.h + 1);
         d.lbufp = d.lbuf;
         d.tw_off = lp.tw;

@@ -21,14 +21,40 @@ constexpr int kFftCapF32 = 8192;  // 64 KiB: two blocks per CU with the prime-pa
 constexpr int kFftCapF64 = 8192;  // 128 KiB: one block per CU (the FP64 passes use 228 VGPRs)
 constexpr int kFftThreads = 512;
 
-// Butterflies per thread in a radix-R Stockham pass (rounds of kFftThreads):
-// enough for a block's cap complex values for radices below 11; radices 11
-// and up take one round, and the blocking keeps a block's fields within it
-// (they only occur in rings whose whole FFT is a direct one).
+// Butterflies per thread in an in-place radix-R Stockham pass (rounds of
+// kFftThreads): enough for a block's cap complex values, but one round from
+// radix 13 on (a second would spill), to which the blocking keeps a block's
+// fields.
 __host__ __device__ constexpr int fft_rounds(int cap, int R)
 {
-    return R >= 11 ? 1 : (cap / R + kFftThreads - 1) / kFftThreads;
+    return R >= 13 ? 1 : (cap / R + kFftThreads - 1) / kFftThreads;
 }
+
+// Kinds of Stockham pass, by where the pass reads and writes: LDS to LDS in
+// place; the r2c kernel's first pass, from the grid row; the c2r kernel's first
+// pass, from the Fourier rows with the merge step; the c2r kernel's last pass,
+// to the grid row; the r2c kernel's last pass, with the split step to the
+// Fourier rows.
+enum FftPassKind { kPassLds = 0, kPassFromGrid = 1, kPassFromFour = 2, kPassToGrid = 3, kPassToFour = 4 };
+
+// Radices with a butterfly of each kind.  The Fourier-side passes hold a pair of
+// butterflies (j and its mirror) per thread, so their radices stop earlier;
+// FP64 values take twice the registers.  The sets end where the butterfly would
+// spill at the two blocks (FP64: one) per CU that the LDS allows.
+__host__ __device__ constexpr bool fft_radix_ok(int kind, bool dbl, int R)
+{
+    if (R < 2) return false;
+    switch (kind) {
+    case kPassLds: return R <= 13 || R == 16 || R == 17 || (!dbl && (R == 19 || R == 23));
+    case kPassFromGrid: return R <= 13 || R == 16 || (!dbl && (R == 15 || R == 17));
+    case kPassFromFour: return R <= (dbl ? 9 : 10);
+    case kPassToGrid: return R <= 10 || R == 12 || R == 16 || (!dbl && (R == 14 || R == 15 || R == 18 || R == 20));
+    case kPassToFour: return R <= 6 || R == 8 || (!dbl && (R == 7 || R == 9));
+    }
+    return false;
+}
+// Last radices of Bluestein's second FFT that write the grid themselves.
+__host__ __device__ constexpr bool blue_last_radix(int R) { return R == 2 || R == 4 || R == 8 || R == 16; }
 
 // General prime pass: a ring whose half-length has one prime factor p above
 // the register radices, p <= kGpMaxPrime, runs it as the first pass on the
@@ -42,6 +68,8 @@ constexpr int kGpUnits = 4;
 __host__ __device__ constexpr int gp_row_tiles(int p) { return ((p - 1) / 2 + 16) / 16; }
 __host__ __device__ constexpr int gp_col_tiles(int nbutterflies) { return (2 * nbutterflies + 15) / 16; }
 constexpr int kMaxRadices = 12;
+// Primes above the register butterflies run as general prime passes.
+__host__ __device__ constexpr bool gp_radix(int R, bool dbl) { return R > 24 || (dbl && (R == 19 || R == 23)); }
 
 // One m block of the Legendre tables.
 struct MBlock {
@@ -66,13 +94,15 @@ struct RingDesc {
     int h;        // n / 2: length of the complex FFT
     int M;        // ring cutoff
     int L;        // executed FFT length (h, or the Bluestein length >= 2h - 1)
-    int nrad;     // number of Stockham passes
+    int nrad, nrad_r;  // number of Stockham passes, c2r and r2c
     int blue;     // 1 if the length-h DFT goes through Bluestein's convolution
     int fb;       // fields per FFT block for this ring
     int lbuf;     // complex values per field slot: max(L, h + 1)
     int lbufp;    // LDS entries per field slot
-    int pass_off; // first PassDesc of this ring length's Stockham passes
-    unsigned long long radcode;  // radix of pass s in bits [5s, 5s + 5)
+    int pass_off, pass_off_r;  // first PassDesc of the c2r and the r2c passes
+    int fuse_in, fuse_out;      // c2r: first pass merges, last pass writes the grid
+    int fuse_in_r, fuse_out_r;  // r2c: first pass reads the grid, last pass splits
+    int pad_;
     int64_t tw_off;     // W_L[k] = exp(-2 pi i k / L), k < L
     int64_t post_off;   // exp(-2 pi i m / n), m <= h
     int64_t chirp_off;  // Bluestein chirp exp(-pi i k^2 / h), k < h

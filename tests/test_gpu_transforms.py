@@ -178,6 +178,30 @@ def test_ring_kinds_parity(prec, nlon):
     _check_all(plan, N, plan.ring_lengths(), 13, range(F), prec)
 
 
+# Ring lengths whose FFT plans hold, between them, a pass of every kind (in LDS;
+# first, from the grid or from the Fourier rows; last, to either) at every
+# radix that kind has, single-pass rings, prime passes alone and before each
+# last radix, and Bluestein lengths ending in each power of two; five fields
+# make more than one round of butterflies at the longer lengths.
+PASS_LENGTHS = {
+    "fp64": [4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 30, 32, 34, 36, 38, 44, 46, 58, 64, 260, 512, 520, 612, 874, 972,
+             1058, 1088, 1178, 1306, 1372, 1536, 2310, 2400],
+    "fp32": [4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 30, 32, 36, 40, 58, 110, 112, 156, 162, 384, 400, 510, 512,
+             594, 624, 828, 1024, 1114, 1140, 1198, 1292, 1306, 1372, 1440, 1466, 1960, 2058],
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_ring_pass_kinds_parity(prec):
+    shtx = _shtx()
+    for nlon in PASS_LENGTHS[prec]:
+        N, F = min(31, (nlon - 1) // 2), 5
+        _say(f"ring passes nlon={nlon} {prec}")
+        plan = shtx.Plan(N, "full", 4, F, prec, nlon_full=nlon)
+        _check_all(plan, N, plan.ring_lengths(), 19, range(F), prec)
+        plan.close()
+
+
 # Legendre GEMM column tiling: 128 columns exactly (64 fields), a last tile at
 # most half used (70 fields: covered by the 64-column tail launch) and one
 # more than half used (100 fields: no tail).
