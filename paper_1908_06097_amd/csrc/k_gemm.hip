@@ -485,6 +485,214 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(Ge
 }
 
 // ---------------------------------------------------------------------------
+// Few fields, FP64 / FP32: at most 16 FN real columns.  With so few columns the
+// table is most of the bytes and each entry is used once, so it goes from
+// memory straight to the MFMA operand registers: lane l of a wave reads
+// 16 bytes (VEC consecutive rows) of table row kappa = 4 s + l / 16, and
+// component v of the load is the A operand of the MFMA over rows VEC (l % 16)
+// + v.  A block covers 64 rows and both parities; its four waves take every
+// fourth K step (a small plan has few tiles, so the K range is split over the
+// block, and no barrier stands in the K loop) and their sums meet in LDS in a
+// fixed order.  Bound by the table's bytes: T1279 on O1280, 3 fields, FP32
+// inverse 1.33 -> 0.78 ms, direct 1.43 -> 0.75 ms (3.3 GB of table entries,
+// 4.2-4.4 TB/s) against 128 x 128 tiles, where 122 of 128 columns were
+// padding; T255, 7 fields 30 -> 14 and 47 -> 16 us; T639, 8 fields, FP64 240 ->
+// 227 and 276 -> 235 us (0.9 GB).
+// ---------------------------------------------------------------------------
+constexpr int kNarrowWaves = 4;
+// two complex values at the alignment of one
+template <typename T>
+struct __attribute__((aligned(2 * sizeof(T)))) Vec4 {
+    T a, b, c, d;
+};
+
+template <typename T, int FN, bool INV>
+__global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
+{
+    constexpr int VEC = 16 / sizeof(T), NL = 4 / VEC;  // rows per load, loads per K step and parity
+    constexpr int NW = kNarrowWaves, BM = kNarrowRows, U = sizeof(T) == 4 ? 4 : 2;
+    // INV: columns of one pair of fragments, real parts of NF fields then (in
+    // the upper half of the lanes, or in the second fragment) their imaginary
+    // parts, so that a lane's one load serves both parities (and both parts)
+    constexpr int NF = FN == 1 ? 8 : 16, NP = FN == 1 ? 1 : FN / 2, LDC = INV ? 2 * NF + 2 : 18;
+    typedef typename Acc<T>::type V;
+    typedef T VecT __attribute__((ext_vector_type(VEC)));
+    __shared__ __attribute__((aligned(16))) T red[NW][INV ? 1 : 2][BM][LDC];
+
+    const GemmItem it = a.items[xcd_remap(blockIdx.x, gridDim.x)];
+    if (it.m < 0) return;
+    const int m = it.m;
+    const MBlock b = a.mb[m];
+    const int row0 = it.tr * BM, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4, ncol = 2 * a.nfld;
+    const int64_t pstride = (int64_t)b.Kp * b.Rp;
+    const int lda_g = INV ? b.Rp : b.Kp;
+    const T *A0 = (const T *)a.tab + (INV ? b.off_kr : b.off_rk) + (int64_t)lk * lda_g + row0 + VEC * lr;
+    const int64_t sb = spec_base(a.trunc, m);
+    const int kend = INV ? b.K0 : b.R, nsteps = (kend + 3) / 4;
+
+    V acc[2][4][FN];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[p][v][j] = V{};
+
+    for (int s0 = wave; s0 < nsteps; s0 += NW * U) {
+        VecT av[U][2][NL];
+        T bv[U][2][FN];
+        RingPair ro[U];
+        T rq[U];
+        if constexpr (!INV) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = 4 * (s0 + u * NW) + lk;
+                ro[u] = RingPair{-1, -1};
+                rq[u] = T(0);
+                if (r < b.R) {
+                    ro[u] = a.ring_pair[b.j0 + r];
+                    rq[u] = a.adjoint ? T(1) : ((const T *)a.ring_q)[b.j0 + r];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + u * NW;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int l = 0; l < NL; ++l) {
+                    av[u][p][l] = VecT{};
+                    if (s < nsteps)  // wave-uniform; the tables are padded past kend
+                        av[u][p][l] = *reinterpret_cast<const VecT *>(A0 + p * pstride + (int64_t)(4 * s) * lda_g +
+                                                                      16 * VEC * l);
+                }
+            if constexpr (INV) {
+                const int nrel = 2 * (4 * s + lk);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const int f = NF * j + (lr & (NF - 1));
+                    const Vec2<T> *src = (const Vec2<T> *)a.in + (int64_t)f * a.nspec + sb + nrel;
+                    Vec2<T> z0 = {T(0), T(0)}, z1 = {T(0), T(0)};
+                    if (f < a.nfld && m + nrel + 1 <= a.trunc) {
+                        const Vec4<T> z = *reinterpret_cast<const Vec4<T> *>(src);
+                        z0 = Vec2<T>{z.a, z.b};
+                        z1 = Vec2<T>{z.c, z.d};
+                    } else if (f < a.nfld && m + nrel <= a.trunc) {
+                        z0 = src[0];
+                    }
+                    // Im a^0_n is ignored
+                    if (m == 0) z0.y = z1.y = T(0);
+                    if constexpr (FN == 1) {
+                        bv[u][0][0] = lr < NF ? z0.x : z0.y;
+                        bv[u][1][0] = lr < NF ? z1.x : z1.y;
+                    } else {
+                        bv[u][0][2 * j] = z0.x;
+                        bv[u][0][2 * j + 1] = z0.y;
+                        bv[u][1][2 * j] = z1.x;
+                        bv[u][1][2 * j + 1] = z1.y;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const int c = 16 * j + lr;
+                    bv[u][0][j] = T(0);
+                    bv[u][1][j] = T(0);
+                    if (ro[u].n >= 0 && c < ncol) {
+                        const T *four = (const T *)a.in;
+                        bv[u][0][j] = four[2 * ((int64_t)ro[u].n + m) * a.nfld + c];
+                        bv[u][1][j] = four[2 * ((int64_t)ro[u].s + m) * a.nfld + c];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                T b0 = bv[u][0][j], b1 = bv[u][1][j];
+                if constexpr (!INV) {
+                    // hemispheric fold
+                    const T gn = b0, gs = b1;
+                    b0 = rq[u] * (gn + gs);
+                    b1 = rq[u] * (gn - gs);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    acc[0][v][j] = mfma16x16x4(av[u][0][v / VEC][v % VEC], b0, acc[0][v][j]);
+                    acc[1][v][j] = mfma16x16x4(av[u][1][v / VEC][v % VEC], b1, acc[1][v][j]);
+                }
+            }
+    }
+
+    auto row = [&](int v, int t) { return 16 * VEC * (v / VEC) + VEC * acc_row<T>(lane, t) + v % VEC; };
+    auto sum = [&](int p, int r, int c) {
+        T x = red[0][p][r][c];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) x += red[w][p][r][c];
+        return x;
+    };
+    if constexpr (INV) {
+        // the waves' sums, one pair of fragments and one hemisphere at a time:
+        // runs over fields of each ring row
+#pragma unroll
+        for (int q = 0; q < 2 * NP; ++q) {
+            const int hs = q & 1, j = q >> 1;
+            if (NF * j >= a.nfld) break;
+            if (q) __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if constexpr (FN == 1) {
+                        const T s0 = acc[0][v][0][t], s1 = acc[1][v][0][t];
+                        red[wave][0][row(v, t)][2 * (lr & 7) + (lr >> 3)] = hs ? s0 - s1 : s0 + s1;
+                    } else {
+                        const T x0 = acc[0][v][2 * j][t], x1 = acc[1][v][2 * j][t];
+                        const T y0 = acc[0][v][2 * j + 1][t], y1 = acc[1][v][2 * j + 1][t];
+                        *reinterpret_cast<Vec2<T> *>(&red[wave][0][row(v, t)][2 * lr]) =
+                            hs ? Vec2<T>{x0 - x1, y0 - y1} : Vec2<T>{x0 + x1, y0 + y1};
+                    }
+                }
+            __syncthreads();
+#pragma unroll
+            for (int i = tid; i < BM * NF; i += 64 * NW) {
+                const int r = i / NF, fl = i % NF, f = NF * j + fl;
+                if (row0 + r >= b.R || f >= a.nfld) continue;
+                const RingPair o = a.ring_pair[b.j0 + row0 + r];
+                ((Vec2<T> *)a.out)[((int64_t)(hs ? o.s : o.n) + m) * a.nfld + f] =
+                    Vec2<T>{sum(0, r, 2 * fl), sum(0, r, 2 * fl + 1)};
+            }
+        }
+    } else {
+        // the waves' sums, 16 columns at a time: runs of n of one field
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            if (16 * j >= ncol) break;
+            if (j) __syncthreads();
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) red[wave][p][row(v, t)][lr] = acc[p][v][j][t];
+            __syncthreads();
+#pragma unroll
+            for (int i = tid; i < 2 * BM * 8; i += 64 * NW) {
+                const int fl = i / (2 * BM), nr = i % (2 * BM), f = 8 * j + fl, nrel = 2 * row0 + nr;
+                if (f >= a.nfld || m + nrel > a.trunc) continue;
+                const T x = sum(nr & 1, nr >> 1, 2 * fl);
+                const T y = m == 0 ? T(0) : sum(nr & 1, nr >> 1, 2 * fl + 1);
+                ((Vec2<T> *)a.out)[(int64_t)f * a.nspec + sb + nrel] = Vec2<T>{x, y};
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Split half precision with FP32 accumulation: each operand is a sum hi + lo
 // of two bfloat16 or two IEEE-half values, and a tile product is three MFMAs
 // (hi*lo + lo*hi + hi*hi; lo*lo is dropped).  16x16x32 MFMA: lane l supplies
@@ -1043,6 +1251,29 @@ hipError_t launch_mfma_part(const GemmArgs &args, int first, int count, int bm, 
     return hipErrorInvalidValue;
 }
 
+// The few-fields kernel with fn column fragments (gemm_narrow).
+template <typename T, bool INV>
+hipError_t launch_narrow(const GemmArgs &a, int fn, int grid, hipStream_t s)
+{
+    if (fn == 1) {
+        k_leg_narrow<T, 1, INV><<<grid, 64 * kNarrowWaves, 0, s>>>(a);
+        return hipGetLastError();
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (fn == 2) {
+            k_leg_narrow<T, 2, INV><<<grid, 64 * kNarrowWaves, 0, s>>>(a);
+            return hipGetLastError();
+        }
+        if constexpr (!INV) {
+            if (fn == 4) {
+                k_leg_narrow<T, 4, INV><<<grid, 64 * kNarrowWaves, 0, s>>>(a);
+                return hipGetLastError();
+            }
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
 template <typename T, int BK, bool INV>
 hipError_t launch_mfma(const Plan &p, const GemmArgs &a, int bm, int bn, hipStream_t s)
 {
@@ -1050,6 +1281,8 @@ hipError_t launch_mfma(const Plan &p, const GemmArgs &a, int bm, int bn, hipStre
     const std::vector<GemmItem> &items = INV ? p.inv_items : p.dir_items;
     const int nmain = INV ? p.inv_nmain : p.dir_nmain, tail_bn = INV ? p.inv_tail_bn : p.dir_tail_bn;
     if (!p.shapes_ok || nmain < 1) return hipErrorInvalidValue;
+    const int narrow = INV ? p.inv_narrow : p.dir_narrow;
+    if (narrow) return launch_narrow<T, INV>(a, narrow, nmain, s);
     hipError_t e = launch_mfma_part<T, BK, INV>(a, 0, nmain, bm, bn, s);
     if (e != hipSuccess || nmain == (int)items.size()) return e;
     return launch_mfma_part<T, BK, INV>(a, nmain, (int)items.size() - nmain, bm, tail_bn, s);
@@ -1141,6 +1374,22 @@ bool gemm_tile_supported(int prec, int bm, int bn)
     return false;
 }
 
+// Column fragments of the few-fields kernel for a plan and direction, 0 where
+// the tiled kernels serve it.  The lines lie where the accumulators (32 FN
+// registers in FP32, 64 FN in FP64) leave too few waves to cover the table's
+// latency: T639 on O640, microseconds against the tiled kernel, FP32 inverse
+// 150 / 206 at 16 fields but 360 / 280 at 24, direct 152 / 252 at 16 and 247 /
+// 319 at 32 (its operand loads are fewer), FP64 227 / 240 at 8 and 393 / 308
+// at 12.
+int gemm_narrow(int prec, int nfld, bool inverse)
+{
+    const int ncol = 2 * nfld;
+    if (ncol <= 16 && (prec == SHTX_FP32 || prec == SHTX_FP64)) return 1;
+    if (ncol <= 32 && prec == SHTX_FP32) return 2;
+    if (ncol <= 64 && prec == SHTX_FP32 && !inverse) return 4;
+    return 0;
+}
+
 bool gemm_shapes_ok(const Plan &p)
 {
     const bool split = split_form(p.prec);
@@ -1148,9 +1397,16 @@ bool gemm_shapes_ok(const Plan &p)
     const int bk_dir = split ? split_stage_depth(false, p.dir_bm) : 16;
     if (!gemm_tile_supported(p.prec, p.inv_bm, p.inv_bn) || !gemm_tile_supported(p.prec, p.dir_bm, p.dir_bn))
         return false;
-    bool inv_ok = p.inv_items.empty() ||
-                  check_work_list(p, p.inv_items, p.inv_nmain, true, p.inv_bm, p.inv_bn, p.inv_tail_bn, bk_inv);
-    return inv_ok && check_work_list(p, p.dir_items, p.dir_nmain, false, p.dir_bm, p.dir_bn, p.dir_tail_bn, bk_dir);
+    // each direction's list is for its tiles, or for the few-fields kernel's
+    auto dir_ok = [&](const std::vector<GemmItem> &items, int nmain, bool inverse, int narrow, int bm, int bn,
+                      int tail_bn, int bk) {
+        if (!narrow) return check_work_list(p, items, nmain, inverse, bm, bn, tail_bn, bk);
+        return 2 * p.nfld <= 16 * narrow &&
+               check_work_list(p, items, nmain, inverse, kNarrowRows, 16 * narrow, 0, 4);
+    };
+    return (p.inv_items.empty() ||
+            dir_ok(p.inv_items, p.inv_nmain, true, p.inv_narrow, p.inv_bm, p.inv_bn, p.inv_tail_bn, bk_inv)) &&
+           dir_ok(p.dir_items, p.dir_nmain, false, p.dir_narrow, p.dir_bm, p.dir_bn, p.dir_tail_bn, bk_dir);
 }
 
 hipError_t launch_gemm_inverse(const Plan &p, const void *spec, void *four, unsigned *fmax, hipStream_t s)

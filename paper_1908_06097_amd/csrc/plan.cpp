@@ -344,6 +344,10 @@ int gemm_work_lists(Plan &p)
         return SHTX_EUNSUPPORTED;
     if (kTablePad % p.inv_bm || kTablePad % p.dir_bm) return SHTX_EUNSUPPORTED;
     const int N = p.trunc, ncol = 2 * p.nfld;
+    p.inv_narrow = gemm_narrow(p.prec, p.nfld, true);
+    p.dir_narrow = gemm_narrow(p.prec, p.nfld, false);
+    const int inv_bm = p.inv_narrow ? kNarrowRows : p.inv_bm, inv_bn = p.inv_narrow ? 16 * p.inv_narrow : p.inv_bn;
+    const int dir_bm = p.dir_narrow ? kNarrowRows : p.dir_bm, dir_bn = p.dir_narrow ? 16 * p.dir_narrow : p.dir_bn;
     // a 128-column tile shape whose last column tile would hold at most 64
     // valid columns covers those with one 64-column tile (FP32 has a 128 x 64
     // kernel) in a second launch
@@ -352,8 +356,8 @@ int gemm_work_lists(Plan &p)
                    ? 64
                    : 0;
     };
-    p.inv_tail_bn = tail_of(p.inv_bm, p.inv_bn);
-    p.dir_tail_bn = tail_of(p.dir_bm, p.dir_bn);
+    p.inv_tail_bn = tail_of(inv_bm, inv_bn);
+    p.dir_tail_bn = tail_of(dir_bm, dir_bn);
     std::vector<std::vector<GemmItem>> gi, gd, ti, td;
     std::vector<double> ci, cd, cti, ctd;
     for (int m = 0; m <= N; ++m) {
@@ -361,17 +365,17 @@ int gemm_work_lists(Plan &p)
         double cost = (double)std::max(b.R, 1) * (N - m + 1) * ncol;
         std::vector<GemmItem> a, c, at, ct;
         // main column tiles, then the tail tile's index in units of tail_bn
-        int ntc_i = p.inv_tail_bn ? ncol / p.inv_bn : (ncol + p.inv_bn - 1) / p.inv_bn;
-        int ntr_i = (b.R + p.inv_bm - 1) / p.inv_bm;
+        int ntc_i = p.inv_tail_bn ? ncol / inv_bn : (ncol + inv_bn - 1) / inv_bn;
+        int ntr_i = (b.R + inv_bm - 1) / inv_bm;
         for (int tr = 0; tr < ntr_i; ++tr) {
             for (int tc = 0; tc < ntc_i; ++tc) a.push_back(GemmItem{m, tr, tc, 0});
-            if (p.inv_tail_bn) at.push_back(GemmItem{m, tr, ntc_i * p.inv_bn / p.inv_tail_bn, 0});
+            if (p.inv_tail_bn) at.push_back(GemmItem{m, tr, ntc_i * inv_bn / p.inv_tail_bn, 0});
         }
-        int ntc_d = p.dir_tail_bn ? ncol / p.dir_bn : (ncol + p.dir_bn - 1) / p.dir_bn;
-        int ntk_d = (b.K0 + p.dir_bm - 1) / p.dir_bm;
+        int ntc_d = p.dir_tail_bn ? ncol / dir_bn : (ncol + dir_bn - 1) / dir_bn;
+        int ntk_d = (b.K0 + dir_bm - 1) / dir_bm;
         for (int tk = 0; tk < ntk_d; ++tk) {
             for (int tc = 0; tc < ntc_d; ++tc) c.push_back(GemmItem{m, tk, tc, 0});
-            if (p.dir_tail_bn) ct.push_back(GemmItem{m, tk, ntc_d * p.dir_bn / p.dir_tail_bn, 0});
+            if (p.dir_tail_bn) ct.push_back(GemmItem{m, tk, ntc_d * dir_bn / p.dir_tail_bn, 0});
         }
         if (!a.empty()) {
             gi.push_back(a);

@@ -154,6 +154,8 @@ struct Plan {
 
     // GEMM tiling chosen at plan time (depends on precision).
     int inv_bm = 0, inv_bn = 0, dir_bm = 0, dir_bn = 0;
+    // Column fragments of the few-fields GEMM (gemm_narrow), 0: tiles as above.
+    int inv_narrow = 0, dir_narrow = 0;
     // Each work list is its main part (tiles of bm x bn) followed, when the
     // last column tile would be less than half used, by a tail part whose
     // tiles are tail_bn columns wide; nmain counts the main part's items.
@@ -257,6 +259,10 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
 // defaults, and whether a kernel instantiation exists for a shape.
 void gemm_tiles(int prec, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn);
 bool gemm_tile_supported(int prec, int bm, int bn);
+// Few fields: column fragments of the kernel that serves them, whatever the
+// tile shapes are (0: the tiled kernels do), and its row tile.
+int gemm_narrow(int prec, int nfld, bool inverse);
+constexpr int kNarrowRows = 64;
 // Candidate shapes the autotuner times (count returned, shapes in bm[], bn[]).
 int gemm_tile_candidates(int prec, int *bm, int *bn, int max);
 

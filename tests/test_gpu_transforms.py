@@ -214,6 +214,21 @@ def test_gemm_column_tiles_fp32(F):
     _check_all(plan, N, plan.ring_lengths(), 17, range(F), "fp32")
 
 
+# Few fields: both sides of the lines between the column counts of the
+# few-fields kernel and between it and the tiled ones; rows and K steps that
+# are ragged, fewer than one block's (T2: one row tile, fewer steps than waves)
+# and more than one row tile.
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("F", [1, 8, 9, 16, 17, 32, 33])
+def test_gemm_few_fields(prec, F):
+    shtx = _shtx()
+    for N in (2, 63, 150):
+        _say(f"few fields T{N} F={F} {prec}")
+        plan = shtx.Plan(N, "octahedral", 2 * (N + 1), F, prec)
+        _check_all(plan, N, plan.ring_lengths(), 23, range(F), prec)
+        plan.close()
+
+
 def test_t79_full_fp64_round_trip():
     """T79 on the full 160 x 320 grid, 1 field, FP64: parity and round trip <= 1e-12."""
     shtx, o = _shtx(), _oracle()
