@@ -33,8 +33,10 @@
  *         otherwise.
  *
  * Precision forms (the Legendre arithmetic; the ring FFTs run in the grid
- * type): SHTX_FP64 plain double; SHTX_FP32 single precision on the matrix
- * cores with FP32 accumulation; SHTX_BF16X3 split bfloat16 hi+lo operands
+ * type): SHTX_FP64 plain double; SHTX_FP32 single precision with FP32
+ * accumulation (on the half-precision matrix cores each operand is its exact
+ * sum of three bfloat16, six products of which count; an infinite operand
+ * gives NaN); SHTX_BF16X3 split bfloat16 hi+lo operands
  * (three products, lo*lo dropped) with per-m power-of-two scaling of the
  * Legendre table and FP32 accumulation; SHTX_FP16X3 the same split with IEEE
  * half hi+lo operands (11-bit halves, 5-bit exponent), the table block of

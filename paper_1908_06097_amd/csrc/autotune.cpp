@@ -230,7 +230,7 @@ namespace {
 // The plan state that apply_shapes rebuilds, kept so that a failed call can
 // put it back.
 struct ShapeState {
-    int inv_bm, inv_bn, dir_bm, dir_bn, inv_nmain, dir_nmain, inv_tail_bn, dir_tail_bn;
+    int inv_bm, inv_bn, dir_bm, dir_bn;
     int fft_lds_bytes, fft_lds_max, fft_cap;
     bool shapes_ok;
     std::vector<GemmItem> inv_items, dir_items;
@@ -240,9 +240,8 @@ struct ShapeState {
 
 ShapeState save_shapes(const Plan &p)
 {
-    ShapeState s{p.inv_bm,      p.inv_bn,      p.dir_bm,      p.dir_bn,   p.inv_nmain, p.dir_nmain,
-                 p.inv_tail_bn, p.dir_tail_bn, p.fft_lds_bytes, p.fft_lds_max, p.fft_cap, p.shapes_ok,
-                 p.inv_items,   p.dir_items,   p.fft_items,   {}};
+    ShapeState s{p.inv_bm,  p.inv_bn,    p.dir_bm,    p.dir_bn,    p.fft_lds_bytes, p.fft_lds_max,
+                 p.fft_cap, p.shapes_ok, p.inv_items, p.dir_items, p.fft_items,     {}};
     for (const RingDesc &d : p.rings) s.fb.push_back(d.fb);
     return s;
 }
@@ -253,10 +252,6 @@ void restore_shapes(Plan &p, ShapeState &s)
     p.inv_bn = s.inv_bn;
     p.dir_bm = s.dir_bm;
     p.dir_bn = s.dir_bn;
-    p.inv_nmain = s.inv_nmain;
-    p.dir_nmain = s.dir_nmain;
-    p.inv_tail_bn = s.inv_tail_bn;
-    p.dir_tail_bn = s.dir_tail_bn;
     p.fft_lds_bytes = s.fft_lds_bytes;
     p.fft_lds_max = s.fft_lds_max;
     p.fft_cap = s.fft_cap;

@@ -341,36 +341,28 @@ int shtx_plan_legendre(shtx_plan h, int m, double *out)
     const shtx::MBlock &b = p.mb[m];
     if (!out) return b.R;
     int K = p.trunc - m + 1;
-    size_t el = p.prec == SHTX_FP64 ? 8 : p.prec == SHTX_FP32 ? 4 : 2;
-    size_t cnt = 2 * (size_t)b.Rp * b.Kp;
-    std::vector<unsigned char> hi(cnt * el), lo;
-    hipError_t e = hipMemcpy(hi.data(), (const char *)p.d_tab_rk + b.off_rk * el, cnt * el,
-                             hipMemcpyDeviceToHost);
-    if (e == hipSuccess && shtx::split_form(p.prec)) {
-        lo.resize(cnt * el);
-        e = hipMemcpy(lo.data(), (const char *)p.d_tab_rk_lo + b.off_rk * el, cnt * el,
-                      hipMemcpyDeviceToHost);
-    }
+    const int np = shtx::table_pieces(p, false);
+    const size_t el = shtx::table_entry_bytes(p, false), cnt = 2 * (size_t)b.Rp * b.Kp;
+    std::vector<unsigned char> tab(cnt * el);
+    hipError_t e = hipMemcpy(tab.data(), (const char *)p.d_tab_dir + b.off * el, cnt * el, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_status(e);
-    auto val = [&](size_t idx) -> double {
-        if (p.prec == SHTX_FP64) return reinterpret_cast<const double *>(hi.data())[idx];
-        if (p.prec == SHTX_FP32) return reinterpret_cast<const float *>(hi.data())[idx];
-        auto bf = [&](uint16_t u) {
-            if (p.prec == SHTX_FP16X3) return (double)__builtin_bit_cast(_Float16, u);
-            uint32_t x = (uint32_t)u << 16;
-            float f;
-            std::memcpy(&f, &x, 4);
-            return (double)f;
-        };
-        double v = bf(reinterpret_cast<const uint16_t *>(hi.data())[idx]) +
-                   bf(reinterpret_cast<const uint16_t *>(lo.data())[idx]);
+    auto piece = [&](size_t idx) -> double {
+        const uint16_t u = reinterpret_cast<const uint16_t *>(tab.data())[idx];
+        if (p.prec == SHTX_FP16X3) return (double)__builtin_bit_cast(_Float16, u);
+        return (double)__builtin_bit_cast(float, (uint32_t)u << 16);
+    };
+    auto val = [&](int par, int r, int k) -> double {
+        const size_t idx = ((size_t)par * b.Rp + r) * b.Kp + k;
+        if (!np) return p.prec == SHTX_FP64 ? reinterpret_cast<const double *>(tab.data())[idx]
+                                            : reinterpret_cast<const float *>(tab.data())[idx];
+        double v = 0.0;
+        for (int h = np - 1; h >= 0; --h)
+            v += piece((((size_t)(2 * h + par) * (b.Rp / 8) + r / 8) * b.Kp + k) * 8 + r % 8);
         return std::ldexp(v, -b.e);
     };
     for (int r = 0; r < b.R; ++r)
         for (int t = 0; t < K; ++t) {
-            int par = t & 1, k = t >> 1;
-            size_t idx = (size_t)par * b.Rp * b.Kp + (size_t)r * b.Kp + k;
-            out[(size_t)r * K + t] = val(idx);
+            out[(size_t)r * K + t] = val(t & 1, r, t >> 1);
         }
     return b.R;
 }

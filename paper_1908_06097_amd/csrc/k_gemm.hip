@@ -65,8 +65,7 @@ __device__ inline int acc_row(int lane, int v)
 }
 
 struct GemmArgs {
-    const void *tab;     // table for the A operand
-    const void *tab_lo;  // split-BF16 lo half of the table
+    const void *tab;  // table for the A operand
     const MBlock *mb;
     const GemmItem *items;
     const RingPair *ring_pair;  // per northern ring: Fourier offsets of it and its mirror
@@ -86,7 +85,7 @@ struct GemmArgs {
 __device__ inline int64_t spec_base(int trunc, int m) { return (int64_t)m * (2 * trunc + 3 - m) / 2; }
 
 // ---------------------------------------------------------------------------
-// FP64 / FP32.  NW (4 or 8) waves as 2 x (NW/2), each owning a (BM/2) x
+// FP64.  NW (4 or 8) waves as 2 x (NW/2), each owning a (BM/2) x
 // (2 BN/NW) tile per parity.  LDS tiles are K-major (As[buf][p][kappa][i],
 // Bs[buf][p][kappa][j]) and double-buffered: the global loads of stage s+1
 // are issued into registers before the MFMAs of stage s and written to the
@@ -102,68 +101,8 @@ struct __attribute__((aligned(2 * sizeof(T)))) Vec2 {
     T x, y;
 };
 
-// Inverse epilogue through LDS (single precision and the split forms): the
-// tile's rows of one hemisphere at a time are staged as [row][column] floats
-// (16-column groups swizzled by row so that the fragment writes spread over
-// the banks) and written out as contiguous runs over the fields of each ring
-// row, 16 bytes per lane, instead of 4-byte stores scattered over 64-byte
-// pieces.  val(hs, i, j, v) is the fragment value of hemisphere hs (0 north,
-// 1 south).  Called by every thread of the block after the K loop's final
-// barrier; st must hold BM x BN floats.
-typedef float f32x4s __attribute__((ext_vector_type(4)));
-typedef float f32x4s8 __attribute__((ext_vector_type(4), aligned(8)));
-template <int BM, int BN, int NT, int FM, int FN, typename ValFn>
-__device__ inline void inv_epilogue_staged(const GemmArgs &a, const MBlock &b, int m, int row0, int col0, int wr,
-                                           int wc, int lane, int tid, float *st, ValFn val)
-{
-    constexpr int TPR = BN / 4, RPP = NT / TPR, NPASS = BM / RPP;
-    static_assert(BN >= 64 && NPASS * RPP == BM, "staged rows must split evenly over the block");
-    const int ncol = 2 * a.nfld;
-    // ring offsets of the rows this thread writes, fetched before the staging
-    RingPair ro[NPASS];
-#pragma unroll
-    for (int k = 0; k < NPASS; ++k) {
-        const int r = row0 + tid / TPR + k * RPP;
-        ro[k] = RingPair{-1, -1};
-        if (r < b.R) ro[k] = a.ring_pair[b.j0 + r];
-    }
-    float *four = (float *)a.out;
-    const int cq = 4 * (tid % TPR);
-#pragma unroll
-    for (int hs = 0; hs < 2; ++hs) {
-        if (hs) __syncthreads();  // the north half has been read out
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = wr + i * 16 + 4 * (lane >> 4) + v;
-                    const int c = wc + j * 16 + (lane & 15);
-                    st[r * BN + (c ^ ((r & 12) << 2))] = val(hs, i, j, v);
-                }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < NPASS; ++k) {
-            const RingPair o = ro[k];
-            const int rl = tid / TPR + k * RPP;
-            const int c = col0 + cq;
-            if (o.n < 0 || c >= ncol) continue;
-            const f32x4s x = *reinterpret_cast<const f32x4s *>(&st[rl * BN + (cq ^ ((rl & 12) << 2))]);
-            float *dst = four + 2 * ((int64_t)(hs ? o.s : o.n) + m) * a.nfld + c;
-            if (c + 3 < ncol) {
-                *reinterpret_cast<f32x4s8 *>(dst) = x;
-            } else {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (c + t < ncol) dst[t] = x[t];
-            }
-        }
-    }
-}
-
 template <typename T, int BM, int BN, int BK, bool INV, int NW = 4>
-__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(GemmArgs a)
+__global__ __launch_bounds__(64 * NW, 2) void k_leg_mfma(GemmArgs a)
 {
     // NW waves as 2 x (NW / 2): rows split in two, columns in NW / 2
     constexpr int NT = 64 * NW, NWN = NW / 2;
@@ -198,7 +137,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(Ge
     const int wr = (wave / NWN) * WM, wc = (wave % NWN) * WN;
     const int ncol = 2 * a.nfld;
     const int64_t pstride = (int64_t)b.Kp * b.Rp;
-    const T *A0 = (const T *)a.tab + (INV ? b.off_kr : b.off_rk);
+    const T *A0 = (const T *)a.tab + b.off;
     const int lda_g = INV ? b.Rp : b.Kp;  // global row stride of the table tile
     const int64_t sb = spec_base(a.trunc, m);
     const int kend = INV ? b.K0 : b.R;
@@ -383,14 +322,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(Ge
     else
         kloop(std::integral_constant<int, 0>{});
 
-    if constexpr (INV && sizeof(T) == 4) {
-        static_assert(BM * BN <= NSMEM, "staged inverse tile must fit the operand LDS");
-        inv_epilogue_staged<BM, BN, NT, FM, FN>(a, b, m, row0, col0, wr, wc, lane, tid, reinterpret_cast<float *>(smem),
-                                                [&](int hs, int i, int j, int v) {
-                                                    const float s0 = acc[0][i][j][v], s1 = acc[1][i][j][v];
-                                                    return hs ? s0 - s1 : s0 + s1;
-                                                });
-    } else if constexpr (INV) {
+    if constexpr (INV) {
         T *four = (T *)a.out;
         // all rows' ring offsets first, so that their loads overlap
         RingPair ro[FM][4];
@@ -420,9 +352,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(Ge
                     }
                 }
             }
-    } else if constexpr (sizeof(T) == 8) {
-        // FP64: direct scattered stores (staging measured slower for the
-        // smaller FP64 tiles)
+    } else {
+        // direct scattered stores (staging through LDS measured slower for these
+        // small tiles)
         T *spec = (T *)a.out;
 #pragma unroll
         for (int p = 0; p < 2; ++p)
@@ -441,46 +373,6 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 4 : 2) void k_leg_mfma(Ge
                             spec[2 * ((int64_t)(c >> 1) * a.nspec + sb + nrel) + (c & 1)] = val;
                         }
                     }
-    } else {
-        // The tile covers n = m + 2 row0 + (0 .. 2 BM - 1) for BN/2 fields: each
-        // column half (the fields of waves with the same wc) is staged in LDS
-        // as [field][n] and written as contiguous runs of one field's spectrum.
-        constexpr int FH = BN / 4;      // fields per column half
-        constexpr int RS = 2 * BM + 1;  // staged complex values per field, padded
-        static_assert(FH * RS * 2 <= NSMEM, "staged output half must fit the operand LDS");
-        Vec2<T> *spec = (Vec2<T> *)a.out;
-        const int nrel0 = 2 * row0;
-        const int nvalid = min(2 * BM, a.trunc - m - nrel0 + 1);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            __syncthreads();  // the K loop's (or the previous half's) LDS reads are done
-            if ((wave % NWN) / (NWN / 2) == h) {
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int j = 0; j < FN; ++j)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const int k = wr + i * 16 + acc_row<T>(lane, v);
-                                // column within the staged half
-                                const int cl = wc - h * (BN / 2) + j * 16 + (lane & 15);
-                                T val = acc[p][i][j][v];
-                                if (m == 0 && (cl & 1)) val = 0;
-                                smem[((cl >> 1) * RS + p + 2 * k) * 2 + (cl & 1)] = val;
-                            }
-            }
-            __syncthreads();
-            const int fbase = col0 / 2 + h * FH;
-            for (int fl = wave; fl < FH; fl += NW) {
-                const int f = fbase + fl;
-                if (f >= a.nfld) break;
-                Vec2<T> *dst = spec + (int64_t)f * a.nspec + sb + nrel0;
-                for (int nr = lane; nr < nvalid; nr += 64)
-                    dst[nr] = Vec2<T>{smem[(fl * RS + nr) * 2], smem[(fl * RS + nr) * 2 + 1]};
-            }
-        }
     }
 }
 
@@ -526,9 +418,10 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
     const int row0 = it.tr * BM, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4, ncol = 2 * a.nfld;
+    const int col0 = it.tc * 16 * FN, f0 = it.tc * 8 * FN;
     const int64_t pstride = (int64_t)b.Kp * b.Rp;
     const int lda_g = INV ? b.Rp : b.Kp;
-    const T *A0 = (const T *)a.tab + (INV ? b.off_kr : b.off_rk) + (int64_t)lk * lda_g + row0 + VEC * lr;
+    const T *A0 = (const T *)a.tab + b.off + (int64_t)lk * lda_g + row0 + VEC * lr;
     const int64_t sb = spec_base(a.trunc, m);
     const int kend = INV ? b.K0 : b.R, nsteps = (kend + 3) / 4;
 
@@ -573,7 +466,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
                 const int nrel = 2 * (4 * s + lk);
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
-                    const int f = NF * j + (lr & (NF - 1));
+                    const int f = f0 + NF * j + (lr & (NF - 1));
                     const Vec2<T> *src = (const Vec2<T> *)a.in + (int64_t)f * a.nspec + sb + nrel;
                     Vec2<T> z0 = {T(0), T(0)}, z1 = {T(0), T(0)};
                     if (f < a.nfld && m + nrel + 1 <= a.trunc) {
@@ -598,7 +491,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             } else {
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    const int c = 16 * j + lr;
+                    const int c = col0 + 16 * j + lr;
                     bv[u][0][j] = T(0);
                     bv[u][1][j] = T(0);
                     if (ro[u].n >= 0 && c < ncol) {
@@ -641,7 +534,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 #pragma unroll
         for (int q = 0; q < 2 * NP; ++q) {
             const int hs = q & 1, j = q >> 1;
-            if (NF * j >= a.nfld) break;
+            if (f0 + NF * j >= a.nfld) break;
             if (q) __syncthreads();
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -660,7 +553,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             __syncthreads();
 #pragma unroll
             for (int i = tid; i < BM * NF; i += 64 * NW) {
-                const int r = i / NF, fl = i % NF, f = NF * j + fl;
+                const int r = i / NF, fl = i % NF, f = f0 + NF * j + fl;
                 if (row0 + r >= b.R || f >= a.nfld) continue;
                 const RingPair o = a.ring_pair[b.j0 + row0 + r];
                 ((Vec2<T> *)a.out)[((int64_t)(hs ? o.s : o.n) + m) * a.nfld + f] =
@@ -671,7 +564,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
         // the waves' sums, 16 columns at a time: runs of n of one field
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            if (16 * j >= ncol) break;
+            if (col0 + 16 * j >= ncol) break;
             if (j) __syncthreads();
 #pragma unroll
             for (int p = 0; p < 2; ++p)
@@ -682,7 +575,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             __syncthreads();
 #pragma unroll
             for (int i = tid; i < 2 * BM * 8; i += 64 * NW) {
-                const int fl = i / (2 * BM), nr = i % (2 * BM), f = 8 * j + fl, nrel = 2 * row0 + nr;
+                const int fl = i / (2 * BM), nr = i % (2 * BM), f = f0 + 8 * j + fl, nrel = 2 * row0 + nr;
                 if (f >= a.nfld || m + nrel > a.trunc) continue;
                 const T x = sum(nr & 1, nr >> 1, 2 * fl);
                 const T y = m == 0 ? T(0) : sum(nr & 1, nr >> 1, 2 * fl + 1);
@@ -693,73 +586,91 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Split half precision with FP32 accumulation: each operand is a sum hi + lo
-// of two bfloat16 or two IEEE-half values, and a tile product is three MFMAs
-// (hi*lo + lo*hi + hi*hi; lo*lo is dropped).  16x16x32 MFMA: lane l supplies
-// A[l%16][8(l/16)..+7] and B[8(l/16)..+7][l%16]; LDS tiles are row-major
-// with kappa contiguous: As[p][h][i][kappa], Bs[p][h][j][kappa] (h = hi, lo),
-// unpadded, the 16-byte chunks of each row permuted by an XOR swizzle.
+// FP32 and the split forms, on the half-precision matrix cores with FP32
+// accumulation.  Each operand is a sum of 16-bit pieces and a tile product is
+// the MFMAs of the piece pairs that matter, smallest first:
+//   SHTX_FP32    three bfloat16 pieces, 8 + 8 + 8 significand bits: every float
+//                exactly; the six products down to 2^-16 of the largest (what
+//                is dropped is below 2^-24 of it)
+//   SHTX_BF16X3  bfloat16 hi + lo, three products (lo lo is dropped)
+//   SHTX_FP16X3  IEEE half hi + lo, three products
+// The table is stored in pieces, for the split forms scaled by 2^e_m per m; the
+// data operand is cut into pieces here, once per block and stage.  IEEE half
+// has a 5-bit exponent, so its data operand is also scaled per field by 2^E_f,
+// chosen from a bound on the field's largest value; bfloat16 has the FP32
+// exponent range and needs no data scale.  An infinite value gives NaN.
 //
-// The table is stored already split, scaled by 2^e_m per m.  The data
-// operand is split here, once per block and stage, with the packed
-// round-to-nearest-even conversions of gfx950.  IEEE half has a 5-bit
-// exponent, so its data operand is also scaled per field by 2^E_f, chosen
-// from a bound on the field's largest value; bfloat16 has the FP32 exponent
-// range and needs no data scale.
+// 32x32x16 MFMA: lane l supplies A[l%32][8(l/32)..+7] and B[8(l/32)..+7][l%32]
+// and holds D[8(v/4) + 4(l/32) + v%4][l%32], v = 0..15.  Both operands come in
+// units of 16 bytes, 8 consecutive kappa of one row: the table is laid out in
+// memory as planes [piece][parity][kappa / 8][row] of units, so a stage's
+// loads and LDS writes are runs of units (no transposition, no bank
+// conflicts), and LDS holds one 16-deep stage in the same order.
+//
+// A block covers 64 FI rows and 32 FJ fields (64 FJ columns), both parities, in
+// four waves of 32 fields (real and imaginary parts: two column fragments) and
+// the 32-row fragments wr, wr + WR, ... of the tile; the next stage's loads are
+// in flight over the MFMAs.
+//
+// O1280, 411 fields, against the kernels before (16x16x4 FP32 MFMA; split
+// operands re-staged by field): FP32 inverse 13.4 -> 9.8 ms, direct 13.6 -> 11.1;
+// BF16x3 8.3 -> 6.9 and 8.8 -> 7.8; T399, 137 fields, FP32 244 -> 177 and 285 ->
+// 227 us.  Of the FP32 inverse's 9.8 ms, found by leaving out one part at a
+// time: MFMAs 2.7, operand loads 2.7, conversion and LDS stores 1.4, output and
+// block start 2.3 (8.1 GB written); the parts add up instead of overlapping
+// although two blocks share a CU, at a clock that falls to 2.0 GHz.
 // ---------------------------------------------------------------------------
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-// two complex values at an 8-byte aligned address, one 16-byte load (vector
-// memory instructions need only 4-byte alignment)
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+// vector loads and stores at 8-byte aligned addresses (vector memory
+// instructions need only 4-byte alignment)
 typedef float f32x4a8 __attribute__((ext_vector_type(4), aligned(8)));
 
-// lo = x - hi must be taken against the very hi that is stored.  Left to
-// itself the compiler re-derives hi for that subtraction from the product
-// that produced x, by another instruction (a mixed-precision FMA rounding the
-// exact product to half once) whose result differs from the stored hi
-// wherever the two roundings disagree; hi + lo is then off by a unit of hi.
-// An empty asm statement makes the stored hi's bits opaque, so the residual
-// is computed from them.
-template <bool F16>
-__device__ inline void split2(float x0, float x1, unsigned &hi, unsigned &lo)
+// Two floats -> packed pieces, most significant first.  Residuals must be taken
+// against the very bits that are stored.  Left to itself the compiler
+// re-derives hi for that subtraction from the product that produced x, by
+// another instruction (a mixed-precision FMA rounding the exact product to
+// half once) whose result differs from the stored hi wherever the two
+// roundings disagree; hi + lo is then off by a unit of hi.  An empty asm
+// statement makes the stored bits opaque, so the residual is computed from
+// them.  The FP32 form cuts its leading piece instead of rounding it: values
+// near the largest float stay finite.
+template <int FORM>
+__device__ inline void split_pair(float x0, float x1, unsigned *w)
 {
-    if constexpr (F16) {
+    if constexpr (FORM == SHTX_FP16X3) {
         unsigned hb = __builtin_bit_cast(unsigned, f16x2{(_Float16)x0, (_Float16)x1});
         asm("" : "+v"(hb));
         const f16x2 h = __builtin_bit_cast(f16x2, hb);
-        const f16x2 l = {(_Float16)(x0 - (float)h[0]), (_Float16)(x1 - (float)h[1])};
-        hi = hb;
-        lo = __builtin_bit_cast(unsigned, l);
+        w[0] = hb;
+        w[1] = __builtin_bit_cast(unsigned, f16x2{(_Float16)(x0 - (float)h[0]), (_Float16)(x1 - (float)h[1])});
     } else {
-        unsigned hb = __builtin_bit_cast(unsigned, bf16x2{(__bf16)x0, (__bf16)x1});
+        float r0 = x0, r1 = x1;
+        if constexpr (FORM == SHTX_FP32) {
+            const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
+            *w++ = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+            r0 = x0 - __uint_as_float(b0 & 0xffff0000u);
+            r1 = x1 - __uint_as_float(b1 & 0xffff0000u);
+        }
+        unsigned hb = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
         asm("" : "+v"(hb));
-        const bf16x2 h = __builtin_bit_cast(bf16x2, hb);
-        const bf16x2 l = {(__bf16)(x0 - (float)h[0]), (__bf16)(x1 - (float)h[1])};
-        hi = hb;
-        lo = __builtin_bit_cast(unsigned, l);
+        w[0] = hb;
+        w[1] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(r0 - __uint_as_float(hb << 16)),
+                                                   (__bf16)(r1 - __uint_as_float(hb & 0xffff0000u))});
     }
 }
 
-// eight floats -> one 16-byte word of hi halves and one of lo halves
-template <bool F16>
-__device__ inline void split8(const float *x, u32x4 &hi, u32x4 &lo)
+template <int FORM>
+__device__ inline f32x16 mfma_split(u32x4 a, u32x4 b, f32x16 c)
 {
-    unsigned h[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split2<F16>(x[2 * i], x[2 * i + 1], h[i], l[i]);
-    hi = u32x4{h[0], h[1], h[2], h[3]};
-    lo = u32x4{l[0], l[1], l[2], l[3]};
-}
-
-template <bool F16>
-__device__ inline f32x4 mfma_split(u32x4 a, u32x4 b, f32x4 c)
-{
-    if constexpr (F16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c,
+    if constexpr (FORM == SHTX_FP16X3)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c,
                                                       0, 0, 0);
     else
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
                                                        c, 0, 0, 0);
 }
 
@@ -776,381 +687,282 @@ __device__ inline int field_exp(const unsigned *fmax, int f, float bound)
     return 14 - X;
 }
 
-template <bool F16, int BM, int BN, int BK, bool INVERSE, int NW>
-__global__ __launch_bounds__(64 * NW) void k_leg_split(GemmArgs a)
+// Transposes a quad of lanes' 4 x 4 values in registers: lane q's x[t] becomes
+// lane t's x[q] (odd, upper: bits 0 and 1 of the lane index).
+__device__ inline void quad_transpose(float *x, bool odd, bool upper)
 {
-    // NW waves as 2 x (NW / 2): rows split in two, columns in NW / 2
-    constexpr int NT = 64 * NW, NWN = NW / 2;
-    constexpr int WM = BM / 2, WN = BN / NWN, FM = WM / 16, FN = WN / 16;
-    static_assert(NW == 4 || NW == 8, "4 or 8 waves per block");
-    constexpr int LDK = BK;     // unpadded rows; 16-byte chunks swizzled per row
-    constexpr int CH = BK / 8;  // 16-byte chunks per tile row
-    static_assert(CH == 4 || CH == 8, "the chunk swizzle permutes four or eight chunks");
-    // physical chunk of logical chunk c in tile row r: c ^ sw(r), the bits
-    // of r / PR (PR rows span 512 bytes) to the swizzle's upper bits and bit
-    // 4 of r to bit 0.  Measured with an LDS probe: with four chunks (64-byte
-    // rows) the fragment reads run at the rate of linear reads (unswizzled
-    // 64- to 80-byte rows take twice as long); with eight chunks they still
-    // take twice, off the critical path of these kernels
-    constexpr int PR = 32 / CH;
-    auto sw = [](int r) __attribute__((always_inline)) { return (((r / PR) & (CH / 2 - 1)) << 1) | ((r >> 4) & 1); };
-    // LDS row of operand column (field fl, re/im ri): the inverse keeps them
-    // interleaved, the direct places all real parts before all imaginary ones
-    auto brow = [](int fl, int ri) __attribute__((always_inline)) {
-        return INVERSE ? 2 * fl + ri : ri * (BN / 2) + fl;
+    auto swap = [](float mine, auto ctrl) {
+        return __uint_as_float(
+            __builtin_amdgcn_mov_dpp(__float_as_uint(mine), decltype(ctrl)::value, 0xf, 0xf, true));
     };
-    constexpr int NA = (2 * 2 * BM * CH) / NT;  // table chunk loads per thread
-    // DIR operand units: (field, 8 consecutive rings, north and south)
-    constexpr int NUNIT = (BN / 2) * CH;
-    constexpr int NU = (NUNIT + NT - 1) / NT;
-    static_assert(NUNIT % 64 == 0, "direct operand units must fill whole waves");
-    static_assert(NA * NT == 2 * 2 * BM * CH, "table tile must split evenly");
-    // INV operand chunks: 4 consecutive n (two kappa of each parity) of one
-    // field, 32 bytes; the JC chunks of a field's stage are taken by JC
-    // consecutive lanes, so four lanes share each 128-byte line and one load
-    // instruction of a wave touches 16 lines (one line per lane when each
-    // lane read a whole run of 16 n)
-    constexpr int JC = BK / 2;
-    constexpr int NIU = (BN / 2) * JC / NT;
-    static_assert(!INVERSE || (NIU * NT == (BN / 2) * JC && 4 * NIU <= 16 * NU),
-                  "inverse operand chunks must split evenly");
-    // operand tiles As[p][h][i][kappa], Bs[p][h][j][kappa]; the direct form
-    // reuses the same LDS to stage its output tile
-    constexpr int NOPER16 = 2 * 2 * (BM + BN) * LDK;
-    // the direct form stages one half of its output columns (BN / 4 fields of
-    // 2 BM + 1 complex values) in the same LDS
-    constexpr int NSTAGE16 = INVERSE ? 0 : (BN / 4) * (2 * BM + 1) * 2 * 2;
-    constexpr int NSMEM16 = NOPER16 > NSTAGE16 ? NOPER16 : NSTAGE16;
-    __shared__ __attribute__((aligned(16))) unsigned short smem16[NSMEM16];
-    auto As = reinterpret_cast<unsigned short(*)[2][BM][LDK]>(smem16);
-    auto Bs = reinterpret_cast<unsigned short(*)[2][BN][LDK]>(smem16 + 2 * 2 * BM * LDK);
+    // quad_perm [1, 0, 3, 2] and [2, 3, 0, 1]
+    typedef std::integral_constant<int, 0xB1> xor1;
+    typedef std::integral_constant<int, 0x4E> xor2;
+#pragma unroll
+    for (int t = 0; t < 4; t += 2) {
+        const float r = swap(odd ? x[t] : x[t + 1], xor1{});
+        x[t] = odd ? r : x[t];
+        x[t + 1] = odd ? x[t + 1] : r;
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const float r = swap(upper ? x[t] : x[t + 2], xor2{});
+        x[t] = upper ? r : x[t];
+        x[t + 2] = upper ? x[t + 2] : r;
+    }
+}
 
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const GemmItem it = a.items[item];
+template <int FORM, int FI, int FJ, bool INV>
+__global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArgs a)
+{
+    constexpr bool F16 = FORM == SHTX_FP16X3;
+    constexpr int NP = split_pieces(FORM), BM = 64 * FI, BN = 64 * FJ, NF = 32 * FJ, BK = 16;
+    constexpr int WR = 4 / FJ, NI = BM / (32 * WR);  // waves over the rows, row fragments per wave
+    // units of an LDS plane: the rows of A; of B the real parts at 0 and the
+    // imaginary ones at URI.  The offsets between parts and parities put the
+    // four units that a quad of lanes stores on different banks.
+    constexpr int UA = BM, URI = NF + 8, UB = URI + NF + 2, PA = NP * 4 * UA, PB = NP * 4 * UB;
+    // the direct form stages its output in the same LDS: 2 BM + 1 complex
+    // values of 32 fields
+    constexpr int NSTAGE = INV ? 0 : 32 * (2 * BM + 1) / 2;
+    constexpr int NSMEM = PA + PB > NSTAGE ? PA + PB : NSTAGE;
+    constexpr int NA = NP * FI;  // units of A per thread
+    __shared__ u32x4 smem[NSMEM];
+    u32x4 *As = smem, *Bs = smem + PA;
+
+    const GemmItem it = a.items[xcd_remap(blockIdx.x, gridDim.x)];
     if (it.m < 0) return;
     const int m = it.m;
     const MBlock b = a.mb[m];
-    const int row0 = it.tr * BM, col0 = it.tc * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave / NWN) * WM, wc = (wave % NWN) * WN;
-    const int ncol = 2 * a.nfld;
+    const int row0 = it.tr * BM, f0 = it.tc * NF;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / FJ, fj = wave % FJ;
     const int64_t sb = spec_base(a.trunc, m);
-    // A operand rows are contiguous in kappa: inverse reads [p][r][k], direct [p][k][r]
-    const int64_t off = INVERSE ? b.off_rk : b.off_kr;
-    const int lda = INVERSE ? b.Kp : b.Rp;
-    const int64_t pstride = (int64_t)b.Rp * b.Kp;
-    const unsigned short *Th = (const unsigned short *)a.tab + off;
-    const unsigned short *Tl = (const unsigned short *)a.tab_lo + off;
-    const int kend = INVERSE ? b.K0 : b.R;
-    const int nstages = (kend + BK - 1) / BK;
-
-    // each thread's operand units keep their field over all stages
-    int ufl[NU];
-    bool uon[NU];
-    float usc[NU];  // data scale 2^E_f (half form)
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int idx = tid + u * NT;
-        ufl[u] = INVERSE ? idx / CH : idx % (BN / 2);
-        uon[u] = idx < NUNIT;
-        usc[u] = 1.f;
-        if constexpr (F16) {
-            const int f = col0 / 2 + ufl[u];
-            if (uon[u] && f < a.nfld) usc[u] = ldexpf(1.f, field_exp(a.fmax, f, a.dbound));
-        }
-    }
-    // INV: the fields of this thread's chunks and their data scales
-    const int ij = tid % JC;
-    float isc[NIU];
-#pragma unroll
-    for (int u = 0; u < NIU; ++u) {
-        isc[u] = 1.f;
-        if constexpr (F16 && INVERSE) {
-            const int f = col0 / 2 + (u * NT + tid) / JC;
-            if (f < a.nfld) isc[u] = ldexpf(1.f, field_exp(a.fmax, f, a.dbound));
-        }
-    }
+    const int kend = INV ? b.K0 : b.R, nstages = (kend + BK - 1) / BK;
+    // the m block's table through a buffer descriptor: a unit's plane and row
+    // are a scalar offset, the only vector address is the lane
+    const int rows = INV ? b.Rp : b.Kp, chunks = (INV ? b.Kp : b.Rp) / 8;
+    const int64_t tab_units = (int64_t)NP * 2 * chunks * rows;
+    const auto tab = __builtin_amdgcn_make_buffer_rsrc((void *)((const u32x4 *)a.tab + b.off / 8 * NP), 0,
+                                                       (int)(tab_units * 16), 0x00027000);
+    // This thread's share of B.  INV: a quad of lanes takes the 16 kappa of one
+    // field, reading 64 contiguous bytes at a time, and transposes them so that
+    // lane q holds one parity and part (q / 2, q % 2) of every kappa.  DIR:
+    // rings 8 kh .. + 7 of column t, both hemispheres.
+    const bool bon = FJ == 2 || wave < 2;
+    const int bf = INV ? tid >> 2 : (tid & (BN - 1)) >> 1, kh = FJ == 2 ? wave >> 1 : wave & 1;
+    const int bp = tid >> 1 & 1, bri = tid & 1;
+    const int bfc = min(f0 + bf, a.nfld - 1);  // past the last field: repeated, not stored
+    float scale = 1.f;
+    if constexpr (F16) scale = ldexpf(1.f, field_exp(a.fmax, bfc, a.dbound));
+    // INV: the ring offsets of one row per thread, for the epilogue
+    RingPair orow = {0, 0};
+    if (INV && tid < BM && row0 + tid < b.R) orow = a.ring_pair[b.j0 + row0 + tid];
 
     u32x4 ra[NA];
-    float2 rv[NU][16];
-    // DIR: Fourier offsets and weights of each unit's 8 rings, fetched one
-    // stage ahead of the data so that no data load waits on them
-    constexpr int NMU = INVERSE ? 1 : NU, NMQ = INVERSE ? 1 : 8;
-    RingPair mp1[NMU][NMQ], mp2[NMU][NMQ];
-    float mq1[NMU][NMQ], mq2[NMU][NMQ];
-    auto meta = [&](int kk, RingPair (*mp)[NMQ], float (*mq)[NMQ]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < NMU; ++u) {
-            int rc = (tid + u * NT) / (BN / 2);
-            // with 64 fields per tile a unit's rings are uniform over a wave:
-            // scalar loads into scalar registers
-            if constexpr (BN / 2 == 64) rc = __builtin_amdgcn_readfirstlane(rc);
-#pragma unroll
-            for (int q = 0; q < NMQ; ++q) {
-                int r = kk + rc * 8 + q;
-                RingPair o = {-1, -1};
-                float w = 0.f;
-                // units are whole waves (NUNIT is a multiple of 64), so uon is wave-uniform
-                if ((NUNIT % NT == 0 || __builtin_amdgcn_readfirstlane(uon[u] ? 1 : 0)) && r < b.R) {
-                    o = a.ring_pair[b.j0 + r];
-                    w = a.adjoint ? 1.f : ((const float *)a.ring_q)[b.j0 + r];
-                }
-                mp[u][q] = o;
-                mq[u][q] = w;
-            }
-        }
+    f32x4 rb[4];
+    float rn[8], rs[8];
+    // DIR: lane q < 8 holds ring 8 kh + q of the next load, fetched a stage ahead
+    RingPair mp = {0, 0};
+    float mq = 0.f, q1[8];
+    auto meta = [&](int kk) __attribute__((always_inline)) {
+        // past the last ring: repeated (with weight 0 when taken); nothing here
+        // may wait for these loads, which would wait for the operands' too
+        const int j = b.j0 + min(kk + 8 * kh + (lane & 7), b.R - 1);
+        mp = a.ring_pair[j];
+        mq = ((const float *)a.ring_q)[j];
     };
-
     auto load = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < NA; ++v) {
-            int idx = tid + v * NT;
-            int p = idx / (2 * BM * CH), rem = idx - p * 2 * BM * CH;
-            int hl = rem / (BM * CH);
-            rem -= hl * BM * CH;
-            int i = rem / CH, ch = rem - i * CH;
-            ra[v] = *reinterpret_cast<const u32x4 *>((hl ? Tl : Th) + p * pstride + (int64_t)(row0 + i) * lda + kk +
-                                                     ch * 8);
+        for (int i = 0; i < NA; ++i) {
+            // wave-loads of 64 rows: (plane, row half)
+            const int q = wave + 4 * i, half = q % FI, kc = q / FI & 1, pp = q / (2 * FI);
+            ra[i] = __builtin_bit_cast(
+                u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                           tab, 16 * lane, 16 * ((pp * chunks + kk / 8 + kc) * rows + row0 + 64 * half), 0));
         }
-        const float2 zero = {0.f, 0.f};
-        if constexpr (INVERSE) {
+        if (!bon) return;
+        if constexpr (INV) {
+            const float2 *src = (const float2 *)a.in + (int64_t)bfc * a.nspec + sb;
+            const int nrel = 2 * (kk + (tid & 3));
+            if (m + 2 * kk + 2 * BK - 1 <= a.trunc) {
 #pragma unroll
-            for (int u = 0; u < NIU; ++u) {
-                const int f = col0 / 2 + (u * NT + tid) / JC;
-                const int nrel = 2 * kk + 4 * ij;
-                const float2 *src = (const float2 *)a.in + (int64_t)f * a.nspec + sb + nrel;
-                if (f < a.nfld && m + nrel + 3 <= a.trunc) {
-                    const f32x4a8 v0 = *reinterpret_cast<const f32x4a8 *>(src);
-                    const f32x4a8 v1 = *reinterpret_cast<const f32x4a8 *>(src + 2);
-                    rv[0][4 * u] = float2{v0[0], v0[1]};
-                    rv[0][4 * u + 1] = float2{v0[2], v0[3]};
-                    rv[0][4 * u + 2] = float2{v1[0], v1[1]};
-                    rv[0][4 * u + 3] = float2{v1[2], v1[3]};
-                } else {
+                for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const f32x4a8 *>(src + nrel + 8 * i);
+            } else {
+                // past the last degree: repeated (the table's padding is zero)
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        rv[0][4 * u + t] = (f < a.nfld && m + nrel + t <= a.trunc) ? src[t] : zero;
+                for (int i = 0; i < 4; ++i) {
+                    const float2 z0 = src[min(nrel + 8 * i, a.trunc - m)], z1 = src[min(nrel + 8 * i + 1, a.trunc - m)];
+                    rb[i] = f32x4{z0.x, z0.y, z1.x, z1.y};
                 }
             }
         } else {
+            const float *four = (const float *)a.in;
+            const unsigned c = 2 * bfc + (tid & 1);
 #pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                // 8 consecutive rings of one field, north and south; the
-                // rings' offsets come from the previous stage's meta fetch
-                const int f = col0 / 2 + ufl[u];
-                const float2 *four = (const float2 *)a.in;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    float2 gn = zero, gs = zero;
-                    if (mp1[u][q].n >= 0 && f < a.nfld) {
-                        gn = four[((int64_t)mp1[u][q].n + m) * a.nfld + f];
-                        gs = four[((int64_t)mp1[u][q].s + m) * a.nfld + f];
-                    }
-                    rv[u][2 * q] = gn;
-                    rv[u][2 * q + 1] = gs;
-                }
+            for (int q = 0; q < 8; ++q) {
+                const int on = __builtin_amdgcn_readlane(mp.n, q), os = __builtin_amdgcn_readlane(mp.s, q);
+                rn[q] = (four + 2 * ((int64_t)on + m) * a.nfld)[c];
+                rs[q] = (four + 2 * ((int64_t)os + m) * a.nfld)[c];
+                const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mq), q));
+                q1[q] = kk + 8 * kh + q >= b.R ? 0.f : a.adjoint ? 1.f : w;
             }
         }
     };
     auto store = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < NA; ++v) {
-            int idx = tid + v * NT;
-            int p = idx / (2 * BM * CH), rem = idx - p * 2 * BM * CH;
-            int hl = rem / (BM * CH);
-            rem -= hl * BM * CH;
-            int i = rem / CH, ch = rem - i * CH;
-            *reinterpret_cast<u32x4 *>(&As[p][hl][i][(ch ^ sw(i)) * 8]) = ra[v];
-        }
-        if constexpr (INVERSE) {
-            // chunk u holds n = 4 ij + t (t = 0..3): kappa 2 ij + t / 2 of parity t & 1
+        for (int i = 0; i < NA; ++i) As[(wave + 4 * i) * 64 + lane] = ra[i];
+        if (!bon) return;
+        if constexpr (INV) {
+            // kappa 4 i + q of lane q -> kappa 4 i .. + 3 of lane q's value
+            unsigned w[8][NP];
+            const bool off = bri && m == 0;  // Im a^0_n is ignored
 #pragma unroll
-            for (int u = 0; u < NIU; ++u) {
-                const int fl = (u * NT + tid) / JC;
-                const float sc = isc[u];
-                unsigned hi, lo;
-                const int r0 = brow(fl, 0), r1 = brow(fl, 1);
-                const int k0 = ((ij >> 2) ^ sw(r0)) * 8 + 2 * (ij & 3), k1 = ((ij >> 2) ^ sw(r1)) * 8 + 2 * (ij & 3);
+            for (int i = 0; i < 4; ++i) {
+                float x[4] = {rb[i][0], rb[i][1], rb[i][2], rb[i][3]};
+                quad_transpose(x, bri, bp);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    split2<F16>(rv[0][4 * u + p].x * sc, rv[0][4 * u + 2 + p].x * sc, hi, lo);
-                    *reinterpret_cast<unsigned *>(&Bs[p][0][r0][k0]) = hi;
-                    *reinterpret_cast<unsigned *>(&Bs[p][1][r0][k0]) = lo;
-                    // Im a^0_n is ignored
-                    const float y0 = m == 0 ? 0.f : rv[0][4 * u + p].y * sc;
-                    const float y1 = m == 0 ? 0.f : rv[0][4 * u + 2 + p].y * sc;
-                    split2<F16>(y0, y1, hi, lo);
-                    *reinterpret_cast<unsigned *>(&Bs[p][0][r1][k1]) = hi;
-                    *reinterpret_cast<unsigned *>(&Bs[p][1][r1][k1]) = lo;
-                }
+                for (int t = 0; t < 2; ++t)
+                    split_pair<FORM>(off ? 0.f : x[2 * t] * scale, off ? 0.f : x[2 * t + 1] * scale, w[2 * i + t]);
+            }
+#pragma unroll
+            for (int kc = 0; kc < 2; ++kc) {
+                u32x4 *dst = Bs + (2 * bp + kc) * UB + bri * URI + bf;
+#pragma unroll
+                for (int h = 0; h < NP; ++h)
+                    dst[h * 4 * UB] = u32x4{w[4 * kc][h], w[4 * kc + 1][h], w[4 * kc + 2][h], w[4 * kc + 3][h]};
             }
         } else {
+            // hemispheric fold: parity 0 takes q (north + south), parity 1 q (north - south)
 #pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                if (!uon[u]) continue;
-                const int idx = tid + u * NT;
-                const float sc = usc[u];
-                float x[8];
-                u32x4 hi, lo;
-                // hemispheric fold: parity 0 takes q (north + south), parity 1 q (north - south)
-                const int cp = ufl[u], rc = idx / (BN / 2);
-                const int r0 = brow(cp, 0), r1 = brow(cp, 1);
-                const int k0 = (rc ^ sw(r0)) * 8, k1 = (rc ^ sw(r1)) * 8;
+            for (int p = 0; p < 2; ++p) {
+                unsigned w[4][NP];
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const float sg = p ? -1.f : 1.f;
+                for (int i = 0; i < 4; ++i) {
+                    float x[2];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) x[q] = (mq1[u][q] * sc) * (rv[u][2 * q].x + sg * rv[u][2 * q + 1].x);
-                    split8<F16>(x, hi, lo);
-                    *reinterpret_cast<u32x4 *>(&Bs[p][0][r0][k0]) = hi;
-                    *reinterpret_cast<u32x4 *>(&Bs[p][1][r0][k0]) = lo;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) x[q] = (mq1[u][q] * sc) * (rv[u][2 * q].y + sg * rv[u][2 * q + 1].y);
-                    split8<F16>(x, hi, lo);
-                    *reinterpret_cast<u32x4 *>(&Bs[p][0][r1][k1]) = hi;
-                    *reinterpret_cast<u32x4 *>(&Bs[p][1][r1][k1]) = lo;
+                    for (int t = 0; t < 2; ++t) {
+                        const int q = 2 * i + t;
+                        x[t] = (q1[q] * scale) * (p ? rn[q] - rs[q] : rn[q] + rs[q]);
+                    }
+                    split_pair<FORM>(x[0], x[1], w[i]);
                 }
+                u32x4 *dst = Bs + (2 * p + kh) * UB + (tid & 1) * URI + bf;
+#pragma unroll
+                for (int h = 0; h < NP; ++h) dst[h * 4 * UB] = u32x4{w[0][h], w[1][h], w[2][h], w[3][h]};
             }
         }
     };
 
-    f32x4 acc[2][FM][FN];
+    f32x16 acc[2][NI][2];
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) acc[p][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0.f;
 
-    // a wave whose whole sub-tile lies past the valid rows or columns (the
-    // ragged edge of an m block or of the field range) still loads and
-    // stores its share of the operand tiles but skips the MFMAs
-    const bool mfma_on = __builtin_amdgcn_readfirstlane(
-        (row0 + wr < (INVERSE ? b.R : b.K0) && (INVERSE ? col0 + wc < ncol : col0 / 2 + (wc & (BN / 2 - 1)) < a.nfld))
-            ? 1
-            : 0);
-
-    // The K loop, in two copies: with MFMAs, and without them for a wave
-    // whose sub-tile is wholly ragged (a wave-uniform branch outside the
-    // loop keeps the accumulators in the MFMA accumulation registers).
-    auto kloop = [&](auto with_mfma) __attribute__((always_inline)) {
-        if (!INVERSE) meta(0, mp1, mq1);
+    auto kloop = [&](auto ni_c) __attribute__((always_inline)) {
+        constexpr int NA_I = decltype(ni_c)::value;  // row fragments in use
+        if (nstages == 0) return;                    // a wavenumber that no ring carries
+        if (!INV) meta(0);
         load(0);
-        if (!INVERSE && nstages > 1) meta(BK, mp2, mq2);
+        if (!INV) meta(BK);
         for (int s = 0; s < nstages; ++s) {
-            store();  // uses the weights mq1 of stage s
-            if (!INVERSE && s + 1 < nstages) {
-#pragma unroll
-                for (int u = 0; u < NMU; ++u)
-#pragma unroll
-                    for (int q = 0; q < NMQ; ++q) {
-                        mp1[u][q] = mp2[u][q];
-                        mq1[u][q] = mq2[u][q];
-                    }
-            }
+            store();
             __syncthreads();
             if (s + 1 < nstages) load((s + 1) * BK);  // in flight during the MFMAs
-            if (!INVERSE && s + 2 < nstages) meta((s + 2) * BK, mp2, mq2);
-            if constexpr (decltype(with_mfma)::value) {
+            if (!INV) meta((s + 2) * BK);
+            if constexpr (NA_I > 0) {
+                const int kc = lane >> 5, ln = lane & 31;
 #pragma unroll
-                for (int q = 0; q < BK; q += 32) {
-                    const int kc = q / 8 + (lane >> 4);
+                for (int p = 0; p < 2; ++p) {
+                    u32x4 av[NA_I][NP], bv[2][NP];
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        u32x4 ah[FM], al[FM], bh[FN], bl[FN];
+                    for (int h = 0; h < NP; ++h) {
 #pragma unroll
-                        for (int i = 0; i < FM; ++i) {
-                            const int ai = wr + i * 16 + (lane & 15);
-                            const int ka = (kc ^ sw(ai)) * 8;
-                            ah[i] = *reinterpret_cast<const u32x4 *>(&As[p][0][ai][ka]);
-                            al[i] = *reinterpret_cast<const u32x4 *>(&As[p][1][ai][ka]);
-                        }
+                        for (int i = 0; i < NA_I; ++i)
+                            av[i][h] = As[((2 * h + p) * 2 + kc) * UA + 32 * (WR * i + wr) + ln];
 #pragma unroll
-                        for (int j = 0; j < FN; ++j) {
-                            const int bj = wc + j * 16 + (lane & 15);
-                            const int kb = (kc ^ sw(bj)) * 8;
-                            bh[j] = *reinterpret_cast<const u32x4 *>(&Bs[p][0][bj][kb]);
-                            bl[j] = *reinterpret_cast<const u32x4 *>(&Bs[p][1][bj][kb]);
-                        }
-#pragma unroll
-                        for (int i = 0; i < FM; ++i)
-#pragma unroll
-                            for (int j = 0; j < FN; ++j) {
-                                f32x4 c = acc[p][i][j];
-                                c = mfma_split<F16>(ah[i], bl[j], c);
-                                c = mfma_split<F16>(al[i], bh[j], c);
-                                c = mfma_split<F16>(ah[i], bh[j], c);
-                                acc[p][i][j] = c;
-                            }
+                        for (int j = 0; j < 2; ++j) bv[j][h] = Bs[((2 * h + p) * 2 + kc) * UB + j * URI + 32 * fj + ln];
                     }
+                    // piece pairs (x, y) with x + y < NP, smallest products first
+#pragma unroll
+                    for (int t = NP - 1; t >= 0; --t)
+#pragma unroll
+                        for (int x = t; x >= 0; --x)
+#pragma unroll
+                            for (int i = 0; i < NA_I; ++i)
+#pragma unroll
+                                for (int j = 0; j < 2; ++j)
+                                    acc[p][i][j] = mfma_split<FORM>(av[i][x], bv[j][t - x], acc[p][i][j]);
                 }
             }
             __syncthreads();
         }
     };
-    if (mfma_on)
-        kloop(std::true_type{});
+    // Row fragments of this wave that hold data (wave-uniform; none when its
+    // fields are past the last): the others skip their LDS reads and MFMAs,
+    // while the wave still loads and stores its share.  One copy of the K loop
+    // per count keeps the accumulators in place.
+    const int f = f0 + 32 * fj + (lane & 31);
+    const int nrow = f0 + 32 * fj < a.nfld ? (INV ? b.R : b.K0) - row0 - 32 * wr : 0;
+    if (nrow <= 0)
+        kloop(std::integral_constant<int, 0>{});
+    else if (NI == 1 || nrow > 32 * WR)
+        kloop(std::integral_constant<int, NI>{});
     else
-        kloop(std::false_type{});
+        kloop(std::integral_constant<int, 1>{});
 
-    // unscaling exponent of each of the lane's columns: e_m (+ E_f)
-    int eu[FN];
+    auto frag_row = [&](int i, int v) { return 32 * (WR * i + wr) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
+    // undoes the scales of the table block and of this lane's field
+    int e = 0;
+    if constexpr (FORM != SHTX_FP32) e = -(b.e + (F16 ? field_exp(a.fmax, min(f, a.nfld - 1), a.dbound) : 0));
+    auto unscale = [&](float x) { return FORM == SHTX_FP32 ? x : ldexpf(x, e); };
+    if constexpr (INV) {
+        // a lane holds its field's real and imaginary part of each row: runs of
+        // 32 fields straight to both hemispheres' rows
+        RingPair *orows = reinterpret_cast<RingPair *>(smem);
+        if (tid < BM) orows[tid] = orow;
+        __syncthreads();
+        float2 *four = (float2 *)a.out;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        eu[j] = b.e;
-        if constexpr (F16) {
-            const int bj = wc + j * 16 + (lane & 15);
-            const int f = INVERSE ? (col0 + bj) >> 1 : col0 / 2 + (bj & (BN / 2 - 1));
-            if (f < a.nfld) eu[j] += field_exp(a.fmax, f, a.dbound);
-        }
-    }
-    if constexpr (INVERSE) {
-        static_assert(BM * BN * 2 <= NSMEM16, "staged inverse tile must fit the operand LDS");
-        inv_epilogue_staged<BM, BN, NT, FM, FN>(a, b, m, row0, col0, wr, wc, lane, tid, reinterpret_cast<float *>(smem16),
-                                                [&](int hs, int i, int j, int v) {
-                                                    const float s0 = acc[0][i][j][v], s1 = acc[1][i][j][v];
-                                                    return ldexpf(hs ? s0 - s1 : s0 + s1, -eu[j]);
-                                                });
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = frag_row(i, v);
+                const RingPair o = orows[r];
+                if (row0 + r >= b.R || f >= a.nfld) continue;
+                const float x0 = acc[0][i][0][v], x1 = acc[1][i][0][v], y0 = acc[0][i][1][v], y1 = acc[1][i][1][v];
+                four[((int64_t)o.n + m) * a.nfld + f] = float2{unscale(x0 + x1), unscale(y0 + y1)};
+                four[((int64_t)o.s + m) * a.nfld + f] = float2{unscale(x0 - x1), unscale(y0 - y1)};
+            }
     } else {
-        // staged per column half as [field][n], written as contiguous runs
-        // (as in k_leg_mfma)
-        constexpr int FH = BN / 4, RS = 2 * BM + 1;
-        static_assert(FH * RS * 2 * 2 <= NSMEM16, "staged output half must fit the operand LDS");
-        float *st = reinterpret_cast<float *>(smem16);
+        // 32 fields at a time as [field][n], written as runs of n
+        constexpr int RS = 2 * BM + 1;
+        float2 *st = reinterpret_cast<float2 *>(smem);
         float2 *spec = (float2 *)a.out;
-        const int nrel0 = 2 * row0;
-        const int nvalid = min(2 * BM, a.trunc - m - nrel0 + 1);
+        const int nrel0 = 2 * row0, nvalid = min(2 * BM, a.trunc - m - nrel0 + 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            __syncthreads();
-            // operand column bj is field bj % (BN / 2), real part for
-            // bj < BN / 2; fragments of 16 columns never straddle a half
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int bj0 = wc + j * 16;
-                if (((bj0 & (BN / 2 - 1)) / FH) != h) continue;
-                const int ri = bj0 / (BN / 2);
-                const int fl = (bj0 & (BN / 2 - 1)) - h * FH + (lane & 15);
+        for (int h = 0; h < FJ; ++h) {
+            if (h) __syncthreads();
+            if (fj == h) {
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
-                    for (int i = 0; i < FM; ++i)
+                    for (int i = 0; i < NI; ++i)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int k = wr + i * 16 + 4 * (lane >> 4) + v;
-                            float val = ldexpf(acc[p][i][j][v], -eu[j]);
-                            if (m == 0 && ri) val = 0.f;
-                            st[(fl * RS + p + 2 * k) * 2 + ri] = val;
-                        }
+                        for (int v = 0; v < 16; ++v)
+                            st[(lane & 31) * RS + p + 2 * frag_row(i, v)] =
+                                float2{unscale(acc[p][i][0][v]), m == 0 ? 0.f : unscale(acc[p][i][1][v])};
             }
             __syncthreads();
-            const int fbase = col0 / 2 + h * FH;
-            for (int fl = wave; fl < FH; fl += NW) {
-                const int f = fbase + fl;
-                if (f >= a.nfld) break;
-                float2 *dst = spec + (int64_t)f * a.nspec + sb + nrel0;
-                for (int nr = lane; nr < nvalid; nr += 64)
-                    dst[nr] = float2{st[(fl * RS + nr) * 2], st[(fl * RS + nr) * 2 + 1]};
+            for (int fl = wave; fl < 32; fl += 4) {
+                if (f0 + h * 32 + fl >= a.nfld) break;
+                float2 *dst = spec + (int64_t)(f0 + h * 32 + fl) * a.nspec + sb + nrel0;
+                for (int nr = lane; nr < nvalid; nr += 64) dst[nr] = st[fl * RS + nr];
             }
         }
     }
@@ -1170,13 +982,7 @@ GemmArgs make_args(const Plan &p, bool inverse_shape, const void *in, void *out,
     a.nfld = p.nfld;
     a.adjoint = adjoint ? 1 : 0;
     a.nspec = p.nspec;
-    if (split_form(p.prec)) {
-        a.tab = inverse_shape ? p.d_tab_rk : p.d_tab_kr;
-        a.tab_lo = inverse_shape ? p.d_tab_rk_lo : p.d_tab_kr_lo;
-    } else {
-        a.tab = inverse_shape ? p.d_tab_kr : p.d_tab_rk;
-        a.tab_lo = nullptr;
-    }
+    a.tab = inverse_shape ? p.d_tab_inv : p.d_tab_dir;
     // the inverse-shaped launch splits spectral coefficients (bounded by the
     // field maximum itself); the direct-shaped one splits q_r (G_north +-
     // G_south), bounded by 2 max_r q_r times the largest Fourier value
@@ -1185,16 +991,13 @@ GemmArgs make_args(const Plan &p, bool inverse_shape, const void *in, void *out,
     return a;
 }
 
-// Host check that every tile of items [first, first + count) of a work list
-// reads and writes inside the table, Fourier and spectral arrays for the
+// Host check that every tile of a work list reads and writes inside the table, Fourier and spectral arrays for the
 // given tile sizes.  Run when a plan's work lists are built, not per launch.
-bool check_items(const Plan &p, const std::vector<GemmItem> &items, size_t first, size_t count, bool inverse_shape,
-                 int bm, int bn, int bk)
+bool check_items(const Plan &p, const std::vector<GemmItem> &items, bool inverse_shape, int bm, int bn, int bk)
 {
-    if (count == 0 || count % kXcds || first + count > items.size()) return false;
+    if (items.empty() || items.size() % kXcds) return false;
     int ncol = 2 * p.nfld;
-    for (size_t q = first; q < first + count; ++q) {
-        const GemmItem &it = items[q];
+    for (const GemmItem &it : items) {
         if (it.m < 0) continue;
         if (it.m > p.trunc) return false;
         const MBlock &b = p.mb[it.m];
@@ -1211,44 +1014,12 @@ bool check_items(const Plan &p, const std::vector<GemmItem> &items, size_t first
     return true;
 }
 
-// A work list's main part with bm x bn tiles and its tail part (if any) with
-// bm x tail_bn tiles.
-bool check_work_list(const Plan &p, const std::vector<GemmItem> &items, int nmain, bool inverse_shape, int bm,
-                     int bn, int tail_bn, int bk)
+bool check_work_list(const Plan &p, const std::vector<GemmItem> &items, bool inverse_shape, int bm, int bn, int bk)
 {
-    bool ok = nmain >= 1 && nmain <= (int)items.size() &&
-              check_items(p, items, 0, (size_t)nmain, inverse_shape, bm, bn, bk);
-    if (ok && nmain < (int)items.size())
-        ok = tail_bn > 0 && check_items(p, items, (size_t)nmain, items.size() - nmain, inverse_shape, bm, tail_bn, bk);
+    const bool ok = check_items(p, items, inverse_shape, bm, bn, bk);
     if (!ok && std::getenv("SHTX_DEBUG"))
         std::fprintf(stderr, "shtx: Legendre GEMM work-list check failed (%s)\n", inverse_shape ? "inverse" : "direct");
     return ok;
-}
-
-
-// One launch over items [first, first + count) of a work list, tiles bm x bn.
-template <typename T, int BK, bool INV>
-hipError_t launch_mfma_part(const GemmArgs &args, int first, int count, int bm, int bn, hipStream_t s)
-{
-    GemmArgs a = args;
-    a.items += first;
-    const int grid = count;
-#define SHTX_TILE(BM, BN, NW)                                              \
-    if (bm == BM && bn == BN) {                                            \
-        k_leg_mfma<T, BM, BN, BK, INV, NW><<<grid, 64 * NW, 0, s>>>(a);    \
-        return hipGetLastError();                                          \
-    }
-    if constexpr (sizeof(T) == 4) {
-        SHTX_TILE(128, 128, 8)
-        SHTX_TILE(64, 128, 8)
-        SHTX_TILE(128, 64, 8)
-    } else {
-        SHTX_TILE(64, 64, 8)
-        SHTX_TILE(32, 64, 8)
-        SHTX_TILE(64, 32, 4)
-    }
-#undef SHTX_TILE
-    return hipErrorInvalidValue;
 }
 
 // The few-fields kernel with fn column fragments (gemm_narrow).
@@ -1274,18 +1045,23 @@ hipError_t launch_narrow(const GemmArgs &a, int fn, int grid, hipStream_t s)
     return hipErrorInvalidValue;
 }
 
-template <typename T, int BK, bool INV>
-hipError_t launch_mfma(const Plan &p, const GemmArgs &a, int bm, int bn, hipStream_t s)
+template <bool INV>
+hipError_t launch_fp64(const Plan &p, const GemmArgs &a, int bm, int bn, hipStream_t s)
 {
     // the work lists were checked against these shapes when they were built
-    const std::vector<GemmItem> &items = INV ? p.inv_items : p.dir_items;
-    const int nmain = INV ? p.inv_nmain : p.dir_nmain, tail_bn = INV ? p.inv_tail_bn : p.dir_tail_bn;
-    if (!p.shapes_ok || nmain < 1) return hipErrorInvalidValue;
-    const int narrow = INV ? p.inv_narrow : p.dir_narrow;
-    if (narrow) return launch_narrow<T, INV>(a, narrow, nmain, s);
-    hipError_t e = launch_mfma_part<T, BK, INV>(a, 0, nmain, bm, bn, s);
-    if (e != hipSuccess || nmain == (int)items.size()) return e;
-    return launch_mfma_part<T, BK, INV>(a, nmain, (int)items.size() - nmain, bm, tail_bn, s);
+    const int grid = (int)(INV ? p.inv_items : p.dir_items).size(), narrow = INV ? p.inv_narrow : p.dir_narrow;
+    if (!p.shapes_ok || grid < 1) return hipErrorInvalidValue;
+    if (narrow) return launch_narrow<double, INV>(a, narrow, grid, s);
+#define SHTX_TILE(BM, BN, NW)                                              \
+    if (bm == BM && bn == BN) {                                            \
+        k_leg_mfma<double, BM, BN, 16, INV, NW><<<grid, 64 * NW, 0, s>>>(a); \
+        return hipGetLastError();                                          \
+    }
+    SHTX_TILE(64, 64, 8)
+    SHTX_TILE(32, 64, 8)
+    SHTX_TILE(64, 32, 4)
+#undef SHTX_TILE
+    return hipErrorInvalidValue;
 }
 
 // Largest magnitude of each field's spectral coefficients (Re and Im of
@@ -1326,31 +1102,36 @@ __global__ __launch_bounds__(1024) void k_spec_absmax(const float2 *spec, int64_
     }
 }
 
-// K-stage depth of the split kernels: 128 x 128 direct tiles take 64-deep
-// stages (each tile row of a stage one whole 128-byte line of the table;
-// measured 9.9 -> 8.8 ms at TCo1279), every other shape 32 (64 measured
-// slower for the inverse)
-constexpr int split_stage_depth(bool inverse, int bm) { return (!inverse && bm == 128) ? 64 : 32; }
-
-template <bool F16, bool INV>
+template <int FORM, bool INV>
 hipError_t launch_split(const Plan &p, const GemmArgs &a, int bm, int bn, hipStream_t s)
 {
-    const std::vector<GemmItem> &items = INV ? p.inv_items : p.dir_items;
-    const int grid = (int)items.size();
+    const int grid = (int)(INV ? p.inv_items : p.dir_items).size();
     if (!p.shapes_ok || grid < 1) return hipErrorInvalidValue;
-    if (bm == 128 && bn == 128)
-        k_leg_split<F16, 128, 128, split_stage_depth(INV, 128), INV, 8><<<grid, 512, 0, s>>>(a);
-    else if (bm == 64 && bn == 128)
-        k_leg_split<F16, 64, 128, split_stage_depth(INV, 64), INV, 4><<<grid, 256, 0, s>>>(a);
-    else
+    if (bm == 128 && bn == 128) {
+        k_leg_split<FORM, 2, 2, INV><<<grid, 256, 0, s>>>(a);
+    } else if (bm == 64 && bn == 128) {
+        k_leg_split<FORM, 1, 2, INV><<<grid, 256, 0, s>>>(a);
+    } else if constexpr (FORM == SHTX_FP32) {
+        if (bm != 128 || bn != 64) return hipErrorInvalidValue;
+        k_leg_split<FORM, 2, 1, INV><<<grid, 256, 0, s>>>(a);
+    } else {
         return hipErrorInvalidValue;
+    }
     return hipGetLastError();
+}
+
+template <bool INV>
+hipError_t launch_fp32(const Plan &p, const GemmArgs &a, int bm, int bn, hipStream_t s)
+{
+    const int narrow = INV ? p.inv_narrow : p.dir_narrow;
+    if (!narrow) return launch_split<SHTX_FP32, INV>(p, a, bm, bn, s);
+    if (!p.shapes_ok) return hipErrorInvalidValue;
+    return launch_narrow<float, INV>(a, narrow, (int)(INV ? p.inv_items : p.dir_items).size(), s);
 }
 
 }  // namespace
 
-// Tile shapes with a kernel instantiation (split forms: 128 x 128 with eight
-// waves, 64 x 128 with four).
+// Tile shapes with a kernel instantiation.
 int gemm_tile_candidates(int prec, int *bm, int *bn, int max)
 {
     static const int f32[][2] = {{128, 128}, {64, 128}, {128, 64}};
@@ -1381,9 +1162,13 @@ bool gemm_tile_supported(int prec, int bm, int bn)
 // 150 / 206 at 16 fields but 360 / 280 at 24, direct 152 / 252 at 16 and 247 /
 // 319 at 32 (its operand loads are fewer), FP64 227 / 240 at 8 and 393 / 308
 // at 12.
-int gemm_narrow(int prec, int nfld, bool inverse)
+int gemm_narrow(int prec, int nfld, bool inverse, int64_t tab_elems)
 {
     const int ncol = 2 * nfld;
+    // any field count, 16 fields at a time, where the three pieces of both
+    // layouts (12 bytes an entry, against 8 for plain values) would take more
+    // than a third of the memory (truncations above about 2700)
+    if (prec == SHTX_FP32 && ncol > 32 && 12 * tab_elems > (int64_t)96 << 30) return 2;
     if (ncol <= 16 && (prec == SHTX_FP32 || prec == SHTX_FP64)) return 1;
     if (ncol <= 32 && prec == SHTX_FP32) return 2;
     if (ncol <= 64 && prec == SHTX_FP32 && !inverse) return 4;
@@ -1392,52 +1177,47 @@ int gemm_narrow(int prec, int nfld, bool inverse)
 
 bool gemm_shapes_ok(const Plan &p)
 {
-    const bool split = split_form(p.prec);
-    const int bk_inv = split ? split_stage_depth(true, p.inv_bm) : 16;
-    const int bk_dir = split ? split_stage_depth(false, p.dir_bm) : 16;
+    const int bk = 16;
     if (!gemm_tile_supported(p.prec, p.inv_bm, p.inv_bn) || !gemm_tile_supported(p.prec, p.dir_bm, p.dir_bn))
         return false;
     // each direction's list is for its tiles, or for the few-fields kernel's
-    auto dir_ok = [&](const std::vector<GemmItem> &items, int nmain, bool inverse, int narrow, int bm, int bn,
-                      int tail_bn, int bk) {
-        if (!narrow) return check_work_list(p, items, nmain, inverse, bm, bn, tail_bn, bk);
-        return 2 * p.nfld <= 16 * narrow &&
-               check_work_list(p, items, nmain, inverse, kNarrowRows, 16 * narrow, 0, 4);
+    auto dir_ok = [&](const std::vector<GemmItem> &items, bool inverse, int narrow, int bm, int bn) {
+        return narrow ? check_work_list(p, items, inverse, kNarrowRows, 16 * narrow, 4)
+                      : check_work_list(p, items, inverse, bm, bn, bk);
     };
-    return (p.inv_items.empty() ||
-            dir_ok(p.inv_items, p.inv_nmain, true, p.inv_narrow, p.inv_bm, p.inv_bn, p.inv_tail_bn, bk_inv)) &&
-           dir_ok(p.dir_items, p.dir_nmain, false, p.dir_narrow, p.dir_bm, p.dir_bn, p.dir_tail_bn, bk_dir);
+    return (p.inv_items.empty() || dir_ok(p.inv_items, true, p.inv_narrow, p.inv_bm, p.inv_bn)) &&
+           dir_ok(p.dir_items, false, p.dir_narrow, p.dir_bm, p.dir_bn);
 }
 
 hipError_t launch_gemm_inverse(const Plan &p, const void *spec, void *four, unsigned *fmax, hipStream_t s)
 {
     GemmArgs a = make_args(p, true, spec, four, false, fmax);
     if (p.inv_items.empty()) return hipSuccess;
-    if (p.prec == SHTX_FP64) return launch_mfma<double, 16, true>(p, a, p.inv_bm, p.inv_bn, s);
-    if (p.prec == SHTX_FP32) return launch_mfma<float, 16, true>(p, a, p.inv_bm, p.inv_bn, s);
+    if (p.prec == SHTX_FP64) return launch_fp64<true>(p, a, p.inv_bm, p.inv_bn, s);
+    if (p.prec == SHTX_FP32) return launch_fp32<true>(p, a, p.inv_bm, p.inv_bn, s);
     if (p.prec == SHTX_FP16X3) {
         if (!fmax) return hipErrorInvalidValue;
         k_clear_u32<<<(p.nfld + 255) / 256, 256, 0, s>>>(fmax, p.nfld);
         k_spec_absmax<<<dim3(kAbsmaxChunks, p.nfld), 1024, 0, s>>>((const float2 *)spec, p.nspec, p.trunc, fmax);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        return launch_split<true, true>(p, a, p.inv_bm, p.inv_bn, s);
+        return launch_split<SHTX_FP16X3, true>(p, a, p.inv_bm, p.inv_bn, s);
     }
-    return launch_split<false, true>(p, a, p.inv_bm, p.inv_bn, s);
+    return launch_split<SHTX_BF16X3, true>(p, a, p.inv_bm, p.inv_bn, s);
 }
 
 hipError_t launch_gemm_direct(const Plan &p, const void *four, void *spec, bool adjoint, unsigned *fmax,
                               hipStream_t s)
 {
     GemmArgs a = make_args(p, false, four, spec, adjoint, fmax);
-    if (p.prec == SHTX_FP64) return launch_mfma<double, 16, false>(p, a, p.dir_bm, p.dir_bn, s);
-    if (p.prec == SHTX_FP32) return launch_mfma<float, 16, false>(p, a, p.dir_bm, p.dir_bn, s);
+    if (p.prec == SHTX_FP64) return launch_fp64<false>(p, a, p.dir_bm, p.dir_bn, s);
+    if (p.prec == SHTX_FP32) return launch_fp32<false>(p, a, p.dir_bm, p.dir_bn, s);
     if (p.prec == SHTX_FP16X3) {
         // the ring r2c FFT that wrote the workspace recorded each field's maximum
         if (!fmax) return hipErrorInvalidValue;
-        return launch_split<true, false>(p, a, p.dir_bm, p.dir_bn, s);
+        return launch_split<SHTX_FP16X3, false>(p, a, p.dir_bm, p.dir_bn, s);
     }
-    return launch_split<false, false>(p, a, p.dir_bm, p.dir_bn, s);
+    return launch_split<SHTX_BF16X3, false>(p, a, p.dir_bm, p.dir_bn, s);
 }
 
 }  // namespace shtx

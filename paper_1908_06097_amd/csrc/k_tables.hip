@@ -7,6 +7,8 @@
 // (Section 3.1.1) keeps all such data resident on the GPU.
 #include <cmath>
 
+#include <type_traits>
+
 #include "shtx_internal.h"
 
 namespace shtx {
@@ -184,25 +186,46 @@ __device__ inline unsigned short bf16_rne(float f)
 
 __device__ inline float bf16_to_f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
-// Column recurrence over n for one (m, ring).  MODE 0: per-m max |P̄| only;
-// MODE 1: store FP64; MODE 2: store FP32; MODE 3: store split BF16 hi + lo
-// scaled by 2^e_m, e_m putting the block's largest entry in [1/2, 1); MODE 4:
-// store split IEEE half hi + lo scaled by 2^e_m, the largest entry in
-// [2^13, 2^14) (half's 5-bit exponent: entries that small relative to the
-// block's largest lose their lo half to the subnormal range, a loss relative
-// to that largest entry of at most 2^-38).  Both table layouts are written:
-// kr = [p][k][r] and rk = [p][r][k] (k = (n - m - p) / 2).
-template <int MODE>
-__global__ void k_legendre_table(int trunc, const double *mu, const double *diag, const int *diag_e, MBlock *mbs,
-                                 unsigned long long *mmax, void *tab_kr, void *tab_rk,
-                                 void *lo_kr, void *lo_rk)
+// 16-bit pieces of v, most significant first: each the nearest to what the
+// ones before it leave.
+template <int PREC>
+__device__ inline void table_split(double v, unsigned short *w)
 {
+    if (PREC == SHTX_FP16X3) {
+        const _Float16 h = (_Float16)(float)v, l = (_Float16)(float)(v - (double)h);
+        w[0] = __builtin_bit_cast(unsigned short, h);
+        w[1] = __builtin_bit_cast(unsigned short, l);
+        return;
+    }
+#pragma unroll
+    for (int h = 0; h < split_pieces(PREC); ++h) {
+        w[h] = bf16_rne((float)v);
+        v -= (double)bf16_to_f(w[h]);
+    }
+}
+
+// Column recurrence over n for one (m, ring).  MODE 0: per-m max |P̄| only (the
+// split forms' exponents).  MODE 1: store, in the forms of the plan's
+// precision: plain values of type T as tab_inv = [p][k][r] and tab_dir =
+// [p][r][k] (k = (n - m - p) / 2), or with INV_UNITS / DIR_UNITS 16-bit pieces
+// [piece][p][k / 8][r][k % 8] and [piece][p][r / 8][k][r % 8].  The split forms'
+// pieces are scaled by 2^e_m: BF16x3 puts the block's largest entry in [1/2, 1);
+// FP16x3 in [2^13, 2^14) (half's 5-bit exponent: entries that small relative
+// to the block's largest lose their lo half to the subnormal range, a loss
+// relative to that largest entry of at most 2^-38).
+template <int PREC, int MODE, bool INV_UNITS, bool DIR_UNITS>
+__global__ void k_legendre_table(int trunc, const double *mu, const double *diag, const int *diag_e, MBlock *mbs,
+                                 unsigned long long *mmax, void *tab_inv, void *tab_dir)
+{
+    typedef typename std::conditional<PREC == SHTX_FP64, double, float>::type T;
+    constexpr bool SCALED = MODE == 1 && (PREC == SHTX_BF16X3 || PREC == SHTX_FP16X3);
+    constexpr int NP = split_pieces(PREC);
     const int m = blockIdx.y;
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     const MBlock b = mbs[m];
     // exponent: max * 2^e in [2^(t-1), 2^t), t = 0 (BF16) or 14 (IEEE half)
-    constexpr int t_top = MODE == 4 ? 14 : 0;
-    if (MODE >= 3 && r == 0 && blockIdx.x == 0) {
+    constexpr int t_top = PREC == SHTX_FP16X3 ? 14 : 0;
+    if (SCALED && r == 0 && blockIdx.x == 0) {
         double mx = __longlong_as_double((long long)mmax[m]);
         int E = 0;
         if (mx > 0.0) frexp(mx, &E);
@@ -212,7 +235,7 @@ __global__ void k_legendre_table(int trunc, const double *mu, const double *diag
     const int j = b.j0 + r;
     const double x = mu[j];
     double scale = 1.0;
-    if (MODE >= 3) {
+    if (SCALED) {
         double mx = __longlong_as_double((long long)mmax[m]);
         int E = 0;
         if (mx > 0.0) frexp(mx, &E);
@@ -224,33 +247,25 @@ __global__ void k_legendre_table(int trunc, const double *mu, const double *diag
             vmax = fmax(vmax, fabs(v));
             return;
         }
-        int t = n - m, par = t & 1, k = t >> 1;
-        int64_t ikr = b.off_kr + (int64_t)par * b.Kp * b.Rp + (int64_t)k * b.Rp + r;
-        int64_t irk = b.off_rk + (int64_t)par * b.Rp * b.Kp + (int64_t)r * b.Kp + k;
-        if (MODE == 1) {
-            ((double *)tab_kr)[ikr] = v;
-            ((double *)tab_rk)[irk] = v;
-        } else if (MODE == 2) {
-            ((float *)tab_kr)[ikr] = (float)v;
-            ((float *)tab_rk)[irk] = (float)v;
-        } else if (MODE == 3) {
-            double vs = v * scale;
-            unsigned short hi = bf16_rne((float)vs);
-            unsigned short lo = bf16_rne((float)(vs - (double)bf16_to_f(hi)));
-            ((unsigned short *)tab_kr)[ikr] = hi;
-            ((unsigned short *)tab_rk)[irk] = hi;
-            ((unsigned short *)lo_kr)[ikr] = lo;
-            ((unsigned short *)lo_rk)[irk] = lo;
+        const int t = n - m, par = t & 1, k = t >> 1;
+        const int64_t blk = 2 * (int64_t)b.Kp * b.Rp;  // entries of the block, and of each piece
+        unsigned short w[NP];
+        if (INV_UNITS || DIR_UNITS) table_split<PREC>(v * scale, w);
+        if (INV_UNITS) {
+            unsigned short *dst = (unsigned short *)tab_inv + NP * b.off;
+#pragma unroll
+            for (int h = 0; h < NP; ++h)
+                dst[h * blk + (((int64_t)par * (b.Kp / 8) + k / 8) * b.Rp + r) * 8 + k % 8] = w[h];
         } else {
-            double vs = v * scale;
-            _Float16 h = (_Float16)(float)vs;
-            _Float16 l = (_Float16)(float)(vs - (double)h);
-            unsigned short hi = __builtin_bit_cast(unsigned short, h);
-            unsigned short lo = __builtin_bit_cast(unsigned short, l);
-            ((unsigned short *)tab_kr)[ikr] = hi;
-            ((unsigned short *)tab_rk)[irk] = hi;
-            ((unsigned short *)lo_kr)[ikr] = lo;
-            ((unsigned short *)lo_rk)[irk] = lo;
+            ((T *)tab_inv)[b.off + ((int64_t)par * b.Kp + k) * b.Rp + r] = (T)v;
+        }
+        if (DIR_UNITS) {
+            unsigned short *dst = (unsigned short *)tab_dir + NP * b.off;
+#pragma unroll
+            for (int h = 0; h < NP; ++h)
+                dst[h * blk + (((int64_t)par * (b.Rp / 8) + r / 8) * b.Kp + k) * 8 + r % 8] = w[h];
+        } else {
+            ((T *)tab_dir)[b.off + ((int64_t)par * b.Rp + r) * b.Kp + k] = (T)v;
         }
     };
     // the column runs on values scaled by 2^-E (E <= 0 from the seed; a power
@@ -297,35 +312,34 @@ hipError_t launch_legendre_tables(Plan &p, hipStream_t s)
     // host check: every table write of every (m, r) lands inside the allocation
     for (const MBlock &b : p.mb) {
         if (b.R > b.Rp || b.K0 > b.Kp || b.j0 + b.R > NL) return hipErrorInvalidValue;
-        if (b.off_kr + 2 * (int64_t)b.Kp * b.Rp > p.tab_elems) return hipErrorInvalidValue;
+        if (b.off + 2 * (int64_t)b.Kp * b.Rp > p.tab_elems) return hipErrorInvalidValue;
     }
-    size_t el = p.prec == SHTX_FP64 ? 8 : p.prec == SHTX_FP32 ? 4 : 2;
-    hipError_t e = hipMemsetAsync(p.d_tab_kr, 0, el * p.tab_elems, s);
-    if (e == hipSuccess) e = hipMemsetAsync(p.d_tab_rk, 0, el * p.tab_elems, s);
-    if (e == hipSuccess && p.d_tab_kr_lo) e = hipMemsetAsync(p.d_tab_kr_lo, 0, el * p.tab_elems, s);
-    if (e == hipSuccess && p.d_tab_rk_lo) e = hipMemsetAsync(p.d_tab_rk_lo, 0, el * p.tab_elems, s);
+    hipError_t e = hipMemsetAsync(p.d_tab_inv, 0, table_entry_bytes(p, true) * p.tab_elems, s);
+    if (e == hipSuccess) e = hipMemsetAsync(p.d_tab_dir, 0, table_entry_bytes(p, false) * p.tab_elems, s);
     if (e == hipSuccess) e = hipMemsetAsync(p.d_mmax, 0, sizeof(unsigned long long) * (N + 1), s);
     if (e != hipSuccess) return e;
     k_sectoral<<<(NL + 127) / 128, 128, 0, s>>>(NL, N, p.d_mu, p.d_diag, p.d_diag_e);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     dim3 grid((NL + 127) / 128, N + 1);
-    if (p.prec == SHTX_FP64) {
-        k_legendre_table<1><<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_kr,
-                                                  p.d_tab_rk, nullptr, nullptr);
-    } else if (p.prec == SHTX_FP32) {
-        k_legendre_table<2><<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_kr,
-                                                  p.d_tab_rk, nullptr, nullptr);
-    } else {
-        k_legendre_table<0><<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, nullptr,
-                                                  nullptr, nullptr, nullptr);
+    auto store = [&](auto kern) {
+        kern<<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_inv, p.d_tab_dir);
+    };
+    if (split_form(p.prec)) {
+        store(k_legendre_table<SHTX_FP64, 0, false, false>);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (p.prec == SHTX_FP16X3)
-            k_legendre_table<4><<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_kr,
-                                                      p.d_tab_rk, p.d_tab_kr_lo, p.d_tab_rk_lo);
-        else
-            k_legendre_table<3><<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_kr,
-                                                      p.d_tab_rk, p.d_tab_kr_lo, p.d_tab_rk_lo);
     }
+    if (p.prec == SHTX_FP64)
+        store(k_legendre_table<SHTX_FP64, 1, false, false>);
+    else if (p.prec == SHTX_BF16X3)
+        store(k_legendre_table<SHTX_BF16X3, 1, true, true>);
+    else if (p.prec == SHTX_FP16X3)
+        store(k_legendre_table<SHTX_FP16X3, 1, true, true>);
+    else if (p.inv_narrow && p.dir_narrow)
+        store(k_legendre_table<SHTX_FP32, 1, false, false>);
+    else if (p.dir_narrow)
+        store(k_legendre_table<SHTX_FP32, 1, true, false>);
+    else
+        store(k_legendre_table<SHTX_FP32, 1, true, true>);
     return hipGetLastError();
 }
 

@@ -198,17 +198,26 @@ hipError_t upload(T **dst, const std::vector<T> &src)
 
 }  // namespace
 
-void gemm_tiles(int prec, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn)
+// Default tiles.  128 x 128 but where rows or columns would mostly be padding;
+// measured on octahedral grids, microseconds at 128 x 128 / 64 x 128 / 128 x 64:
+//   few rows a wavenumber: FP32 inverse T213 37 fields 26 / 21 / 21, T639 40
+//   fields 236 / 230; BF16x3 inverse T213 20 / 18, T639 411 fields 1131 / 1266;
+//   direct FP32 T255 411 fields 184 / 169, T639 1577 / 1640, BF16x3 T399 137
+//   fields 192 / 175, T639 518 / 541;
+//   columns: FP32 inverse T639 137 fields (274 columns in 384 or 320) 575 / 572
+//   / 524, T1279 4094 / 4502 / 3725, but 411 fields (822 in 896 or 832) 9830 /
+//   - / 10160.
+void gemm_tiles(int prec, int trunc, int nfld, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn)
 {
     if (prec == SHTX_FP64) {
         *inv_bm = 64; *inv_bn = 64; *dir_bm = 64; *dir_bn = 64;
-    } else if (split_form(prec)) {
-        // the autotuner's choices at TCo1279: 128 x 128 with eight waves in
-        // both directions (64 x 128, four waves, wins on small workloads)
-        *inv_bm = 128; *inv_bn = 128; *dir_bm = 128; *dir_bn = 128;
-    } else {
-        *inv_bm = 128; *inv_bn = 128; *dir_bm = 128; *dir_bn = 128;
+        return;
     }
+    const int64_t by64 = round_up(2 * nfld, 64), by128 = round_up(2 * nfld, 128);
+    *inv_bm = trunc < 240 ? 64 : 128;
+    *inv_bn = prec == SHTX_FP32 && trunc >= 240 && 9 * by64 < 8 * by128 ? 64 : 128;
+    *dir_bm = trunc < 512 ? 64 : 128;
+    *dir_bn = 128;
 }
 
 // Long-double mixed-radix DFT (forward) over a 2^a 3^b length, used once per
@@ -265,8 +274,7 @@ void bluestein_filter(int h, int L, std::vector<long double> &re, std::vector<lo
 
 void free_plan(Plan &p)
 {
-    void *ptrs[] = {p.d_mu, p.d_w, p.d_diag, p.d_tab_kr, p.d_tab_rk, p.d_tab_kr_lo,
-                    p.d_tab_rk_lo, p.d_mmax, p.d_mb, p.d_inv_items, p.d_dir_items,
+    void *ptrs[] = {p.d_mu, p.d_w, p.d_diag, p.d_tab_inv, p.d_tab_dir, p.d_mmax, p.d_mb, p.d_inv_items, p.d_dir_items,
                     p.d_rings, p.d_ring_four_off, p.d_ring_pair, p.d_ring_q, p.d_fft_items, p.d_passes,
                     p.d_twid, p.d_four, p.d_fmax, p.d_diag_e, p.d_uvspec};
     for (void *q : ptrs)
@@ -344,66 +352,29 @@ int gemm_work_lists(Plan &p)
         return SHTX_EUNSUPPORTED;
     if (kTablePad % p.inv_bm || kTablePad % p.dir_bm) return SHTX_EUNSUPPORTED;
     const int N = p.trunc, ncol = 2 * p.nfld;
-    p.inv_narrow = gemm_narrow(p.prec, p.nfld, true);
-    p.dir_narrow = gemm_narrow(p.prec, p.nfld, false);
     const int inv_bm = p.inv_narrow ? kNarrowRows : p.inv_bm, inv_bn = p.inv_narrow ? 16 * p.inv_narrow : p.inv_bn;
     const int dir_bm = p.dir_narrow ? kNarrowRows : p.dir_bm, dir_bn = p.dir_narrow ? 16 * p.dir_narrow : p.dir_bn;
-    // a 128-column tile shape whose last column tile would hold at most 64
-    // valid columns covers those with one 64-column tile (FP32 has a 128 x 64
-    // kernel) in a second launch
-    auto tail_of = [&](int bm, int bn) {
-        return p.prec == SHTX_FP32 && bm == 128 && bn == 128 && ncol > 128 && ncol % 128 != 0 && ncol % 128 <= 64
-                   ? 64
-                   : 0;
-    };
-    p.inv_tail_bn = tail_of(inv_bm, inv_bn);
-    p.dir_tail_bn = tail_of(dir_bm, dir_bn);
-    std::vector<std::vector<GemmItem>> gi, gd, ti, td;
-    std::vector<double> ci, cd, cti, ctd;
+    std::vector<std::vector<GemmItem>> gi, gd;
+    std::vector<double> ci, cd;
     for (int m = 0; m <= N; ++m) {
         const MBlock &b = p.mb[m];
         double cost = (double)std::max(b.R, 1) * (N - m + 1) * ncol;
-        std::vector<GemmItem> a, c, at, ct;
-        // main column tiles, then the tail tile's index in units of tail_bn
-        int ntc_i = p.inv_tail_bn ? ncol / inv_bn : (ncol + inv_bn - 1) / inv_bn;
-        int ntr_i = (b.R + inv_bm - 1) / inv_bm;
-        for (int tr = 0; tr < ntr_i; ++tr) {
+        std::vector<GemmItem> a, c;
+        const int ntc_i = (ncol + inv_bn - 1) / inv_bn, ntr_i = (b.R + inv_bm - 1) / inv_bm;
+        for (int tr = 0; tr < ntr_i; ++tr)
             for (int tc = 0; tc < ntc_i; ++tc) a.push_back(GemmItem{m, tr, tc, 0});
-            if (p.inv_tail_bn) at.push_back(GemmItem{m, tr, ntc_i * inv_bn / p.inv_tail_bn, 0});
-        }
-        int ntc_d = p.dir_tail_bn ? ncol / dir_bn : (ncol + dir_bn - 1) / dir_bn;
-        int ntk_d = (b.K0 + dir_bm - 1) / dir_bm;
-        for (int tk = 0; tk < ntk_d; ++tk) {
+        const int ntc_d = (ncol + dir_bn - 1) / dir_bn, ntk_d = (b.K0 + dir_bm - 1) / dir_bm;
+        for (int tk = 0; tk < ntk_d; ++tk)
             for (int tc = 0; tc < ntc_d; ++tc) c.push_back(GemmItem{m, tk, tc, 0});
-            if (p.dir_tail_bn) ct.push_back(GemmItem{m, tk, ntc_d * dir_bn / p.dir_tail_bn, 0});
-        }
         if (!a.empty()) {
             gi.push_back(a);
             ci.push_back(cost);
-            if (!at.empty()) {
-                ti.push_back(at);
-                cti.push_back(cost);
-            }
         }
         gd.push_back(c);
         cd.push_back(cost);
-        if (!ct.empty()) {
-            td.push_back(ct);
-            ctd.push_back(cost);
-        }
     }
     p.inv_items = layout_by_xcd(gi, ci, GemmItem{-1, 0, 0, 0});
     p.dir_items = layout_by_xcd(gd, cd, GemmItem{-1, 0, 0, 0});
-    p.inv_nmain = (int)p.inv_items.size();
-    p.dir_nmain = (int)p.dir_items.size();
-    if (!ti.empty()) {
-        std::vector<GemmItem> t = layout_by_xcd(ti, cti, GemmItem{-1, 0, 0, 0});
-        p.inv_items.insert(p.inv_items.end(), t.begin(), t.end());
-    }
-    if (!td.empty()) {
-        std::vector<GemmItem> t = layout_by_xcd(td, ctd, GemmItem{-1, 0, 0, 0});
-        p.dir_items.insert(p.dir_items.end(), t.begin(), t.end());
-    }
     return SHTX_OK;
 }
 
@@ -463,8 +434,7 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         b.K1 = (N - m + 1) / 2;
         b.Rp = (int)round_up(std::max(b.R, 1), kTablePad);
         b.Kp = (int)round_up(b.K0, kTablePad);
-        b.off_kr = off;
-        b.off_rk = off;
+        b.off = off;
         off += 2 * (int64_t)b.Kp * b.Rp;
         p.mb[m] = b;
         flops += 4.0 * F * (double)b.R * (N - m + 1);
@@ -472,8 +442,9 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
     p.tab_elems = off;
     p.legendre_flops = flops;
 
-    size_t tab_el = prec == SHTX_FP64 ? 8 : prec == SHTX_FP32 ? 4 : 2;
-    p.table_bytes = (split_form(prec) ? 4 : 2) * tab_el * p.tab_elems;
+    p.inv_narrow = gemm_narrow(prec, F, true, off);
+    p.dir_narrow = gemm_narrow(prec, F, false, off);
+    p.table_bytes = (table_entry_bytes(p, true) + table_entry_bytes(p, false)) * p.tab_elems;
 
     // ---- ring FFT plans and twiddle pool --------------------------------------
     const bool dbl = prec == SHTX_FP64;
@@ -618,7 +589,7 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
     if (rc != SHTX_OK) return rc;
 
     // ---- GEMM work lists ----------------------------------------------------------
-    gemm_tiles(prec, &p.inv_bm, &p.inv_bn, &p.dir_bm, &p.dir_bn);
+    gemm_tiles(prec, trunc, nfld, &p.inv_bm, &p.inv_bn, &p.dir_bm, &p.dir_bn);
     rc = gemm_work_lists(p);
     if (rc != SHTX_OK) return rc;
 
@@ -643,15 +614,8 @@ int build_plan(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld, 
     PLAN_TRY(hipMalloc(&p.d_w, sizeof(double) * nlat));
     PLAN_TRY(launch_gauss_nodes(nlat, p.d_mu, p.d_w, stream));
 
-    size_t tab_el = prec == SHTX_FP64 ? 8 : prec == SHTX_FP32 ? 4 : 2;
-    PLAN_TRY(hipMalloc(&p.d_tab_kr, tab_el * p.tab_elems));
-    PLAN_TRY(hipMalloc(&p.d_tab_rk, tab_el * p.tab_elems));
-    p.table_bytes = 2 * tab_el * p.tab_elems;
-    if (split_form(prec)) {
-        PLAN_TRY(hipMalloc(&p.d_tab_kr_lo, tab_el * p.tab_elems));
-        PLAN_TRY(hipMalloc(&p.d_tab_rk_lo, tab_el * p.tab_elems));
-        p.table_bytes *= 2;
-    }
+    PLAN_TRY(hipMalloc(&p.d_tab_inv, table_entry_bytes(p, true) * p.tab_elems));
+    PLAN_TRY(hipMalloc(&p.d_tab_dir, table_entry_bytes(p, false) * p.tab_elems));
     PLAN_TRY(hipMalloc(&p.d_diag, sizeof(double) * (size_t)NL * (N + 1)));
     PLAN_TRY(hipMalloc(&p.d_diag_e, sizeof(int) * (size_t)NL * (N + 1)));
     PLAN_TRY(hipMalloc(&p.d_mmax, sizeof(unsigned long long) * (N + 1)));

@@ -79,8 +79,7 @@ struct MBlock {
     int Rp, Kp;     // padded ring and parity-k extents
     int e;          // power-of-two exponent applied to the stored split table
     int pad_;
-    int64_t off_kr; // element offset of the [p][Kp][Rp] block (parity 1 at + Kp*Rp)
-    int64_t off_rk; // element offset of the [p][Rp][Kp] block (parity 1 at + Rp*Kp)
+    int64_t off;    // entries of the m blocks before this one (2 Kp Rp each)
 };
 
 // One GEMM work item: wavenumber m, row tile, column tile (m < 0: no work).
@@ -141,6 +140,9 @@ constexpr int kKinds = 5;
 
 // The split-precision forms: hi + lo halves of bfloat16 or IEEE half.
 inline bool split_form(int prec) { return prec == SHTX_BF16X3 || prec == SHTX_FP16X3; }
+// 16-bit pieces of a table entry in the half-precision matrix-core GEMM (FP32:
+// three bfloat16).
+__host__ __device__ constexpr int split_pieces(int prec) { return prec == SHTX_FP32 ? 3 : 2; }
 
 struct Plan {
     int trunc = 0, grid = 0, nlat = 0, nlon_full = 0, nfld = 0, prec = 0;
@@ -156,11 +158,7 @@ struct Plan {
     int inv_bm = 0, inv_bn = 0, dir_bm = 0, dir_bn = 0;
     // Column fragments of the few-fields GEMM (gemm_narrow), 0: tiles as above.
     int inv_narrow = 0, dir_narrow = 0;
-    // Each work list is its main part (tiles of bm x bn) followed, when the
-    // last column tile would be less than half used, by a tail part whose
-    // tiles are tail_bn columns wide; nmain counts the main part's items.
     std::vector<GemmItem> inv_items, dir_items;
-    int inv_nmain = 0, dir_nmain = 0, inv_tail_bn = 0, dir_tail_bn = 0;
     std::vector<FftItem> fft_items;
     std::vector<PassDesc> passes;
     int fft_lds_bytes = 0;
@@ -179,8 +177,11 @@ struct Plan {
     double *d_mu = nullptr, *d_w = nullptr;  // nlat
     double *d_diag = nullptr;                // [NL][N+1] sectoral seeds q (plan time only) ...
     int *d_diag_e = nullptr;                 // ... and their exponents E: P̄_m^m = q 2^E
-    void *d_tab_kr = nullptr, *d_tab_rk = nullptr;        // FP64/FP32 values or BF16 hi
-    void *d_tab_kr_lo = nullptr, *d_tab_rk_lo = nullptr;  // BF16 lo
+    // Legendre tables of the inverse- and the direct-shaped GEMM, per m block:
+    // plain values [p][k][r] and [p][r][k] where a kernel of the plan's own
+    // precision reads them (FP64, few fields), else 16-bit pieces
+    // [piece][p][k / 8][r][k % 8] and [piece][p][r / 8][k][r % 8].
+    void *d_tab_inv = nullptr, *d_tab_dir = nullptr;
     unsigned long long *d_mmax = nullptr;                  // per-m max |P̄| bits (plan time)
     MBlock *d_mb = nullptr;
     GemmItem *d_inv_items = nullptr, *d_dir_items = nullptr;
@@ -257,11 +258,21 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
 
 // GEMM tile sizes per precision (rows, columns) for each direction: the
 // defaults, and whether a kernel instantiation exists for a shape.
-void gemm_tiles(int prec, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn);
+void gemm_tiles(int prec, int trunc, int nfld, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn);
 bool gemm_tile_supported(int prec, int bm, int bn);
 // Few fields: column fragments of the kernel that serves them, whatever the
 // tile shapes are (0: the tiled kernels do), and its row tile.
-int gemm_narrow(int prec, int nfld, bool inverse);
+int gemm_narrow(int prec, int nfld, bool inverse, int64_t tab_elems);
+// 16-bit pieces of a plan's table entries in one direction, 0: plain values.
+inline int table_pieces(const Plan &p, bool inverse)
+{
+    return p.prec == SHTX_FP64 || (inverse ? p.inv_narrow : p.dir_narrow) ? 0 : split_pieces(p.prec);
+}
+inline size_t table_entry_bytes(const Plan &p, bool inverse)
+{
+    const int np = table_pieces(p, inverse);
+    return np ? 2 * np : p.prec == SHTX_FP64 ? 8 : 4;
+}
 constexpr int kNarrowRows = 64;
 // Candidate shapes the autotuner times (count returned, shapes in bm[], bn[]).
 int gemm_tile_candidates(int prec, int *bm, int *bn, int max);

@@ -229,6 +229,26 @@ def test_gemm_few_fields(prec, F):
         plan.close()
 
 
+# The half-precision matrix-core GEMM around its units: 16-deep stages and
+# 8-deep chunks (T14 to T17, T130), 32-field and 32-row fragments, 64- and
+# 128-wide tiles, an odd field count, a full grid whose rings carry only part
+# of the wavenumbers (none carries the last ones), in every tile shape.
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "fp16x3"])
+@pytest.mark.parametrize("F", [33, 64, 65])
+def test_gemm_split_edges(prec, F):
+    shtx = _shtx()
+    shapes = [(128, 128), (64, 128)] + ([(128, 64)] if prec == "fp32" else [])
+    for i, (N, grid, nlat, nl_full) in enumerate([(14, "octahedral", 30, 0), (15, "octahedral", 32, 0),
+                                                  (16, "full", 26, 24), (17, "octahedral", 36, 0),
+                                                  (130, "octahedral", 262, 0)]):
+        _say(f"split edges T{N} {grid} F={F} {prec}")
+        plan = shtx.Plan(N, grid, nlat, F, prec, nlon_full=nl_full)
+        for t in shapes if N == 130 else [shapes[i % len(shapes)]]:
+            plan.set_shapes(t, t, plan.info.fft_cap)
+            _check_all(plan, N, plan.ring_lengths(), 29, range(F), prec)
+        plan.close()
+
+
 def test_t79_full_fp64_round_trip():
     """T79 on the full 160 x 320 grid, 1 field, FP64: parity and round trip <= 1e-12."""
     shtx, o = _shtx(), _oracle()
