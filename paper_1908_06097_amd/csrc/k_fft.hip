@@ -825,10 +825,15 @@ __device__ __attribute__((noinline)) void pass_to_four(FourSide<T> g, PassDesc p
 //   P_t = sum_{r=1}^{H} Re(w^{rt}) s_r,   Q_t = sum_{r=1}^{H} Im(w^{rt}) d_r,
 // s_r = x_r + x_{p-r}, d_r = x_r - x_{p-r}: two real products of an H x H
 // matrix (cosines, sines) with an H x (2 x butterflies) matrix whose columns
-// are the real and imaginary parts of s or d.  A wave computes 16 x 16 output
-// units (rows t, columns (butterfly, re|im)) with 16x16x4 MFMAs: the matrix
-// operand is read from a table of the p-th roots in LDS at index r t mod p,
-// the data operand forms s and d from the ring's LDS slots as it is read.
+// are the real and imaginary parts of s or d.  A wave computes a tile of NI x NJ
+// output units of 16 x 16 (rows t, columns (butterfly, re|im)) with 16x16x4
+// MFMAs: the matrix operand is read from a table of the p-th roots in LDS at
+// index r t mod p, once for the NJ units of a row; the data operand forms s
+// and d from the ring's LDS slots as it is read, once for the NI units of a
+// column: the root reads' bank conflicts made LDS, not the matrix cores, the
+// bound when each unit read its own.  64 rings of 5136 points (p = 107), 411
+// fields: c2r 3.92 -> 3.54, r2c 4.16 -> 3.72 ps per grid point; 1284 points (p
+// = 107) 3.70 -> 3.23; FP64 5136 points 8.7 -> 7.6.
 // The units' results stay in registers over a barrier (the pass is in place);
 // X_t of butterfly j then goes to j p + t.
 typedef float gp_f32x4 __attribute__((ext_vector_type(4)));
@@ -866,135 +871,152 @@ struct GpGeom {
     int lr, lk;
 };
 
-// K loop of NJ output units of a general prime pass, run together: for unit
-// (row tile i, column tile g) the lane's matrix operand row is t = 16 i + lr
-// with roots w^{r t}, r = 1 + lk + 4 k, addressed by (r t mod p) rstr and
-// stepped by 4 t mod p with an unsigned min(x, x - span) wrap; its data
-// operand column is c = 16 g + lr = 2 b + (re|im), forming s_r and d_r from
-// x_r and x_{p-r}.  Operands of step k + 1 are read before the products of
-// step k.  Rows r past H in the last step contribute 0.
-template <typename T, int NJ, typename V4>
-__device__ __attribute__((always_inline)) inline void gp_run(const GpGeom &g, const int (&unit)[NJ], V4 *P, V4 *Q,
-                                                             T *x0)
+// K loop of a wave's NI x NJ output units: for row tile i the lane's matrix
+// operand row is t = 16 (i0 + i) + lr with roots w^{r t}, r = 1 + lk + 4 k,
+// addressed by (r t mod p) rstr and stepped by 4 t mod p with an unsigned
+// min(x, x - span) wrap; for column tile j its data operand column is
+// c = 16 (g0 + j) + lr = 2 b + (re|im), forming s_r and d_r from x_r and
+// x_{p-r}.  Operands of step k + 1 are read before the products of step k.
+// Rows r past H in the last step contribute 0.
+template <typename T, int NI, int NJ, typename V4>
+__device__ __attribute__((always_inline)) inline void gp_run(const GpGeom &g, int i0, int g0, V4 (&P)[NI][NJ],
+                                                             V4 (&Q)[NI][NJ], T (&x0)[NJ])
 {
     constexpr unsigned CB = sizeof(C2<T>), RB = sizeof(T);
-    unsigned ur[NJ], du[NJ], ar[NJ], am[NJ];
-    C2<T> w[NJ];
+    unsigned ur[NI], du[NI], ar[NJ], am[NJ];
+    C2<T> w[NI];
     T xr[NJ], xm[NJ];
 #pragma unroll
-    for (int q = 0; q < NJ; ++q) {
-        const int i = unit[q] % g.mt, gc = unit[q] / g.mt;
-        const int t = 16 * i + g.lr;
-        ur[q] = (unsigned)((t * (1 + g.lk)) % g.p) * g.rstr;
-        du[q] = (unsigned)((4 * t) % g.p) * g.rstr;
-        const int c = 16 * gc + g.lr;
+    for (int i = 0; i < NI; ++i) {
+        const int t = 16 * (i0 + i) + g.lr;
+        ur[i] = (unsigned)((t * (1 + g.lk)) % g.p) * g.rstr;
+        du[i] = (unsigned)((4 * t) % g.p) * g.rstr;
+        w[i] = ldc<T>((const LdsC2<T> *)(uintptr_t)(g.rb + ur[i]));
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int c = 16 * (g0 + j) + g.lr;
         const int b = min(c >> 1, g.nb - 1);
-        const int f = udiv(b, g.mg_nbf), j = b - f * g.nbf;
-        const unsigned slot = g.lb + (unsigned)(g.buf_off + f * g.lbufp + j) * CB + (unsigned)(c & 1) * RB;
-        ar[q] = slot + (unsigned)(1 + g.lk) * g.nbf * CB;
-        am[q] = slot + (unsigned)(g.p - 1 - g.lk) * g.nbf * CB;
-        x0[q] = lda<T>(slot);
-        P[q] = V4{T(0), T(0), T(0), T(0)};
-        Q[q] = V4{T(0), T(0), T(0), T(0)};
-        w[q] = ldc<T>((const LdsC2<T> *)(uintptr_t)(g.rb + ur[q]));
-        xr[q] = lda<T>(ar[q]);
-        xm[q] = lda<T>(am[q]);
+        const int f = udiv(b, g.mg_nbf), jj = b - f * g.nbf;
+        const unsigned slot = g.lb + (unsigned)(g.buf_off + f * g.lbufp + jj) * CB + (unsigned)(c & 1) * RB;
+        ar[j] = slot + (unsigned)(1 + g.lk) * g.nbf * CB;
+        am[j] = slot + (unsigned)(g.p - 1 - g.lk) * g.nbf * CB;
+        x0[j] = lda<T>(slot);
+        xr[j] = lda<T>(ar[j]);
+        xm[j] = lda<T>(am[j]);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            P[i][j] = V4{T(0), T(0), T(0), T(0)};
+            Q[i][j] = V4{T(0), T(0), T(0), T(0)};
+        }
     }
     for (int k = 0; k < g.ksteps - 1; ++k) {
-        C2<T> w1[NJ];
+        C2<T> w1[NI];
         T xr1[NJ], xm1[NJ];
 #pragma unroll
-        for (int q = 0; q < NJ; ++q) {
-            const unsigned nx = ur[q] + du[q];
-            ur[q] = min(nx, nx - g.rspan);
-            ar[q] += g.rstep;
-            am[q] -= g.rstep;
-            w1[q] = ldc<T>((const LdsC2<T> *)(uintptr_t)(g.rb + ur[q]));
-            xr1[q] = lda<T>(ar[q]);
-            xm1[q] = lda<T>(am[q]);
+        for (int i = 0; i < NI; ++i) {
+            const unsigned nx = ur[i] + du[i];
+            ur[i] = min(nx, nx - g.rspan);
+            w1[i] = ldc<T>((const LdsC2<T> *)(uintptr_t)(g.rb + ur[i]));
         }
 #pragma unroll
-        for (int q = 0; q < NJ; ++q) {
-            P[q] = gp_mfma(w[q].x, xr[q] + xm[q], P[q]);
-            Q[q] = gp_mfma(w[q].y, xr[q] - xm[q], Q[q]);
-            w[q] = w1[q];
-            xr[q] = xr1[q];
-            xm[q] = xm1[q];
+        for (int j = 0; j < NJ; ++j) {
+            ar[j] += g.rstep;
+            am[j] -= g.rstep;
+            xr1[j] = lda<T>(ar[j]);
+            xm1[j] = lda<T>(am[j]);
         }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const T sm = xr[j] + xm[j], df = xr[j] - xm[j];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                P[i][j] = gp_mfma(w[i].x, sm, P[i][j]);
+                Q[i][j] = gp_mfma(w[i].y, df, Q[i][j]);
+            }
+            xr[j] = xr1[j];
+            xm[j] = xm1[j];
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) w[i] = w1[i];
     }
     const bool live = 4 * (g.ksteps - 1) + 1 + g.lk <= g.H;
 #pragma unroll
-    for (int q = 0; q < NJ; ++q) {
-        P[q] = gp_mfma(w[q].x, live ? xr[q] + xm[q] : T(0), P[q]);
-        Q[q] = gp_mfma(w[q].y, live ? xr[q] - xm[q] : T(0), Q[q]);
+    for (int j = 0; j < NJ; ++j) {
+        const T sm = live ? xr[j] + xm[j] : T(0), df = live ? xr[j] - xm[j] : T(0);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            P[i][j] = gp_mfma(w[i].x, sm, P[i][j]);
+            Q[i][j] = gp_mfma(w[i].y, df, Q[i][j]);
+        }
     }
 }
 
-template <typename T>
-__device__ __attribute__((noinline)) void gp_pass(int buf_off, int lbufp, int nf, PassDesc pd, GlobalC2<T> *Wg)
+// The pass in tiles of NI x NJ units, one per wave (GpShape; the plan's field
+// blocking leaves at most one).
+template <typename T, int NI, int NJ>
+__device__ __attribute__((noinline)) void gp_pass(int lbufp, int nf, PassDesc pd, GlobalC2<T> *Wg)
 {
     using V4 = typename std::conditional<sizeof(T) == 4, gp_f32x4, gp_f64x4>::type;
     constexpr unsigned CB = sizeof(C2<T>), RB = sizeof(T);
-    constexpr int NWV = kFftThreads / 64;
     pd = uniform(pd);
-    buf_off = uni(buf_off);
     lbufp = uni(lbufp);
     nf = uni(nf);
     const int p = pd.R, H = (p - 1) / 2, nbf = pd.nbf, nb = nf * nbf;
-    const int mt = gp_row_tiles(p), nunits = mt * gp_col_tiles(nb), ksteps = (H + 3) / 4;
+    const int mt = gp_row_tiles(p), ct = gp_col_tiles(nb), ksteps = (H + 3) / 4;
     // 1. w^u = W_L[u nbf] (u < p) to a table of p roots after the field slots
-    const int roots_off = buf_off + nf * lbufp;
+    const int roots_off = nf * lbufp;
     for (int u = threadIdx.x; u < p; u += kFftThreads)
         stb<T>((unsigned)(roots_off + u) * CB, C2<T>{Wg[u * nbf].x, Wg[u * nbf].y});
     __syncthreads();
-    const unsigned rbase = (unsigned)roots_off * CB, rstr = CB;
-    const unsigned rspan = (unsigned)p * rstr, rstep = 4u * nbf * CB;
-    const unsigned lb = lds_base(), rb = lb + rbase;
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, lr = lane & 15, lk = lane >> 4;
-    constexpr int NU = kGpUnits;
-    static_assert(NU % 2 == 0, "units run in pairs");
-    V4 accp[NU], accq[NU];
-    T x0[NU];
-    // 2. units wave, wave + NWV, ...: rows t = 16 i + (0..15), columns
-    //    c = 16 g + (0..15) = 2 b + (re|im); two units at a time run their
-    //    K loops together (four independent MFMA chains per wave)
-    const GpGeom gm{p, H, mt, nb, nbf, pd.mg_nbf, buf_off, lbufp, ksteps, rb, rstr, rspan, rstep, lb, lr, lk};
-#pragma unroll
-    for (int s = 0; s < NU; s += 2) {
-        const int ua = wave + s * NWV, ub = wave + (s + 1) * NWV;
-        if (ub < nunits) {
-            const int u2[2] = {ua, ub};
-            gp_run<T, 2>(gm, u2, accp + s, accq + s, x0 + s);
-        } else if (ua < nunits) {
-            const int u1[1] = {ua};
-            gp_run<T, 1>(gm, u1, accp + s, accq + s, x0 + s);
-        }
-    }
+    const unsigned rstr = CB, rspan = (unsigned)p * rstr, rstep = 4u * nbf * CB;
+    const unsigned lb = lds_base(), rb = lb + (unsigned)roots_off * CB;
+    const int wave = uni((int)(threadIdx.x / 64)), lane = threadIdx.x % 64, lr = lane & 15, lk = lane >> 4;
+    V4 accp[NI][NJ], accq[NI][NJ];
+    T x0[NJ];
+    // 2. the wave's row tiles i0 .. and column tiles g0 ..
+    const GpGeom gm{p, H, mt, nb, nbf, pd.mg_nbf, 0, lbufp, ksteps, rb, rstr, rspan, rstep, lb, lr, lk};
+    const int mi = (mt + NI - 1) / NI, i0 = wave % mi * NI, g0 = wave / mi * NJ;
+    if (g0 < ct) gp_run<T, NI, NJ>(gm, i0, g0, accp, accq, x0);
     __syncthreads();
     // 3. lane (column c, four rows) holds P and Q of one real component; i Q
     //    takes the other component's Q from the neighbour lane.  Output rows of
     //    the 16x16x4 MFMA: 4 (lane / 16) + v in FP32, lane / 16 + 4 v in FP64.
+    if (g0 < ct) {
 #pragma unroll
-    for (int s = 0; s < NU; ++s) {
-        const int unit = wave + s * NWV;
-        if (unit < nunits) {
-            const int i = unit % mt, g = unit / mt;
-            const int c = 16 * g + lr, b = c >> 1, im = c & 1;
-            const int f = udiv(min(b, nb - 1), pd.mg_nbf), j = min(b, nb - 1) - f * nbf;
-            const unsigned ob = (unsigned)(buf_off + f * lbufp + j * p) * CB + (unsigned)im * RB;
+        for (int j = 0; j < NJ; ++j) {
+            const int c = 16 * (g0 + j) + lr, b = c >> 1, im = c & 1;
+            const int f = udiv(min(b, nb - 1), pd.mg_nbf), jj = min(b, nb - 1) - f * nbf;
+            const unsigned ob = (unsigned)(f * lbufp + jj * p) * CB + (unsigned)im * RB;
             const T sg = im ? T(1) : T(-1);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const T qo = __shfl_xor(accq[s][v], 1);
-                const int t = 16 * i + (sizeof(T) == 8 ? lk + 4 * v : 4 * lk + v);
-                if (b < nb && t <= H) {
-                    str<T>(ob + (unsigned)t * CB, x0[s] + accp[s][v] + sg * qo);
-                    if (t > 0) str<T>(ob + (unsigned)(p - t) * CB, x0[s] + accp[s][v] - sg * qo);
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const T qo = __shfl_xor(accq[i][j][v], 1);
+                    const int t = 16 * (i0 + i) + (sizeof(T) == 8 ? lk + 4 * v : 4 * lk + v);
+                    if (b < nb && t <= H) {
+                        str<T>(ob + (unsigned)t * CB, x0[j] + accp[i][j][v] + sg * qo);
+                        if (t > 0) str<T>(ob + (unsigned)(p - t) * CB, x0[j] + accp[i][j][v] - sg * qo);
+                    }
                 }
-            }
         }
     }
     __syncthreads();
+}
+
+// The prime pass in the tile shape of the work item.
+template <typename T>
+__device__ inline void gp_dispatch(int shape, int lbufp, int nf, const PassDesc &pd, GlobalC2<T> *W)
+{
+#define SHTX_GP(NI, NJ)                                                                 \
+    case gp_shape(NI, NJ):                                                              \
+        gp_pass<T, NI, NJ>(lbufp, nf, pd, W);                                           \
+        break;
+    switch (shape) {
+        SHTX_GP_SHAPES(SHTX_GP)
+    }
+#undef SHTX_GP
 }
 
 // Calls fn(std::integral_constant<int, R>) for the radix R of a pass of one
@@ -1033,9 +1055,10 @@ __device__ inline void radix_dispatch(int R, Fn fn)
 }
 
 template <typename T, int CAP, bool BHAT>
-__device__ inline void pass_dispatch(int buf_off, int lbufp, int nf, const PassDesc &pd, const C2<T> *W,
+__device__ inline void pass_dispatch(int lbufp, int nf, int shape, const PassDesc &pd, const C2<T> *W,
                                      const C2<T> *bhat)
 {
+    constexpr int buf_off = 0;
     if constexpr (BHAT) {
         // Bluestein lengths start with a radix-9 pass (checked on the host), so
         // the filter pass is always radix 9
@@ -1043,7 +1066,7 @@ __device__ inline void pass_dispatch(int buf_off, int lbufp, int nf, const PassD
         return;
     }
     if (gp_radix(pd.R, sizeof(T) == 8)) {
-        gp_pass<T>(buf_off, lbufp, nf, pd, (GlobalC2<T> *)W);
+        gp_dispatch<T>(shape, lbufp, nf, pd, (GlobalC2<T> *)W);
         return;
     }
     radix_dispatch<kPassLds, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
@@ -1059,20 +1082,20 @@ __device__ inline void pass_dispatch(int buf_off, int lbufp, int nf, const PassD
 // and the caller multiplies by the chirp when reading the first h outputs.
 template <typename T, int CAP>
 __device__ inline void dft_passes(const RingDesc &d, const PassDesc *ps, int nrad, int first, int last, int nf,
-                                  const C2<T> *W, const C2<T> *bhat)
+                                  int shape, const C2<T> *W, const C2<T> *bhat)
 {
     const int end1 = d.blue ? nrad : last;
     for (int s = first; s < end1; ++s) {
         const PassDesc pd = ps[s];
-        pass_dispatch<T, CAP, false>(0, d.lbufp, nf, pd, W, bhat);
+        pass_dispatch<T, CAP, false>(d.lbufp, nf, shape, pd, W, bhat);
     }
     if (d.blue)
         for (int s = 0; s < last; ++s) {
             const PassDesc pd = ps[s];
             if (s == 0)
-                pass_dispatch<T, CAP, true>(0, d.lbufp, nf, pd, W, bhat);
+                pass_dispatch<T, CAP, true>(d.lbufp, nf, shape, pd, W, bhat);
             else
-                pass_dispatch<T, CAP, false>(0, d.lbufp, nf, pd, W, bhat);
+                pass_dispatch<T, CAP, false>(d.lbufp, nf, shape, pd, W, bhat);
         }
 }
 
@@ -1177,7 +1200,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r
         merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, y0_fac);
     }
     // forward DFT of length h; z = conj(DFT(u)): even samples Re z, odd samples Im z
-    dft_passes<T, CAP>(d, ps, d.nrad, d.fuse_in, d.nrad - d.fuse_out, nf, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.nrad, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, W, bhat);
     if (d.fuse_out) {
         const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
         const PassDesc pd = ps[d.nrad - 1];
@@ -1316,7 +1339,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c
         }
     }
     if (!d.fuse_in_r) __syncthreads();
-    dft_passes<T, CAP>(d, ps, d.nrad_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.nrad_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, it.shape, W, bhat);
     // 2. split: Y_m = (Z_m + conj Z_{h-m}) / 2 - (i/2) e^{-2 pi i m / n} (Z_m - conj Z_{h-m})
     const T scale = a.adjoint ? T(1) : T(1.0 / d.n);
     C2<T> *fourb = (C2<T> *)a.out + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
@@ -1413,13 +1436,11 @@ bool check_fft(const Plan &p, int cap)
                 if (R < 2 || d.L % R) SHTX_FFT_FAIL;
                 if (gp_radix(R, sizeof(T) == 8)) {
                     // a general prime pass: the first pass only, an odd prime up to
-                    // kGpMaxPrime, at most kGpUnits output units per wave
+                    // kGpMaxPrime, whose output units fit one tile per wave
                     if (s != 0 || first || last || R > kGpMaxPrime || R % 2 == 0 || d.blue) SHTX_FFT_FAIL;
                     for (int q = 3; q * q <= R; q += 2)
                         if (R % q == 0) SHTX_FFT_FAIL;
-                    if ((int64_t)gp_row_tiles(R) * gp_col_tiles(d.fb * pd.nbf) >
-                        (int64_t)kGpUnits * (kFftThreads / 64))
-                        SHTX_FFT_FAIL;
+                    if (!gp_best_shape(R, d.fb * pd.nbf)) SHTX_FFT_FAIL;
                     extra = R;
                 } else {
                     if (!fft_radix_ok(kind, sizeof(T) == 8, R)) SHTX_FFT_FAIL;
@@ -1452,7 +1473,12 @@ bool check_fft(const Plan &p, int cap)
     for (const FftItem &it : p.fft_items) {
         if (it.ring < 0) continue;
         if (it.ring >= p.nlat || it.f0 < 0 || it.nf < 1 || it.f0 + it.nf > p.nfld) SHTX_FFT_FAIL;
-        if (it.nf > p.rings[it.ring].fb) SHTX_FFT_FAIL;
+        const RingDesc &d = p.rings[it.ring];
+        if (it.nf > d.fb) SHTX_FFT_FAIL;
+        // a prime pass's tile shape has to cover the item's units
+        const PassDesc &pd = p.passes[d.pass_off];
+        if (gp_radix(pd.R, sizeof(T) == 8) && !gp_shape_ok(it.shape, pd.R, it.nf * pd.nbf))
+            SHTX_FFT_FAIL;
     }
     return true;
 #undef SHTX_FFT_FAIL

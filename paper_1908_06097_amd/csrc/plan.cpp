@@ -116,7 +116,7 @@ PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
     double best_cost = 1e300;
     std::vector<int> cur;
     auto go = [&](auto &&self, int Ns, double cost, int fuse_in) -> void {
-        if (cost >= best_cost) return;
+        if (cost + 10 >= best_cost) return;  // no pass costs less than 10
         const int left = L / Ns;
         for (int R = 24; R >= 2; --R) {
             if (left % R) continue;
@@ -124,7 +124,10 @@ PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
             const bool last = left == R;
             cur.push_back(R);
             auto step = [&](int kind, bool fin, bool fout) {
-                if (!fft_radix_ok(kind, dbl, R)) return;
+                // one field's butterflies have to fit the pass's rounds
+                if (!fft_radix_ok(kind, dbl, R) ||
+                    nbf > fft_rounds(dbl ? kFftCapF64 : kFftCapF32, R) * kFftThreads)
+                    return;
                 double c = cost + pass_cost(R, Ns, nbf, !fout);
                 if (Ns == 1 && !fin) c += kUnfused;
                 if (last) {
@@ -310,9 +313,9 @@ int fft_blocking(Plan &p, int cap)
         RingDesc &d = p.rings[j];
         if (d.lbuf > maxcap) return SHTX_EUNSUPPORTED;
         d.fb = std::max(1, std::min(F, cap / d.lbuf));
-        // a general prime pass holds at most kGpUnits output units per wave,
-        // a pass in LDS its rounds of kFftThreads butterflies
-        int extra = 0;
+        // a general prime pass takes one tile of output units per wave, a
+        // pass in LDS its rounds of kFftThreads butterflies
+        int extra = 0, gp = 0, gp_nbf = 0;
         for (int dir = 0; dir < 2; ++dir) {
             const int nrad = dir ? d.nrad_r : d.nrad;
             for (int s = 0; s < nrad; ++s) {
@@ -320,9 +323,9 @@ int fft_blocking(Plan &p, int cap)
                 const int R = q.R;
                 int lim;
                 if (gp_radix(R, p.prec == SHTX_FP64)) {
-                    // units = row tiles x ceil(2 fb nbf / 16)
-                    lim = 8 * (kGpUnits * (kFftThreads / 64) / gp_row_tiles(R)) / q.nbf;
-                    extra = R;
+                    lim = gp_fields(R, d.h, d.fb);
+                    extra = gp = R;
+                    gp_nbf = q.nbf;
                 } else {
                     lim = fft_rounds(maxcap, R) * kFftThreads / q.nbf;
                 }
@@ -332,7 +335,10 @@ int fft_blocking(Plan &p, int cap)
         }
         lds_elems = std::max(lds_elems, d.fb * d.lbufp + extra);
         std::vector<FftItem> g;
-        for (int f0 = 0; f0 < F; f0 += d.fb) g.push_back(FftItem{j, f0, std::min(d.fb, F - f0), 0});
+        for (int f0 = 0; f0 < F; f0 += d.fb) {
+            const int nf = std::min(d.fb, F - f0);
+            g.push_back(FftItem{j, f0, nf, gp ? gp_best_shape(gp, nf * gp_nbf) : 0});
+        }
         fgroups.push_back(g);
         fcost.push_back((double)F * d.L * (1 + d.blue) * std::log2((double)d.L + 1));
     }
@@ -491,7 +497,7 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         // choice measured faster in double precision too (C5 c2r 29.2 ->
         // 27.1 ms against the prime pass limited to 191)
         bool gp = rem > 1 && rem <= kGpMaxPrime && is_prime(rem) &&
-                  gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpUnits * (kFftThreads / 64);
+                  gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
         if (gp && rem > 191 && Lb <= cap) gp = 3.2 + 0.0086 * rem < 0.37 * Lb / h * std::log2((double)Lb);
         if (rem == 1 || gp) {
             lp.L = h;
@@ -501,6 +507,10 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
             lp.blue = 1;
         }
         if (std::max(lp.L, h + 1) > cap) return SHTX_EUNSUPPORTED;
+        // not supported: a register prime of 11 or more with more butterflies
+        // than a block has threads
+        for (int q : f)
+            if (!lp.blue && q >= 11 && lp.L / q > kFftThreads) return SHTX_EUNSUPPORTED;
         for (int dir = 0; dir < 2; ++dir) {
             PassPlan &pp = lp.pass[dir];
             pp = lp.blue ? bluestein_passes(lp.L, dir == 1, dbl) : plan_passes(lp.L, gp ? rem : 1, dir == 1, dbl);

@@ -60,13 +60,61 @@ __host__ __device__ constexpr bool blue_last_radix(int R) { return R == 2 || R =
 // the register radices, p <= kGpMaxPrime, runs it as the first pass on the
 // matrix cores, reading the p-th roots of unity from p LDS entries after the
 // field slots.  Its outputs come in units of 16 rows t (t = 0 .. (p-1)/2) by
-// 16 columns (butterfly, real | imaginary part); each wave holds at most
-// kGpUnits units (more would push the single-precision FFT kernels past the
-// 128 VGPRs that keep two blocks per CU).
+// 16 columns (butterfly, real | imaginary part); each wave holds one tile of
+// NI x NJ of them, at most kGpUnits (more would push the FFT kernels past the
+// registers that keep two blocks, FP64 one, per CU).
 constexpr int kGpMaxPrime = 1021;
-constexpr int kGpUnits = 4;
+constexpr int kGpUnits = 6;
+constexpr int kGpFieldUnits = 32;  // and one field at most this many in all
 __host__ __device__ constexpr int gp_row_tiles(int p) { return ((p - 1) / 2 + 16) / 16; }
 __host__ __device__ constexpr int gp_col_tiles(int nbutterflies) { return (2 * nbutterflies + 15) / 16; }
+__host__ __device__ constexpr int gp_shape(int ni, int nj) { return 8 * ni + nj; }
+// Tile shapes with an instantiation (X(NI, NJ)).
+#define SHTX_GP_SHAPES(X) \
+    X(1, 1) X(1, 2) X(2, 1) X(1, 3) X(3, 1) X(2, 2) X(1, 4) X(4, 1) X(1, 5) X(5, 1) X(2, 3) X(3, 2)
+// Whether one tile of a shape per wave covers the units of nb butterflies.
+inline bool gp_shape_ok(int shape, int p, int nb)
+{
+    const int ni = shape / 8, nj = shape % 8;
+    if (ni < 1 || nj < 1 || ni * nj > kGpUnits) return false;
+    return (gp_row_tiles(p) + ni - 1) / ni * ((gp_col_tiles(nb) + nj - 1) / nj) <= kFftThreads / 64;
+}
+// The cheapest shape that does, 0 if none: MFMAs by the units of a wave, LDS
+// reads by its row tiles (root reads, with bank conflicts) and column tiles.
+inline double gp_cost(int shape)
+{
+    const int ni = shape / 8, nj = shape % 8;
+    return ni * nj + 0.25 * ni + 0.125 * nj;
+}
+inline int gp_best_shape(int p, int nb)
+{
+    int best = 0;
+#define SHTX_GP(NI, NJ)                                                                       \
+    if (gp_shape_ok(gp_shape(NI, NJ), p, nb) && (!best || gp_cost(gp_shape(NI, NJ)) < gp_cost(best))) \
+        best = gp_shape(NI, NJ);
+    SHTX_GP_SHAPES(SHTX_GP)
+#undef SHTX_GP
+    return best;
+}
+// Fields per block (at most fb) of a ring of half-length h with a prime pass:
+// the fewest cycles per field of the pass (16 p for each unit of a wave) and
+// of what a block costs whatever its fields (0.7 h: shorter runs in the
+// Fourier rows).  0 if not even one field's units fit.
+inline int gp_fields(int p, int h, int fb)
+{
+    int best = 0;
+    double cost = 0;
+    for (int nf = 1; nf <= fb; ++nf) {
+        const int shape = gp_best_shape(p, nf * (h / p));
+        if (!shape) break;
+        const double c = (16.0 * p * gp_cost(shape) + 0.7 * h) / nf;
+        if (!best || c < cost) {
+            best = nf;
+            cost = c;
+        }
+    }
+    return best;
+}
 constexpr int kMaxRadices = 12;
 // Primes above the register butterflies run as general prime passes.
 __host__ __device__ constexpr bool gp_radix(int R, bool dbl) { return R > 24 || (dbl && (R == 19 || R == 23)); }
@@ -130,9 +178,10 @@ struct __attribute__((aligned(8))) RingPair {
     int n, s;
 };
 
-// One FFT work item: a ring and a run of fields (ring < 0: no work).
+// One FFT work item: a ring, a run of fields (ring < 0: no work) and the tile
+// shape of the ring's prime pass for them, if it has one.
 struct FftItem {
-    int ring, f0, nf, pad_;
+    int ring, f0, nf, shape;
 };
 
 enum TransformKind { kInverse = 0, kDirect = 1, kInverseAdj = 2, kDirectAdj = 3, kWind = 4 };

@@ -202,6 +202,22 @@ def test_ring_pass_kinds_parity(prec):
         plan.close()
 
 
+# General prime passes in every tile shape of output units (row tiles of the
+# prime by column tiles of the block's butterflies): small primes with many
+# butterflies, large ones with two, and field counts that leave a block's last
+# run in a smaller shape than the others.
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("F", [1, 5, 23])
+def test_prime_pass_shapes_parity(prec, F):
+    shtx = _shtx()
+    for nlon in (58, 62, 74, 134, 202, 268, 422, 428, 514, 1142, 1284, 1604, 1608, 3712):
+        N = min(20, (nlon - 1) // 2)
+        _say(f"prime pass nlon={nlon} F={F} {prec}")
+        plan = shtx.Plan(N, "full", 4, F, prec, nlon_full=nlon)
+        _check_all(plan, N, plan.ring_lengths(), 37, range(F), prec)
+        plan.close()
+
+
 # Legendre GEMM column tiling: 128 columns exactly (64 fields), a last tile at
 # most half used (70 fields: covered by the 64-column tail launch) and one
 # more than half used (100 fields: no tail).
