@@ -299,6 +299,22 @@ void free_plan(Plan &p)
         }                                                \
     } while (0)
 
+// Time of one field of a ring in picoseconds, fitted to single-precision
+// timings of 64 equal rings of 320 to 5136 points, 411 fields, on MI355X
+// (double precision takes about twice as long throughout): a ring without
+// large primes 2.05 ps per grid point; a prime pass (p, nf fields per block) on
+// top of 2.4 by its units, 16 p cycles each; Bluestein 0.36 (L / h) log2 L a
+// point.  It deals the rings to the XCDs, whose loads have to match: by L log2 L
+// alone some XCDs held more of the slow rings than others, and O640, 411
+// fields, took 2.66 instead of 2.29 ms, O400, 137 fields, 296 instead of 280 us.
+static double ring_cost(int h, int L, int blue, int p, int nf)
+{
+    const double n = 2.0 * h;
+    if (blue) return n * 0.36 * L / h * std::log2((double)L);
+    if (!p) return n * 2.05;
+    return n * 2.4 + 16.0 * p * gp_cost(gp_best_shape(p, nf * (h / p))) / nf / 0.614;
+}
+
 // FFT blocking: fields per block (at most `cap` complex values of LDS per
 // block), the XCD-segmented work list and the dynamic LDS size.
 int fft_blocking(Plan &p, int cap)
@@ -340,7 +356,7 @@ int fft_blocking(Plan &p, int cap)
             g.push_back(FftItem{j, f0, nf, gp ? gp_best_shape(gp, nf * gp_nbf) : 0});
         }
         fgroups.push_back(g);
-        fcost.push_back((double)F * d.L * (1 + d.blue) * std::log2((double)d.L + 1));
+        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue, gp, d.fb));
     }
     p.fft_lds_bytes = lds_elems * (int)celem;
     p.fft_lds_max = lds_elems;
@@ -364,7 +380,6 @@ int gemm_work_lists(Plan &p)
     std::vector<double> ci, cd;
     for (int m = 0; m <= N; ++m) {
         const MBlock &b = p.mb[m];
-        double cost = (double)std::max(b.R, 1) * (N - m + 1) * ncol;
         std::vector<GemmItem> a, c;
         const int ntc_i = (ncol + inv_bn - 1) / inv_bn, ntr_i = (b.R + inv_bm - 1) / inv_bm;
         for (int tr = 0; tr < ntr_i; ++tr)
@@ -372,12 +387,13 @@ int gemm_work_lists(Plan &p)
         const int ntc_d = (ncol + dir_bn - 1) / dir_bn, ntk_d = (b.K0 + dir_bm - 1) / dir_bm;
         for (int tk = 0; tk < ntk_d; ++tk)
             for (int tc = 0; tc < ntc_d; ++tc) c.push_back(GemmItem{m, tk, tc, 0});
+        // a tile's K stages, and about six more for its start and its output
         if (!a.empty()) {
+            ci.push_back((double)a.size() * (b.K0 / 16.0 + 6));
             gi.push_back(a);
-            ci.push_back(cost);
         }
+        cd.push_back((double)c.size() * (b.R / 16.0 + 6));
         gd.push_back(c);
-        cd.push_back(cost);
     }
     p.inv_items = layout_by_xcd(gi, ci, GemmItem{-1, 0, 0, 0});
     p.dir_items = layout_by_xcd(gd, cd, GemmItem{-1, 0, 0, 0});
@@ -491,14 +507,12 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         // one prime factor above the register radices, up to kGpMaxPrime, is
         // run as a general prime pass (first, at Ns = 1) instead of Bluestein
         // when one field's output units fit the block's waves and, above 191,
-        // when the cost model of the two (fitted to single-precision ring
-        // FFT timings on MI355X, in ps per grid point: prime pass
-        // 3.2 + 0.0086 p, Bluestein 0.37 (L / h) log2 L) favours it; the same
-        // choice measured faster in double precision too (C5 c2r 29.2 ->
-        // 27.1 ms against the prime pass limited to 191)
+        // when ring_cost favours it
         bool gp = rem > 1 && rem <= kGpMaxPrime && is_prime(rem) &&
                   gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
-        if (gp && rem > 191 && Lb <= cap) gp = 3.2 + 0.0086 * rem < 0.37 * Lb / h * std::log2((double)Lb);
+        if (gp && rem > 191 && Lb <= cap)
+            gp = ring_cost(h, h, 0, rem, gp_fields(rem, h, std::max(1, std::min(F, cap / (h + 1))))) <
+                 ring_cost(h, Lb, 1, 0, 1);
         if (rem == 1 || gp) {
             lp.L = h;
             lp.blue = 0;
