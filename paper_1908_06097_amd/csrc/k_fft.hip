@@ -10,9 +10,9 @@
 // its output where the radix allows.  One larger prime factor (up to 1021:
 // always up to 191, above that where the plan's cost model prefers it to
 // Bluestein) runs as a general prime pass on the matrix cores (below); other
-// lengths go through Bluestein's chirp convolution at a length L = 2^a 3^b
-// >= 2h - 1 (2^a 3^b 5^c when that exceeds the LDS cap), with the filter
-// spectrum precomputed per ring length at plan time.  Only the kept
+// lengths go through Bluestein's chirp convolution at a length L = 2^a 3^b 5^c
+// 7^d >= 2h - 1 chosen by the cost of its passes, with the filter spectrum
+// precomputed per ring length at plan time.  Only the kept
 // wavenumbers m <= M_j are read or written; they live in the Fourier
 // workspace laid out [ring][m][field], so a block's loads and stores are runs
 // over fields.  For the split IEEE-half Legendre form the r2c kernel also
@@ -396,21 +396,23 @@ __device__ inline void odd_butterfly_store(C2<T> *v, unsigned a0, unsigned strid
 // One in-place Stockham pass of radix R over nf fields of length L in LDS:
 // every thread reads all of its butterflies into registers, the block
 // synchronises, then each butterfly is twiddled, transformed and written.
-// BHAT (the first pass of Bluestein's second FFT, where Ns = 1): each input
-// X_i is first replaced by conj(X_i bhat_i), the pointwise step of the chirp
-// convolution.
 template <typename T>
 using GlobalC2 = const __attribute__((address_space(1))) C2<T>;
+template <typename T>
+__device__ inline C2<T> ldg(GlobalC2<T> *p)
+{
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    const V2 w = *(const __attribute__((address_space(1))) V2 *)p;
+    return C2<T>{w.x, w.y};
+}
 
-template <typename T, int R, int CAP, bool BHAT, typename WPtr>
-__device__ __attribute__((noinline)) void stockham_pass_impl(int buf_off, int lbufp, int nf, PassDesc pd, WPtr W,
-                                                             GlobalC2<T> *bhat)
+template <typename T, int R, int CAP>
+__device__ __attribute__((noinline)) void stockham_pass(int lbufp, int nf, PassDesc pd, GlobalC2<T> *W)
 {
     constexpr int NB = fft_rounds(CAP, R);
     constexpr int C2ND = twiddle_step2<R>();
     constexpr unsigned CB = sizeof(C2<T>);
     pd = uniform(pd);
-    buf_off = uni(buf_off);
     lbufp = uni(lbufp);
     nf = uni(nf);
     const int nbf = pd.nbf, total = nf * nbf, Ns = pd.Ns;
@@ -429,7 +431,7 @@ __device__ __attribute__((noinline)) void stockham_pass_impl(int buf_off, int lb
         if (e < total) {
             int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
             int q = udiv(j, pd.mg_ns), k = j - q * Ns;
-            fo[b] = buf_off + f * lbufp;
+            fo[b] = f * lbufp;
             qk[b][0] = q;
             qk[b][1] = k;
             if (Ns > 1) {
@@ -444,13 +446,6 @@ __device__ __attribute__((noinline)) void stockham_pass_impl(int buf_off, int lb
             const unsigned a0 = (unsigned)(fo[b] + j) * CB;
 #pragma unroll
             for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
-            if constexpr (BHAT) {
-                // first pass of Bluestein's second FFT (Ns = 1): its inputs
-                // are conj(X_i bhat_i), X the first FFT's output
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    v[b][r] = cconj(cmul(v[b][r], C2<T>{bhat[j + r * nbf].x, bhat[j + r * nbf].y}));
-            }
         }
     }
     __syncthreads();
@@ -487,15 +482,6 @@ __device__ __attribute__((noinline)) void stockham_pass_impl(int buf_off, int lb
     __syncthreads();
 }
 
-// Twiddles and filter from the global tables (L1/L2 resident), through
-// global-address-space pointers so that the pass uses global_* loads.
-template <typename T, int R, int CAP, bool BHAT>
-__device__ inline void stockham_pass(int buf_off, int lbufp, int nf, const PassDesc &pd, const C2<T> *Wg,
-                                     const C2<T> *bhat)
-{
-    stockham_pass_impl<T, R, CAP, BHAT>(buf_off, lbufp, nf, pd, (GlobalC2<T> *)Wg, (GlobalC2<T> *)bhat);
-}
-
 // Twiddles (for Ns > 1) and radix-R butterfly of v, from the twiddle table
 // values w1 and w2 of the butterfly.
 template <typename T, int R>
@@ -508,6 +494,61 @@ __device__ inline void twiddled_dft(C2<T> *v, int Ns, C2<T> w1, C2<T> w2)
         for (int r = 1; r < R; ++r) v[r] = cmul(v[r], tw[r]);
     }
     dft_reg<T, R>(v);
+}
+
+// The seam of Bluestein's two FFTs: the first one's last pass and the second
+// one's first pass have the same radix R, and then a butterfly of the one
+// leaves exactly the inputs of a butterfly of the other (outputs k + t L / R,
+// inputs j + t L / R), so both run in registers around the filter,
+// conj(X_i bhat_i), and the two FFTs need one pass through LDS less.  Bluestein
+// rings are bound by their passes' vector and LDS work (three times a plain
+// ring's, at under 1 TB/s); against two whole FFTs of radix-9, -16 and smaller
+// passes at the next 2^a 3^b length, 411 fields, ps per grid point, c2r / r2c:
+// 5116 points 9.8 / 9.1 -> 8.1 / 7.2, 4076 11.6 / 10.7 -> 8.6 / 8.1, 2572
+// 8.1 / 8.2 -> 6.0 / 5.8, 2348 9.5 / 9.5 -> 5.9 / 5.9; FP64 4996 20.0 / 17.6 ->
+// 16.1 / 14.0.
+template <typename T, int R, int CAP>
+__device__ __attribute__((noinline)) void seam_pass(int lbufp, int nf, PassDesc pd, GlobalC2<T> *W, GlobalC2<T> *bhat)
+{
+    constexpr int NB = fft_rounds(CAP, R), C2ND = twiddle_step2<R>();
+    constexpr unsigned CB = sizeof(C2<T>);
+    pd = uniform(pd);
+    lbufp = uni(lbufp);
+    nf = uni(nf);
+    const int nbf = pd.nbf, total = nf * nbf;
+    const unsigned srd = nbf * CB;
+    C2<T> v[NB][R];
+    int fj[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int e = threadIdx.x + b * kFftThreads;
+        if (e < total) {
+            const int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
+            fj[b] = f * lbufp + j * R;
+            const C2<T> w1 = ldg<T>(W + (unsigned)j);
+            C2<T> w2{};
+            if constexpr (C2ND > 0) w2 = ldg<T>(W + (unsigned)(C2ND * j));
+            const unsigned a0 = (unsigned)(f * lbufp + j) * CB;
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
+            twiddled_dft<T, R>(v[b], nbf, w1, w2);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // four filter values in registers at a time
+                v[b][r] = cconj(cmul(v[b][r], ldg<T>(bhat + (unsigned)(j + r * nbf))));
+            }
+            dft_reg<T, R>(v[b]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if ((int)threadIdx.x + b * kFftThreads >= total) continue;
+        const unsigned a0 = (unsigned)fj[b] * CB;
+#pragma unroll
+        for (int r = 0; r < R; ++r) stb<T>(a0 + r * CB, v[b][r]);
+    }
+    __syncthreads();
 }
 
 // The first and last passes of a ring's FFT join the kernels' global reads and
@@ -526,13 +567,6 @@ template <typename T>
 using GlobalReal = __attribute__((address_space(1))) T;
 template <typename T>
 using GlobalOut = __attribute__((address_space(1))) C2<T>;
-template <typename T>
-__device__ inline C2<T> ldg(GlobalC2<T> *p)
-{
-    typedef T V2 __attribute__((ext_vector_type(2)));
-    const V2 w = *(const __attribute__((address_space(1))) V2 *)p;
-    return C2<T>{w.x, w.y};
-}
 template <typename T>
 __device__ inline void stg(GlobalOut<T> *p, C2<T> v)
 {
@@ -1054,49 +1088,35 @@ __device__ inline void radix_dispatch(int R, Fn fn)
 #undef SHTX_RADIX
 }
 
-template <typename T, int CAP, bool BHAT>
-__device__ inline void pass_dispatch(int lbufp, int nf, int shape, const PassDesc &pd, const C2<T> *W,
-                                     const C2<T> *bhat)
+template <typename T, int CAP>
+__device__ inline void pass_dispatch(int lbufp, int nf, int shape, const PassDesc &pd, const C2<T> *W)
 {
-    constexpr int buf_off = 0;
-    if constexpr (BHAT) {
-        // Bluestein lengths start with a radix-9 pass (checked on the host), so
-        // the filter pass is always radix 9
-        stockham_pass<T, 9, CAP, true>(buf_off, lbufp, nf, pd, W, bhat);
-        return;
-    }
     if (gp_radix(pd.R, sizeof(T) == 8)) {
         gp_dispatch<T>(shape, lbufp, nf, pd, (GlobalC2<T> *)W);
         return;
     }
     radix_dispatch<kPassLds, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
-        stockham_pass<T, decltype(r)::value, CAP, false>(buf_off, lbufp, nf, pd, W, bhat);
+        stockham_pass<T, decltype(r)::value, CAP>(lbufp, nf, pd, (GlobalC2<T> *)W);
     });
 }
 
-// Passes first .. last - 1 of the length-L FFT of each field slot (the plain
-// FFT, or Bluestein's first), then, for Bluestein, the passes of its second
-// FFT up to last - 1: the input must already be multiplied by the chirp and
-// zero-padded to L; the second FFT's first pass applies the filter
-// (conj(X bhat)) to the first FFT's output, the second FFT leaves conj(conv),
-// and the caller multiplies by the chirp when reading the first h outputs.
+// Passes first .. last - 1 of each field slot's FFT; pass `seam` (Bluestein; -1:
+// none) is the seam of its two FFTs: the input must already be multiplied by
+// the chirp and zero-padded to L, the second FFT leaves conj(conv), and the
+// caller multiplies by the chirp when reading the first h outputs.
 template <typename T, int CAP>
-__device__ inline void dft_passes(const RingDesc &d, const PassDesc *ps, int nrad, int first, int last, int nf,
+__device__ inline void dft_passes(const RingDesc &d, const PassDesc *ps, int seam, int first, int last, int nf,
                                   int shape, const C2<T> *W, const C2<T> *bhat)
 {
-    const int end1 = d.blue ? nrad : last;
-    for (int s = first; s < end1; ++s) {
+    for (int s = first; s < last; ++s) {
         const PassDesc pd = ps[s];
-        pass_dispatch<T, CAP, false>(d.lbufp, nf, shape, pd, W, bhat);
+        if (s == seam)
+            radix_dispatch<kPassSeam, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+                seam_pass<T, decltype(r)::value, CAP>(d.lbufp, nf, pd, (GlobalC2<T> *)W, (GlobalC2<T> *)bhat);
+            });
+        else
+            pass_dispatch<T, CAP>(d.lbufp, nf, shape, pd, W);
     }
-    if (d.blue)
-        for (int s = 0; s < last; ++s) {
-            const PassDesc pd = ps[s];
-            if (s == 0)
-                pass_dispatch<T, CAP, true>(d.lbufp, nf, shape, pd, W, bhat);
-            else
-                pass_dispatch<T, CAP, false>(d.lbufp, nf, shape, pd, W, bhat);
-        }
 }
 
 // A ring's grid rows can be moved two complex values (four points) at a time
@@ -1200,13 +1220,13 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r
         merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, y0_fac);
     }
     // forward DFT of length h; z = conj(DFT(u)): even samples Re z, odd samples Im z
-    dft_passes<T, CAP>(d, ps, d.nrad, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.seam, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, W, bhat);
     if (d.fuse_out) {
         const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
         const PassDesc pd = ps[d.nrad - 1];
         radix_dispatch<kPassToGrid, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
             constexpr int R = decltype(r)::value;
-            if constexpr (blue_last_radix(R)) {
+            if constexpr (blue_last_radix(R, sizeof(T) == 8)) {
                 if (d.blue) return pass_to_grid<T, R, true>(gs, pd, (GlobalC2<T> *)W, scale);
             }
             pass_to_grid<T, R, false>(gs, pd, (GlobalC2<T> *)W, scale);
@@ -1279,12 +1299,13 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c
     if (d.fuse_in_r) {
         const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
         const PassDesc pd = ps[0];
-        if (d.blue)
-            pass_from_grid<T, 9, true>(gs, pd);  // Bluestein lengths start with radix 9
-        else
-            radix_dispatch<kPassFromGrid, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
-                pass_from_grid<T, decltype(r)::value, false>(gs, pd);
-            });
+        radix_dispatch<kPassFromGrid, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+            constexpr int R = decltype(r)::value;
+            if constexpr (blue_first_radix(R, sizeof(T) == 8)) {
+                if (d.blue) return pass_from_grid<T, R, true>(gs, pd);
+            }
+            pass_from_grid<T, R, false>(gs, pd);
+        });
     }
     const int span = d.blue ? d.L : h;
     const unsigned mg_span = div_magic(span);
@@ -1339,7 +1360,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c
         }
     }
     if (!d.fuse_in_r) __syncthreads();
-    dft_passes<T, CAP>(d, ps, d.nrad_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, it.shape, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.seam_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, it.shape, W, bhat);
     // 2. split: Y_m = (Z_m + conj Z_{h-m}) / 2 - (i/2) e^{-2 pi i m / n} (Z_m - conj Z_{h-m})
     const T scale = a.adjoint ? T(1) : T(1.0 / d.n);
     C2<T> *fourb = (C2<T> *)a.out + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
@@ -1421,6 +1442,9 @@ bool check_fft(const Plan &p, int cap)
         for (int dir = 0; dir < 2; ++dir) {
             const int off = dir ? d.pass_off_r : d.pass_off, nrad = dir ? d.nrad_r : d.nrad;
             const int fin = dir ? d.fuse_in_r : d.fuse_in, fout = dir ? d.fuse_out_r : d.fuse_out;
+            const int seam = dir ? d.seam_r : d.seam;
+            // Bluestein's seam stands between passes of both its FFTs
+            if (d.blue ? seam < 1 || seam > nrad - 2 : seam != -1) SHTX_FFT_FAIL;
             if (off < 0 || nrad < 1 || off + nrad > (int)p.passes.size()) SHTX_FFT_FAIL;
             // fused passes: one pass cannot be both; Bluestein's Fourier side
             // goes through LDS
@@ -1430,9 +1454,10 @@ bool check_fft(const Plan &p, int cap)
                 const PassDesc &pd = p.passes[off + s];
                 const int R = pd.R;
                 const bool first = s == 0 && fin, last = s == nrad - 1 && fout;
-                const int kind = first ? (dir ? kPassFromGrid : kPassFromFour)
-                                 : last ? (dir ? kPassToFour : kPassToGrid)
-                                        : kPassLds;
+                const int kind = s == seam ? kPassSeam
+                                 : first   ? (dir ? kPassFromGrid : kPassFromFour)
+                                 : last    ? (dir ? kPassToFour : kPassToGrid)
+                                           : kPassLds;
                 if (R < 2 || d.L % R) SHTX_FFT_FAIL;
                 if (gp_radix(R, sizeof(T) == 8)) {
                     // a general prime pass: the first pass only, an odd prime up to
@@ -1444,10 +1469,9 @@ bool check_fft(const Plan &p, int cap)
                     extra = R;
                 } else {
                     if (!fft_radix_ok(kind, sizeof(T) == 8, R)) SHTX_FFT_FAIL;
-                    // Bluestein also runs its first and last passes in LDS (at the
-                    // seam of its two FFTs), its first with the filter at radix 9
-                    if (d.blue && last && !blue_last_radix(R)) SHTX_FFT_FAIL;
-                    if (d.blue && (!fft_radix_ok(kPassLds, sizeof(T) == 8, R) || (s == 0 && R != 9))) SHTX_FFT_FAIL;
+                    if (d.blue && ((last && !blue_last_radix(R, sizeof(T) == 8)) ||
+                                   (first && !blue_first_radix(R, sizeof(T) == 8))))
+                        SHTX_FFT_FAIL;
                     // every butterfly of a block's fields is covered by the pass's rounds
                     if ((int64_t)d.fb * (d.L / R) > (int64_t)fft_rounds(cap, R) * kFftThreads) SHTX_FFT_FAIL;
                 }
@@ -1458,6 +1482,11 @@ bool check_fft(const Plan &p, int cap)
                 const int cmax = R == 23 ? 17 : R == 9 ? 3 : R >= 10 ? 4 : 1;
                 if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= d.L) SHTX_FFT_FAIL;
                 prod *= R;
+                if (s == seam) {
+                    // ends the first FFT and begins the second
+                    if (prod != d.L) SHTX_FFT_FAIL;
+                    prod = R;
+                }
             }
             if (prod != d.L) SHTX_FFT_FAIL;
         }

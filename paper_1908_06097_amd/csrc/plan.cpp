@@ -80,9 +80,13 @@ double butterfly_cost(int R)
 double write_conflicts(int R, int Ns, int nbf)
 {
     int load[32] = {0}, top = 0, n = std::min(64, nbf);
-    for (int j = 0; j < n; ++j) {
-        const int a = (j / Ns) * Ns * R + j % Ns;
+    for (int j = 0, a = 0, r = 0; j < n; ++j) {  // a = (j / Ns) Ns R + j % Ns
         top = std::max(top, ++load[a % 32]);
+        ++a;
+        if (++r == Ns) {
+            r = 0;
+            a += Ns * (R - 1);
+        }
     }
     return std::max(1.0, top / 2.0);
 }
@@ -101,23 +105,35 @@ double pass_cost(int R, int Ns, int nbf, bool to_lds)
 // The passes of a ring FFT of length L in one direction.
 struct PassPlan {
     std::vector<int> rad;
-    int fuse_in = 0, fuse_out = 0;
+    int fuse_in = 0, fuse_out = 0, seam = -1;
+    double cost = 1e300;  // vector instructions per value, idle lanes counted
 };
 
-// The cheapest radices for length L after a first pass of radix `lead` (1:
-// none) that ran already, in LDS: every ordered factorisation with a butterfly
-// for each pass's kind, the first pass fused with the kernel's reads and the
-// last with its writes where that radix has such a butterfly.
-PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
+constexpr double kUnfused = 12;  // a separate loop for the reads or writes
+
+// Lanes without a butterfly in a pass's rounds hide less latency: a quarter of
+// their share counts (half picked more passes of smaller radices, and rings of 4076
+// points, 411 fields, took 9.0 instead of 8.3 ps per point).
+double idle_factor(int butterflies)
 {
-    constexpr double kUnfused = 12;  // a separate loop for the reads or writes
-    const int kin = r2c ? kPassFromGrid : kPassFromFour, kout = r2c ? kPassToFour : kPassToGrid;
+    const int lanes = (butterflies + kFftThreads - 1) / kFftThreads * kFftThreads;
+    return 0.75 + 0.25 * lanes / butterflies;
+}
+
+// The cheapest passes that bring a length-L FFT from stride Ns0 to stride Ns1
+// (the product of the radices so far): every ordered factorisation with a
+// butterfly for each pass's kind.  kin, kout: kinds that the first and the last
+// of them may take instead of LDS (kPassLds: none).  fields: per block.  No
+// passes if none cost less than `limit`.
+PassPlan order_passes(int L, int Ns0, int Ns1, int kin, int kout, int fields, bool dbl, bool blue, double limit = 1e300)
+{
     PassPlan best;
-    double best_cost = 1e300;
+    best.cost = limit;
     std::vector<int> cur;
     auto go = [&](auto &&self, int Ns, double cost, int fuse_in) -> void {
-        if (cost + 10 >= best_cost) return;  // no pass costs less than 10
-        const int left = L / Ns;
+        const int left = Ns1 / Ns;
+        // no pass costs less than 7 log2(R), 8 of them its writes and 8 its twiddles
+        if (cost + std::max(10.0, 7.0 * std::log2(left) - (Ns == 1 ? 16 : 8)) >= best.cost) return;
         for (int R = 24; R >= 2; --R) {
             if (left % R) continue;
             const int nbf = L / R;
@@ -128,12 +144,15 @@ PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
                 if (!fft_radix_ok(kind, dbl, R) ||
                     nbf > fft_rounds(dbl ? kFftCapF64 : kFftCapF32, R) * kFftThreads)
                     return;
-                double c = cost + pass_cost(R, Ns, nbf, !fout);
-                if (Ns == 1 && !fin) c += kUnfused;
+                if (blue && ((fin && !blue_first_radix(R, dbl)) || (fout && !blue_last_radix(R, dbl)))) return;
+                const double idle = blue ? idle_factor(nbf * fields) : 1.0;
+                if (cost + idle * pass_cost(R, Ns, nbf, false) >= best.cost) return;  // before the conflicts
+                double c = cost + idle * pass_cost(R, Ns, nbf, !fout);
+                if (Ns == 1 && kin != kPassLds && !fin) c += kUnfused;
                 if (last) {
-                    if (!fout) c += kUnfused;
-                    if (c < best_cost) {
-                        best_cost = c;
+                    if (kout != kPassLds && !fout) c += kUnfused;
+                    if (c < best.cost) {
+                        best.cost = c;
                         best.rad = cur;
                         best.fuse_in = fin || fuse_in;
                         best.fuse_out = fout;
@@ -142,49 +161,83 @@ PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
                     self(self, Ns * R, c, fin || fuse_in);
                 }
             };
-            if (Ns == 1 && !last) step(kin, true, false);
+            if (Ns == 1 && kin != kPassLds && (!last || blue)) step(kin, true, false);
             step(kPassLds, false, false);
-            if (last) step(kout, false, true);
+            if (last && kout != kPassLds) step(kout, false, true);
             cur.pop_back();
         }
     };
-    if (lead == L) {
-        best.rad = {lead};
-        return best;
-    }
-    go(go, lead, 0.0, 0);
-    if (lead > 1 && !best.rad.empty()) best.rad.insert(best.rad.begin(), lead);
+    if (Ns0 == Ns1)
+        best.cost = 0;
+    else
+        go(go, Ns0, 0.0, 0);
     return best;
 }
 
-// Bluestein's radices (both of its FFTs, either direction): radix-9 passes
-// first (the filter pass is a radix-9 one), then a factor 3, the fives and the
-// power of two.  The first pass joins the r2c kernel's reads, the last the c2r
-// kernel's writes.
+// Passes of a plain FFT of length L, after a first pass of radix `lead` (1:
+// none) that ran already, in LDS.
+PassPlan plan_passes(int L, int lead, bool r2c, bool dbl)
+{
+    PassPlan p = order_passes(L, lead, L, lead > 1 ? kPassLds : r2c ? kPassFromGrid : kPassFromFour,
+                              r2c ? kPassToFour : kPassToGrid, 1, dbl, false);
+    if (lead > 1) p.rad.insert(p.rad.begin(), lead);
+    return p;
+}
+
+// Bluestein's passes of length L in one direction: the first FFT up to its last
+// pass, the seam, and the rest of the second FFT, for the cheapest radix of
+// the seam; the r2c kernel's first pass reads the grid and the c2r kernel's
+// last one writes it.
 PassPlan bluestein_passes(int L, bool r2c, bool dbl)
 {
-    std::vector<int> f;
-    smooth_factor(L, f);
-    int twos = 0, threes = 0;
-    std::vector<int> odd;
-    for (int p : f) {
-        if (p == 2)
-            ++twos;
-        else if (p == 3)
-            ++threes;
-        else
-            odd.push_back(p);
+    PassPlan best;
+    const int cap = dbl ? kFftCapF64 : kFftCapF32, fields = std::max(1, cap / L);
+    for (int J = 24; J >= 2; --J) {
+        if (L % J || L == J || !fft_radix_ok(kPassSeam, dbl, J) || L / J > fft_rounds(cap, J) * kFftThreads) continue;
+        const double seam = idle_factor(L / J * fields) * (pass_cost(J, 2, L / J, true) + butterfly_cost(J) + 8 +
+                                                           3 * (write_conflicts(J, 1, L / J) - 1));
+        const PassPlan a = order_passes(L, 1, L / J, r2c ? kPassFromGrid : kPassLds, kPassLds, fields, dbl, true,
+                                        best.cost - seam - 10);
+        if (a.rad.empty()) continue;
+        const PassPlan b = order_passes(L, J, L, kPassLds, r2c ? kPassLds : kPassToGrid, fields, dbl, true,
+                                        best.cost - seam - a.cost);
+        if (b.rad.empty()) continue;
+        best = a;
+        best.seam = (int)a.rad.size();
+        best.rad.push_back(J);
+        best.rad.insert(best.rad.end(), b.rad.begin(), b.rad.end());
+        best.fuse_out = b.fuse_out;
+        best.cost = a.cost + b.cost + seam;
     }
-    for (; threes >= 2; threes -= 2) odd.push_back(9);
-    if (threes) odd.push_back(3);
-    std::sort(odd.rbegin(), odd.rend());
-    PassPlan p;
-    p.rad.assign(odd.begin(), odd.end());
-    for (; twos >= 4; twos -= 4) p.rad.push_back(16);
-    if (twos) p.rad.push_back(1 << twos);
-    p.fuse_in = r2c && p.rad.size() > 1 && fft_radix_ok(kPassFromGrid, dbl, p.rad.front());
-    p.fuse_out = !r2c && p.rad.size() > 1 && blue_last_radix(p.rad.back());
-    return p;
+    return best;
+}
+
+// Both directions' passes of a Bluestein length, made once per length.
+struct BluePlan {
+    PassPlan pass[2];
+    double cost = 1e300;
+};
+
+// The cheapest Bluestein length from lo to cap (factors up to 7) and its cost
+// per field and value, with its passes in `plans`.
+std::pair<double, int> bluestein_length(int lo, int cap, bool dbl, std::map<int, BluePlan> &plans)
+{
+    std::pair<double, int> best = {1e300, 0};
+    for (int L = lo; L <= cap && L <= lo + lo / 8 + 32; ++L) {
+        int y = L;
+        for (int q : {2, 3, 5, 7})
+            while (y % q == 0) y /= q;
+        if (y != 1) continue;
+        auto it = plans.find(L);
+        if (it == plans.end()) {
+            BluePlan b;
+            for (int dir = 0; dir < 2; ++dir) b.pass[dir] = bluestein_passes(L, dir == 1, dbl);
+            b.cost = 0.5 * (b.pass[0].cost + b.pass[1].cost);
+            it = plans.emplace(L, b).first;
+        }
+        if (it->second.cost * L < best.first * best.second || !best.second) best = {it->second.cost, L};
+    }
+    return best;
 }
 
 template <class T>
@@ -223,11 +276,14 @@ void gemm_tiles(int prec, int trunc, int nfld, int *inv_bm, int *inv_bn, int *di
     *dir_bn = 128;
 }
 
-// Long-double mixed-radix DFT (forward) over a 2^a 3^b length, used once per
-// ring length at plan time for the Bluestein filter spectrum.
-static void dft_ld(std::complex<long double> *x, int n, int stride,
-                   const std::vector<std::complex<long double>> &tw, int N,
-                   std::vector<std::complex<long double>> &tmp)
+// Long-double mixed-radix DFT (forward), used once per ring length at plan time
+// for the Bluestein filter spectrum.  tw: the N-th roots of unity, n | N.
+using cld = std::complex<long double>;
+static cld mul(const cld &a, const cld &b)
+{
+    return {a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real()};
+}
+static void dft_ld(cld *x, int n, const std::vector<cld> &tw, int N)
 {
     if (n == 1) return;
     int p = 2;
@@ -236,37 +292,50 @@ static void dft_ld(std::complex<long double> *x, int n, int stride,
             p = q;
             break;
         }
-    int m = n / p;
+    const int m = n / p, step = N / n;  // tw[t step] = exp(-2 pi i t / n)
     // decimation in time: sub-sequence r holds x[k p + r]
-    std::vector<std::complex<long double>> sub((size_t)n);
+    std::vector<cld> sub((size_t)n);
     for (int r = 0; r < p; ++r)
-        for (int k = 0; k < m; ++k) sub[(size_t)r * m + k] = x[(size_t)(k * p + r) * stride];
-    for (int r = 0; r < p; ++r) dft_ld(sub.data() + (size_t)r * m, m, 1, tw, N, tmp);
-    int step = N / n;  // tw[t * step] = exp(-2 pi i t / n)
-    for (int k = 0; k < m; ++k)
-        for (int q = 0; q < p; ++q) {
-            std::complex<long double> acc = 0;
-            int kk = k + q * m;
-            for (int r = 0; r < p; ++r) {
-                int t = (int)(((int64_t)r * kk) % n);
-                acc += sub[(size_t)r * m + k] * tw[(size_t)t * step];
-            }
-            x[(size_t)kk * stride] = acc;
+        for (int k = 0; k < m; ++k) sub[(size_t)r * m + k] = x[(size_t)k * p + r];
+    for (int r = 0; r < p; ++r) dft_ld(sub.data() + (size_t)r * m, m, tw, N);
+    cld b[23];
+    for (int k = 0; k < m; ++k) {
+        b[0] = sub[k];
+        for (int r = 1; r < p; ++r) b[r] = mul(sub[(size_t)r * m + k], tw[(size_t)r * k * step]);
+        if (p == 2) {
+            x[k] = b[0] + b[1];
+            x[k + m] = b[0] - b[1];
+            continue;
         }
+        cld sum = b[0];  // p odd: outputs q and p - q from the pairs r and p - r
+        for (int r = 1; r < p; ++r) sum += b[r];
+        x[k] = sum;
+        for (int q = 1; q <= p / 2; ++q) {
+            cld u = b[0], v = 0;
+            for (int r = 1; r <= p / 2; ++r) {
+                const cld w = tw[(size_t)(r * q % p) * (N / p)];
+                u += w.real() * (b[r] + b[p - r]);
+                v += w.imag() * (b[r] - b[p - r]);
+            }
+            x[(size_t)q * m + k] = {u.real() - v.imag(), u.imag() + v.real()};
+            x[(size_t)(p - q) * m + k] = {u.real() + v.imag(), u.imag() - v.real()};
+        }
+    }
 }
 
-void bluestein_filter(int h, int L, std::vector<long double> &re, std::vector<long double> &im)
+// Bluestein's filter: DFT_L(b) / L in long double, b the conjugate chirp of
+// half-length h wrapped to length L, from the plan's twiddles of L and chirp
+// (interleaved).
+static void bluestein_filter(int h, int L, const long double *twid, const long double *chirp,
+                             std::vector<long double> &re, std::vector<long double> &im)
 {
-    const long double pi = 3.141592653589793238462643383279502884L;
-    std::vector<std::complex<long double>> b((size_t)L, 0), tw((size_t)L), tmp;
-    for (int k = 0; k < L; ++k) tw[k] = std::polar(1.0L, -2.0L * pi * k / L);
+    std::vector<cld> b((size_t)L, 0), tw((size_t)L);
+    for (int k = 0; k < L; ++k) tw[k] = {twid[2 * k], twid[2 * k + 1]};
     for (int j = 0; j < h; ++j) {
-        int64_t t = ((int64_t)j * j) % (2 * (int64_t)h);
-        std::complex<long double> c = std::polar(1.0L, -pi * (long double)t / h);  // chirp
-        b[j] = std::conj(c);
-        if (j > 0) b[L - j] = std::conj(c);
+        b[j] = {chirp[2 * j], -chirp[2 * j + 1]};
+        if (j > 0) b[L - j] = b[j];
     }
-    dft_ld(b.data(), L, 1, tw, L, tmp);
+    dft_ld(b.data(), L, tw, L);
     re.resize(L);
     im.resize(L);
     for (int k = 0; k < L; ++k) {
@@ -303,14 +372,17 @@ void free_plan(Plan &p)
 // timings of 64 equal rings of 320 to 5136 points, 411 fields, on MI355X
 // (double precision takes about twice as long throughout): a ring without
 // large primes 2.05 ps per grid point; a prime pass (p, nf fields per block) on
-// top of 2.4 by its units, 16 p cycles each; Bluestein 0.36 (L / h) log2 L a
-// point.  It deals the rings to the XCDs, whose loads have to match: by L log2 L
-// alone some XCDs held more of the slow rings than others, and O640, 411
-// fields, took 2.66 instead of 2.29 ms, O400, 137 fields, 296 instead of 280 us.
-static double ring_cost(int h, int L, int blue, int p, int nf)
+// top of 2.4 by its units, 16 p cycles each; Bluestein 0.0160 L / h by its
+// passes' instructions per value (bluestein_passes).  It deals the rings to the
+// XCDs, whose loads have to match: by L log2 L alone some XCDs held more of the
+// slow rings than others, and O640, 411 fields, took 2.66 instead of 2.29 ms,
+// O400, 137 fields, 296 instead of 280 us.  It also chooses between a prime
+// pass and Bluestein: 1604 points (p = 401) take 6.4 and 5.6 ps per point, 1556
+// (p = 389) 6.4 and 5.8.
+static double ring_cost(int h, int L, double blue, int p, int nf)
 {
     const double n = 2.0 * h;
-    if (blue) return n * 0.36 * L / h * std::log2((double)L);
+    if (blue > 0) return n * 0.0160 * blue * L / h;
     if (!p) return n * 2.05;
     return n * 2.4 + 16.0 * p * gp_cost(gp_best_shape(p, nf * (h / p))) / nf / 0.614;
 }
@@ -356,7 +428,7 @@ int fft_blocking(Plan &p, int cap)
             g.push_back(FftItem{j, f0, nf, gp ? gp_best_shape(gp, nf * gp_nbf) : 0});
         }
         fgroups.push_back(g);
-        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue, gp, d.fb));
+        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue ? d.blue_cost : 0.0, gp, d.fb));
     }
     p.fft_lds_bytes = lds_elems * (int)celem;
     p.fft_lds_max = lds_elems;
@@ -477,6 +549,8 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         int64_t tw, post, chirp, bhat;
     };
     std::map<int, LenPlan> lens;
+    std::map<int, BluePlan> blues;
+    std::map<int, int64_t> tws;  // first root of unity by length
     std::vector<long double> pool;  // interleaved re, im
     const long double pi = 3.141592653589793238462643383279502884L;
     for (int j = 0; j < nlat; ++j) {
@@ -487,12 +561,9 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         std::vector<int> f;
         const int maxp = dbl ? 17 : 23;
         const int rem = smooth_factor(h, f, maxp);
-        // Bluestein length: the smallest 2^a 3^b >= 2h - 1 with 9 | L
-        // (radix-16/9 passes; the leading radix-9 passes keep the power-of-two
-        // passes' LDS writes off a single bank); if that exceeds the LDS cap
-        // (rings of more than about 7776 points), the smallest such length
-        // that may also hold factors 5 (radix-5 passes), e.g. 8100 for the
-        // longest TCo1999 rings
+        // A length takes Bluestein if a 2^a 3^b >= 2h - 1 with 9 | L (or 2^a 3^b
+        // 5^c, for the longest TCo1999 rings) fits the LDS cap; the length and
+        // passes used are the cheapest among those of factors up to 7.
         auto smallest = [](int lo, bool fives) {
             for (int x = lo;; ++x) {
                 int y = x, threes = 0;
@@ -504,6 +575,8 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         };
         int Lb = smallest(2 * h - 1, false);
         if (Lb > cap) Lb = smallest(2 * h - 1, true);
+        std::pair<double, int> bl = {1e300, 0};  // cost of a field, length
+        if (rem > 1 && Lb <= cap) bl = bluestein_length(2 * h - 1, cap, dbl, blues);
         // one prime factor above the register radices, up to kGpMaxPrime, is
         // run as a general prime pass (first, at Ns = 1) instead of Bluestein
         // when one field's output units fit the block's waves and, above 191,
@@ -512,12 +585,12 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
                   gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
         if (gp && rem > 191 && Lb <= cap)
             gp = ring_cost(h, h, 0, rem, gp_fields(rem, h, std::max(1, std::min(F, cap / (h + 1))))) <
-                 ring_cost(h, Lb, 1, 0, 1);
+                 ring_cost(h, bl.second, bl.first, 0, 1);
         if (rem == 1 || gp) {
             lp.L = h;
             lp.blue = 0;
         } else {
-            lp.L = Lb;
+            lp.L = Lb <= cap ? bl.second : Lb;
             lp.blue = 1;
         }
         if (std::max(lp.L, h + 1) > cap) return SHTX_EUNSUPPORTED;
@@ -527,10 +600,10 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
             if (!lp.blue && q >= 11 && lp.L / q > kFftThreads) return SHTX_EUNSUPPORTED;
         for (int dir = 0; dir < 2; ++dir) {
             PassPlan &pp = lp.pass[dir];
-            pp = lp.blue ? bluestein_passes(lp.L, dir == 1, dbl) : plan_passes(lp.L, gp ? rem : 1, dir == 1, dbl);
+            pp = lp.blue ? blues[lp.L].pass[dir] : plan_passes(lp.L, gp ? rem : 1, dir == 1, dbl);
             if (pp.rad.empty() || (int)pp.rad.size() > kMaxRadices) return SHTX_EUNSUPPORTED;
             lp.pass_off[dir] = (int)p.passes.size();
-            for (int s = 0, Ns = 1; s < (int)pp.rad.size(); Ns *= pp.rad[s], ++s) {
+            for (int s = 0, Ns = 1; s < (int)pp.rad.size(); ++s) {
                 PassDesc q{};
                 q.R = pp.rad[s];
                 q.Ns = Ns;
@@ -539,32 +612,46 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
                 q.mg_nbf = div_magic(q.nbf);
                 q.mg_ns = div_magic(Ns);
                 p.passes.push_back(q);
+                Ns = s == pp.seam ? q.R : Ns * q.R;  // the seam begins the second FFT
             }
         }
         auto push = [&](long double re, long double im) {
             pool.push_back(re);
             pool.push_back(im);
         };
-        lp.tw = (int64_t)pool.size() / 2;
-        for (int k = 0; k < lp.L; ++k) {
-            long double a = 2.0L * pi * k / lp.L;
-            push(cosl(a), -sinl(a));
-        }
+        auto root = [&](long double a) {  // exp(-i a)
+            long double si, co;
+            sincosl(a, &si, &co);
+            push(co, -si);
+        };
         lp.post = (int64_t)pool.size() / 2;
-        for (int m = 0; m <= h; ++m) {
-            long double a = 2.0L * pi * m / n;
-            push(cosl(a), -sinl(a));
+        for (int m = 0; m <= h; ++m) root(2.0L * pi * m / n);
+        // roots of unity of L: the second half mirrors the first; a plain ring's
+        // first half is every other entry of the n-th roots above, Bluestein
+        // lengths are shared between rings
+        int64_t &tw = tws[lp.L];
+        if (!lp.blue || !tw) {
+            tw = (int64_t)pool.size() / 2;
+            for (int k = 0; k < lp.L; ++k) {
+                const size_t i = 2 * (size_t)(2 * k > lp.L ? tw + lp.L - k : lp.post + 2 * k);
+                if (lp.blue && 2 * k <= lp.L) {
+                    root(2.0L * pi * k / lp.L);
+                } else {
+                    const long double re = pool[i], im = pool[i + 1];
+                    push(re, 2 * k > lp.L ? -im : im);
+                }
+            }
         }
+        lp.tw = tw;
         lp.chirp = lp.bhat = -1;
         if (lp.blue) {
             lp.chirp = (int64_t)pool.size() / 2;
             for (int k = 0; k < h; ++k) {
                 int64_t t = ((int64_t)k * k) % (2 * (int64_t)h);
-                long double a = pi * (long double)t / h;
-                push(cosl(a), -sinl(a));
+                root(pi * (long double)t / h);
             }
             std::vector<long double> bre, bim;
-            bluestein_filter(h, lp.L, bre, bim);
+            bluestein_filter(h, lp.L, &pool[2 * lp.tw], &pool[2 * lp.chirp], bre, bim);
             lp.bhat = (int64_t)pool.size() / 2;
             for (int k = 0; k < lp.L; ++k) push(bre[k], bim[k]);
         }
@@ -593,6 +680,9 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         d.fuse_out = lp.pass[0].fuse_out;
         d.fuse_in_r = lp.pass[1].fuse_in;
         d.fuse_out_r = lp.pass[1].fuse_out;
+        d.seam = lp.pass[0].seam;
+        d.seam_r = lp.pass[1].seam;
+        d.blue_cost = lp.blue ? (float)blues[lp.L].cost : 0.f;
         d.lbuf = std::max(d.L, d.h + 1);
         d.lbufp = d.lbuf;
         d.tw_off = lp.tw;

@@ -34,8 +34,8 @@ __host__ __device__ constexpr int fft_rounds(int cap, int R)
 // place; the r2c kernel's first pass, from the grid row; the c2r kernel's first
 // pass, from the Fourier rows with the merge step; the c2r kernel's last pass,
 // to the grid row; the r2c kernel's last pass, with the split step to the
-// Fourier rows.
-enum FftPassKind { kPassLds = 0, kPassFromGrid = 1, kPassFromFour = 2, kPassToGrid = 3, kPassToFour = 4 };
+// Fourier rows; the seam between Bluestein's two FFTs, in LDS.
+enum FftPassKind { kPassLds = 0, kPassFromGrid = 1, kPassFromFour = 2, kPassToGrid = 3, kPassToFour = 4, kPassSeam = 5 };
 
 // Radices with a butterfly of each kind.  The Fourier-side passes hold a pair of
 // butterflies (j and its mirror) per thread, so their radices stop earlier;
@@ -45,16 +45,25 @@ __host__ __device__ constexpr bool fft_radix_ok(int kind, bool dbl, int R)
 {
     if (R < 2) return false;
     switch (kind) {
-    case kPassLds: return R <= 13 || R == 16 || R == 17 || (!dbl && (R == 19 || R == 23));
-    case kPassFromGrid: return R <= 13 || R == 16 || (!dbl && (R == 15 || R == 17));
+    case kPassLds: return R <= 13 || R == 16 || R == 17 || (!dbl && (R == 18 || R == 19 || R == 23));
+    case kPassFromGrid: return R <= 13 || R == 16 || (!dbl && (R == 15 || R == 17 || R == 18));
     case kPassFromFour: return R <= (dbl ? 9 : 10);
     case kPassToGrid: return R <= 10 || R == 12 || R == 16 || (!dbl && (R == 14 || R == 15 || R == 18 || R == 20));
     case kPassToFour: return R <= 6 || R == 8 || (!dbl && (R == 7 || R == 9));
+    case kPassSeam: return R == 9 || R == 10 || (dbl ? R == 12 : R == 15 || R == 18);
     }
     return false;
 }
-// Last radices of Bluestein's second FFT that write the grid themselves.
-__host__ __device__ constexpr bool blue_last_radix(int R) { return R == 2 || R == 4 || R == 8 || R == 16; }
+// First radices of Bluestein's first FFT that read the grid themselves (with
+// the chirp), and last ones of its second that write it.
+__host__ __device__ constexpr bool blue_first_radix(int R, bool dbl)
+{
+    return R == 9 || R == 10 || R == 12 || (dbl ? R == 8 : R == 15 || R == 18);
+}
+__host__ __device__ constexpr bool blue_last_radix(int R, bool dbl)
+{
+    return R == 8 || R == 9 || R == 10 || (dbl ? R == 4 : R == 12 || R == 16);
+}
 
 // General prime pass: a ring whose half-length has one prime factor p above
 // the register radices, p <= kGpMaxPrime, runs it as the first pass on the
@@ -149,7 +158,8 @@ struct RingDesc {
     int pass_off, pass_off_r;  // first PassDesc of the c2r and the r2c passes
     int fuse_in, fuse_out;      // c2r: first pass merges, last pass writes the grid
     int fuse_in_r, fuse_out_r;  // r2c: first pass reads the grid, last pass splits
-    int pad_;
+    int seam, seam_r;           // index of Bluestein's seam pass, c2r and r2c (-1: none)
+    float blue_cost;            // Bluestein: cost of its passes (host only)
     int64_t tw_off;     // W_L[k] = exp(-2 pi i k / L), k < L
     int64_t post_off;   // exp(-2 pi i m / n), m <= h
     int64_t chirp_off;  // Bluestein chirp exp(-pi i k^2 / h), k < h
@@ -342,10 +352,6 @@ int apply_shapes(Plan &p, int inv_bm, int inv_bn, int dir_bm, int dir_bn, int ff
 // Let the ring-FFT kernels of the plan's precision use the whole LDS of a
 // workgroup as dynamic LDS (set per device at plan creation).
 hipError_t fft_prepare(const Plan &p);
-
-// Host-side Bluestein filter: out[k] = DFT_L(b)[k] / L in long double, b the
-// conjugate chirp wrapped to length L.
-void bluestein_filter(int h, int L, std::vector<long double> &re, std::vector<long double> &im);
 
 // Work lists are laid out as 8 equal segments, one per XCD (the hardware
 // deals workgroups to the 8 XCDs round-robin), padded with no-op items.

@@ -181,7 +181,7 @@ def test_ring_kinds_parity(prec, nlon):
 # Ring lengths whose FFT plans hold, between them, a pass of every kind (in LDS;
 # first, from the grid or from the Fourier rows; last, to either) at every
 # radix that kind has, single-pass rings, prime passes alone and before each
-# last radix, and Bluestein lengths ending in each power of two; five fields
+# last radix, and Bluestein lengths; five fields
 # make more than one round of butterflies at the longer lengths.
 PASS_LENGTHS = {
     "fp64": [4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 30, 32, 34, 36, 38, 44, 46, 58, 64, 260, 512, 520, 612, 874, 972,
@@ -199,6 +199,28 @@ def test_ring_pass_kinds_parity(prec):
         _say(f"ring passes nlon={nlon} {prec}")
         plan = shtx.Plan(N, "full", 4, F, prec, nlon_full=nlon)
         _check_all(plan, N, plan.ring_lengths(), 19, range(F), prec)
+        plan.close()
+
+
+# Bluestein rings: every radix of the pass between its two FFTs (9, 10, 12 in
+# FP64; 9, 10, 15, 18 in FP32), of a first pass from the grid and of a last one
+# to it, lengths where those run through LDS instead, and the longest length
+# that fits; one field, and enough for several a block and a shorter last run.
+BLUE_LENGTHS = {
+    "fp64": [386, 1006, 1082, 1604, 2594, 4502, 8098],
+    "fp32": [542, 614, 1082, 1682, 2894, 3242, 8098],
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("F", [1, 11])
+def test_bluestein_passes_parity(prec, F):
+    shtx = _shtx()
+    for nlon in BLUE_LENGTHS[prec]:
+        N = 20
+        _say(f"bluestein nlon={nlon} F={F} {prec}")
+        plan = shtx.Plan(N, "full", 4, F, prec, nlon_full=nlon)
+        _check_all(plan, N, plan.ring_lengths(), 41, range(F), prec)
         plan.close()
 
 
