@@ -7,10 +7,11 @@
 // mixed-radix FFT (radices up to 20 and 23; 17 in FP64) held in LDS, run in
 // place: each pass reads its butterflies into registers, synchronises, then
 // writes.  The first pass reads the kernel's input itself and the last writes
-// its output where the radix allows.  One larger prime factor (up to 1021:
-// always up to 191, above that where the plan's cost model prefers it to
-// Bluestein) runs as a general prime pass on the matrix cores (below); other
-// lengths go through Bluestein's chirp convolution at a length L = 2^a 3^b 5^c
+// its output where the radix allows.  One larger prime factor p is the first
+// pass: by convolution where p - 1 has small factors and p is not small, else,
+// up to 1021, a general prime pass on the matrix cores (both below); the plan's
+// cost model chooses between them and Bluestein, which takes all other lengths
+// through a chirp convolution at a length L = 2^a 3^b 5^c
 // 7^d >= 2h - 1 chosen by the cost of its passes, with the filter spectrum
 // precomputed per ring length at plan time.  Only the kept
 // wavenumbers m <= M_j are read or written; they live in the Fourier
@@ -28,6 +29,7 @@
 //
 // The paper (Section 3.1.1) keeps fields resident on the device and packs on
 // the device; this kernel's layout and algorithm are this library's own.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -406,16 +408,57 @@ __device__ inline C2<T> ldg(GlobalC2<T> *p)
     return C2<T>{w.x, w.y};
 }
 
-template <typename T, int R, int CAP>
-__device__ __attribute__((noinline)) void stockham_pass(int lbufp, int nf, PassDesc pd, GlobalC2<T> *W)
+// A prime pass by convolution (C. M. Rader, Proc. IEEE 56 (1968) 1107): with g
+// a primitive root of p, a length-p DFT's outputs at g^-q, but for x_0, are the
+// cyclic convolution over q of its inputs at g^k with W_p^(g^-k), which two
+// FFTs of length P = p - 1 make.  The pass at Ns = 1 of a ring of h = p per is
+// per such transforms a field, of inputs i + r per and outputs i p + t.  Its
+// passes stay in LDS: kPassGather, a Stockham pass that reads the inputs in the
+// order g^k and leaves transform i at i p, entry P taking x_0; kPassSub; the
+// seam of the two FFTs; kPassSub; and kPassScatter, which writes the outputs in
+// the order g^-k.  Both permutations are read from memory (one table for all
+// fields, in the L2).  Like Bluestein, bound by vector and LDS work, but over p
+// - 1 values and not twice h: FP32, 411 fields, ps per grid point, c2r / r2c,
+// against the general prime pass or Bluestein before: 2424 points (p = 101)
+// 3.6 / 3.7 -> 3.2 / 3.25, 2416 (151) 4.2 / 4.15 -> 3.1 / 3.1, 1604 (401)
+// 5.8 / 5.7 -> 3.7 / 3.6, 4036 (1009) 9.0 / 8.4 -> 3.6 / 3.4, 5042 (2521)
+// 8.3 / 7.5 -> 4.5 / 4.4; FP64 1604 12.3 / 13.4 -> 7.4 / 8.6, 4034 (2017)
+// 14.1 / 13.2 -> 7.8 / 7.8.
+
+// Where the transforms of a pass lie in LDS: n of them, transform s at
+// a s + b (s / per): the fields' slots (per = 1, b = 0), or the per = h / p
+// length-p transforms of each field that a prime pass by convolution makes
+// (a = p, a per + b entries a field).
+struct Slots {
+    int n, a, b, per;
+    unsigned mg;  // div_magic(per)
+};
+__device__ inline Slots uniform(const Slots &s)
+{
+    return Slots{uni(s.n), uni(s.a), uni(s.b), uni(s.per), (unsigned)uni((int)s.mg)};
+}
+
+// Entry k of a permutation (part 0: g^k, 1: g^-k), stored as 2^23 (FP64: 2^52)
+// plus the number, which is then the low bits of its low word.
+template <typename T>
+__device__ inline int perm_entry(GlobalC2<T> *perm, int k, int part)
+{
+    const unsigned w = ((const __attribute__((address_space(1))) unsigned *)(perm + (unsigned)k))[part * sizeof(T) / 4];
+    return (int)(sizeof(T) == 4 ? w & 0x7fffffu : w);
+}
+
+// One pass in LDS, in place.  KIND: kPassLds over the fields' slots, and for a
+// prime pass by convolution kPassGather, kPassSub and kPassScatter (below).
+template <typename T, int R, int CAP, int KIND>
+__device__ __attribute__((noinline)) void stockham_pass(Slots sl, PassDesc pd, GlobalC2<T> *W, GlobalC2<T> *perm)
 {
     constexpr int NB = fft_rounds(CAP, R);
     constexpr int C2ND = twiddle_step2<R>();
     constexpr unsigned CB = sizeof(C2<T>);
+    constexpr bool SUB = KIND != kPassLds, GATHER = KIND == kPassGather, SCATTER = KIND == kPassScatter;
     pd = uniform(pd);
-    lbufp = uni(lbufp);
-    nf = uni(nf);
-    const int nbf = pd.nbf, total = nf * nbf, Ns = pd.Ns;
+    sl = uniform(sl);
+    const int nbf = pd.nbf, total = sl.n * nbf, Ns = GATHER ? 1 : pd.Ns;
     const unsigned srd = nbf * CB, swr = Ns * CB;  // byte strides of a butterfly's reads and writes
     // radices above 19 run a streamed butterfly: twiddles by stepping from
     // table values read every 8 powers, outputs stored as they are formed
@@ -425,13 +468,26 @@ __device__ __attribute__((noinline)) void stockham_pass(int lbufp, int nf, PassD
     C2<T> w1[NB], w2[NB];  // twiddle table values, fetched before the barrier
     C2<T> wrs[NB][NRS];
     int fo[NB], qk[NB][2];
+    // input 0 of the thread's transform goes to the extra entry after the
+    // others, and output 0 comes from there
+    C2<T> x0{};
+    unsigned x0_to = 0;
+    const int t0 = threadIdx.x;
+    if ((GATHER || SCATTER) && t0 < sl.n) {
+        const int fld = udiv(t0, sl.mg);
+        const unsigned in = (unsigned)(fld * (sl.a * sl.per + sl.b) + t0 - fld * sl.per) * CB;
+        const unsigned base = (unsigned)(t0 * sl.a + fld * sl.b) * CB, extra = base + (unsigned)(nbf * R) * CB;
+        x0 = ldb<T>(GATHER ? in : extra);
+        x0_to = GATHER ? extra : base;
+    }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         int e = threadIdx.x + b * kFftThreads;
         if (e < total) {
             int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
-            int q = udiv(j, pd.mg_ns), k = j - q * Ns;
-            fo[b] = f * lbufp;
+            int q = GATHER ? j : udiv(j, pd.mg_ns), k = j - q * Ns;
+            const int fld = SUB ? udiv(f, sl.mg) : 0;
+            fo[b] = f * sl.a + fld * sl.b;
             qk[b][0] = q;
             qk[b][1] = k;
             if (Ns > 1) {
@@ -443,20 +499,37 @@ __device__ __attribute__((noinline)) void stockham_pass(int lbufp, int nf, PassD
                     for (int c = 0; c < NRS; ++c) wrs[b][c] = C2<T>{W[(8 * c + 1) * t1].x, W[(8 * c + 1) * t1].y};
                 }
             }
-            const unsigned a0 = (unsigned)(fo[b] + j) * CB;
+            if constexpr (GATHER) {
+                // input k of transform i of a field is entry i + g^k h / p
+                const unsigned a0 = (unsigned)(fld * (sl.a * sl.per + sl.b) + f - fld * sl.per) * CB;
+                int gk[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
+                for (int r = 0; r < R; ++r) gk[r] = perm_entry<T>(perm, j + r * nbf, 0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)gk[r], (unsigned)sl.per * CB));
+            } else {
+                const unsigned a0 = (unsigned)(fo[b] + j) * CB;
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
+            }
         }
     }
     __syncthreads();
+    if ((GATHER || SCATTER) && t0 < sl.n) stb<T>(x0_to, x0);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         int e = threadIdx.x + b * kFftThreads;
         if (e < total) {
             const int q = qk[b][0], k = qk[b][1];
+            int to[SCATTER ? R : 1];  // where the outputs go, fetched over the butterfly
+            if constexpr (SCATTER) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) to[r] = perm_entry<T>(perm, k + r * nbf, 1);
+            }
             const int base = q * Ns * R + k;
             const unsigned a0 = (unsigned)(fo[b] + base) * CB;
             if constexpr (STREAM) {
+                static_assert(!SCATTER, "streamed butterflies store at a stride");
                 if (Ns > 1) {
                     C2<T> t = wrs[b][0];
 #pragma unroll
@@ -475,7 +548,12 @@ __device__ __attribute__((noinline)) void stockham_pass(int lbufp, int nf, PassD
                 }
                 dft_reg<T, R>(v[b]);
 #pragma unroll
-                for (int r = 0; r < R; ++r) stb<T>(a0 + __umul24((unsigned)r, swr), v[b][r]);
+                for (int r = 0; r < R; ++r) {
+                    if constexpr (SCATTER)
+                        stb<T>((unsigned)(fo[b] + to[r]) * CB, cconj(v[b][r]));
+                    else
+                        stb<T>(a0 + __umul24((unsigned)r, swr), v[b][r]);
+                }
             }
         }
     }
@@ -507,35 +585,45 @@ __device__ inline void twiddled_dft(C2<T> *v, int Ns, C2<T> w1, C2<T> w2)
 // 5116 points 9.8 / 9.1 -> 8.1 / 7.2, 4076 11.6 / 10.7 -> 8.6 / 8.1, 2572
 // 8.1 / 8.2 -> 6.0 / 5.8, 2348 9.5 / 9.5 -> 5.9 / 5.9; FP64 4996 20.0 / 17.6 ->
 // 16.1 / 14.0.
-template <typename T, int R, int CAP>
-__device__ __attribute__((noinline)) void seam_pass(int lbufp, int nf, PassDesc pd, GlobalC2<T> *W, GlobalC2<T> *bhat)
+//
+// SUB: the seam of a prime pass by convolution, whose bin 0 is the sum of all
+// inputs but x_0: with x_0 (the extra entry) it is the transform's output 0,
+// kept in the extra entry, and x_0 joins every other output by bin 0.
+template <typename T, int R, int CAP, bool SUB>
+__device__ __attribute__((noinline)) void seam_pass(Slots sl, PassDesc pd, GlobalC2<T> *W, GlobalC2<T> *bhat)
 {
     constexpr int NB = fft_rounds(CAP, R), C2ND = twiddle_step2<R>();
     constexpr unsigned CB = sizeof(C2<T>);
     pd = uniform(pd);
-    lbufp = uni(lbufp);
-    nf = uni(nf);
-    const int nbf = pd.nbf, total = nf * nbf;
+    sl = uniform(sl);
+    const int nbf = pd.nbf, total = sl.n * nbf;
     const unsigned srd = nbf * CB;
-    C2<T> v[NB][R];
-    int fj[NB];
+    C2<T> v[NB][R], x0[NB];
+    int fo[NB], fj[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int e = threadIdx.x + b * kFftThreads;
         if (e < total) {
             const int f = udiv(e, pd.mg_nbf), j = e - f * nbf;
-            fj[b] = f * lbufp + j * R;
+            fo[b] = f * sl.a + (SUB ? udiv(f, sl.mg) * sl.b : 0);
+            fj[b] = j;
             const C2<T> w1 = ldg<T>(W + (unsigned)j);
             C2<T> w2{};
             if constexpr (C2ND > 0) w2 = ldg<T>(W + (unsigned)(C2ND * j));
-            const unsigned a0 = (unsigned)(f * lbufp + j) * CB;
+            const unsigned a0 = (unsigned)(fo[b] + j) * CB;
+            if (SUB && j == 0) x0[b] = ldb<T>(a0 + (unsigned)(R * nbf) * CB);
 #pragma unroll
             for (int r = 0; r < R; ++r) v[b][r] = ldb<T>(a0 + __umul24((unsigned)r, srd));
             twiddled_dft<T, R>(v[b], nbf, w1, w2);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // four filter values in registers at a time
-                v[b][r] = cconj(cmul(v[b][r], ldg<T>(bhat + (unsigned)(j + r * nbf))));
+                const C2<T> x = v[b][r];
+                v[b][r] = cconj(cmul(x, ldg<T>(bhat + (unsigned)(j + r * nbf))));
+                if (SUB && r == 0 && j == 0) {
+                    v[b][0] = cadd(v[b][0], cconj(x0[b]));
+                    x0[b] = cadd(x0[b], x);
+                }
             }
             dft_reg<T, R>(v[b]);
         }
@@ -544,9 +632,10 @@ __device__ __attribute__((noinline)) void seam_pass(int lbufp, int nf, PassDesc 
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if ((int)threadIdx.x + b * kFftThreads >= total) continue;
-        const unsigned a0 = (unsigned)fj[b] * CB;
+        const unsigned a0 = (unsigned)(fo[b] + fj[b] * R) * CB;
 #pragma unroll
         for (int r = 0; r < R; ++r) stb<T>(a0 + r * CB, v[b][r]);
+        if (SUB && fj[b] == 0) stb<T>((unsigned)(fo[b] + R * nbf) * CB, x0[b]);
     }
     __syncthreads();
 }
@@ -1096,7 +1185,16 @@ __device__ inline void pass_dispatch(int lbufp, int nf, int shape, const PassDes
         return;
     }
     radix_dispatch<kPassLds, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
-        stockham_pass<T, decltype(r)::value, CAP>(lbufp, nf, pd, (GlobalC2<T> *)W);
+        stockham_pass<T, decltype(r)::value, CAP, kPassLds>(Slots{nf, lbufp, 0, 1, 0u}, pd, (GlobalC2<T> *)W, nullptr);
+    });
+}
+
+// One pass of a prime pass by convolution.
+template <typename T, int CAP, int KIND>
+__device__ inline void sub_dispatch(const Slots &sl, const PassDesc &pd, const C2<T> *W, const C2<T> *perm)
+{
+    radix_dispatch<KIND, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+        stockham_pass<T, decltype(r)::value, CAP, KIND>(sl, pd, (GlobalC2<T> *)W, (GlobalC2<T> *)perm);
     });
 }
 
@@ -1106,13 +1204,35 @@ __device__ inline void pass_dispatch(int lbufp, int nf, int shape, const PassDes
 // caller multiplies by the chirp when reading the first h outputs.
 template <typename T, int CAP>
 __device__ inline void dft_passes(const RingDesc &d, const PassDesc *ps, int seam, int first, int last, int nf,
-                                  int shape, const C2<T> *W, const C2<T> *bhat)
+                                  int shape, const C2<T> *tw)
 {
+    const C2<T> *W = tw + d.tw_off, *bhat = tw + d.bhat_off;
+    if (d.conv) {
+        const C2<T> *Wp = tw + d.conv_tw_off, *perm = tw + d.conv_perm_off;
+        const int per = uni(d.h) / uni(d.conv_p);
+        const Slots sl{nf * per, d.conv_p, d.lbufp - d.h, per, div_magic(per)};
+        for (int s = 0; s < d.conv; ++s) {
+            const PassDesc pd = ps[s];
+            if (s == 0)
+                sub_dispatch<T, CAP, kPassGather>(sl, pd, Wp, perm);
+            else if (s == seam)
+                radix_dispatch<kPassSubSeam, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
+                    seam_pass<T, decltype(r)::value, CAP, true>(sl, pd, (GlobalC2<T> *)Wp, (GlobalC2<T> *)bhat);
+                });
+            else if (s == d.conv - 1)
+                sub_dispatch<T, CAP, kPassScatter>(sl, pd, Wp, perm);
+            else
+                sub_dispatch<T, CAP, kPassSub>(sl, pd, Wp, nullptr);
+        }
+        first = d.conv;
+        seam = -1;
+    }
     for (int s = first; s < last; ++s) {
         const PassDesc pd = ps[s];
         if (s == seam)
             radix_dispatch<kPassSeam, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
-                seam_pass<T, decltype(r)::value, CAP>(d.lbufp, nf, pd, (GlobalC2<T> *)W, (GlobalC2<T> *)bhat);
+                seam_pass<T, decltype(r)::value, CAP, false>(Slots{nf, d.lbufp, 0, 1, 0u}, pd, (GlobalC2<T> *)W,
+                                                             (GlobalC2<T> *)bhat);
             });
         else
             pass_dispatch<T, CAP>(d.lbufp, nf, shape, pd, W);
@@ -1200,7 +1320,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r
     const C2<T> *tw = (const C2<T> *)a.twid;
     const C2<T> *W = tw + d.tw_off;
     const C2<T> *post = tw + d.post_off;
-    const C2<T> *chirp = tw + d.chirp_off, *bhat = tw + d.bhat_off;
+    const C2<T> *chirp = tw + d.chirp_off;
     const int nf = it.nf, f0 = it.f0, h = d.h, M = d.M, lbufp = d.lbufp;
     const unsigned nfld = (unsigned)a.nfld, npts = (unsigned)a.npts;
     const C2<T> *fourb = (const C2<T> *)a.in + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
@@ -1220,7 +1340,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r
         merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, y0_fac);
     }
     // forward DFT of length h; z = conj(DFT(u)): even samples Re z, odd samples Im z
-    dft_passes<T, CAP>(d, ps, d.seam, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.seam, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, tw);
     if (d.fuse_out) {
         const GridSide<T> gs{lbufp, nf, h, npts, (GlobalReal<T> *)gridb, (GlobalC2<T> *)chirp};
         const PassDesc pd = ps[d.nrad - 1];
@@ -1286,7 +1406,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c
     const C2<T> *tw = (const C2<T> *)a.twid;
     const C2<T> *W = tw + d.tw_off;
     const C2<T> *post = tw + d.post_off;
-    const C2<T> *chirp = tw + d.chirp_off, *bhat = tw + d.bhat_off;
+    const C2<T> *chirp = tw + d.chirp_off;
     const int nf = it.nf, f0 = it.f0, h = d.h, M = d.M, lbufp = d.lbufp;
     const unsigned npts = (unsigned)a.npts;
     const T *gridb = (const T *)a.in + (uint64_t)f0 * npts + d.grid_off;  // field f at gridb + f npts
@@ -1360,7 +1480,7 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_r2c
         }
     }
     if (!d.fuse_in_r) __syncthreads();
-    dft_passes<T, CAP>(d, ps, d.seam_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, it.shape, W, bhat);
+    dft_passes<T, CAP>(d, ps, d.seam_r, d.fuse_in_r, d.nrad_r - d.fuse_out_r, nf, it.shape, tw);
     // 2. split: Y_m = (Z_m + conj Z_{h-m}) / 2 - (i/2) e^{-2 pi i m / n} (Z_m - conj Z_{h-m})
     const T scale = a.adjoint ? T(1) : T(1.0 / d.n);
     C2<T> *fourb = (C2<T> *)a.out + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
@@ -1436,6 +1556,9 @@ bool check_fft(const Plan &p, int cap)
         // the kernels index a field's grid row and a ring's Fourier rows with
         // 32-bit unsigned element offsets
         if (p.npts >= (int64_t(1) << 32) || (int64_t)(d.M + 1) * p.nfld >= (int64_t(1) << 32)) SHTX_FFT_FAIL;
+        if (d.conv && (d.conv_p < 3 || d.h % d.conv_p || d.conv_tw_off < 0 || d.conv_perm_off < 0 || d.bhat_off < 0 ||
+                       std::max({d.conv_tw_off, d.conv_perm_off, d.bhat_off}) + d.conv_p - 1 > p.twid_elems))
+            SHTX_FFT_FAIL;
         // both directions' pass lists: every pass of a kind with a butterfly for
         // its radix, and its descriptor exactly that pass
         int extra = 0;
@@ -1444,7 +1567,9 @@ bool check_fft(const Plan &p, int cap)
             const int fin = dir ? d.fuse_in_r : d.fuse_in, fout = dir ? d.fuse_out_r : d.fuse_out;
             const int seam = dir ? d.seam_r : d.seam;
             // Bluestein's seam stands between passes of both its FFTs
-            if (d.blue ? seam < 1 || seam > nrad - 2 : seam != -1) SHTX_FFT_FAIL;
+            if (d.blue ? seam < 1 || seam > nrad - 2 : !d.conv && seam != -1) SHTX_FFT_FAIL;
+            // so does a prime pass's by convolution, whose passes come first
+            if (d.conv && (d.blue || fin || d.conv > nrad || seam < 1 || seam > d.conv - 2)) SHTX_FFT_FAIL;
             if (off < 0 || nrad < 1 || off + nrad > (int)p.passes.size()) SHTX_FFT_FAIL;
             // fused passes: one pass cannot be both; Bluestein's Fourier side
             // goes through LDS
@@ -1454,7 +1579,28 @@ bool check_fft(const Plan &p, int cap)
                 const PassDesc &pd = p.passes[off + s];
                 const int R = pd.R;
                 const bool first = s == 0 && fin, last = s == nrad - 1 && fout;
-                const int kind = s == seam ? kPassSeam
+                if (s < d.conv) {
+                    // transforms of length p - 1, h / p of them a field
+                    const int P = d.conv_p - 1;
+                    const int kind = s == 0            ? kPassGather
+                                     : s == seam       ? kPassSubSeam
+                                     : s == d.conv - 1 ? kPassScatter
+                                                       : kPassSub;
+                    if (!fft_radix_ok(kind, sizeof(T) == 8, R) || P % R || last) SHTX_FFT_FAIL;
+                    if (d.fb * (d.h / d.conv_p) > kFftThreads) SHTX_FFT_FAIL;  // one extra entry a thread
+                    if ((int64_t)d.fb * (d.h / d.conv_p) * (P / R) > (int64_t)fft_rounds(cap, R) * kFftThreads)
+                        SHTX_FFT_FAIL;
+                    if (pd.Ns != prod || pd.nbf * R != P || pd.tstep * prod * R != P) SHTX_FFT_FAIL;
+                    if (pd.mg_nbf != div_magic(pd.nbf) || pd.mg_ns != div_magic(pd.Ns)) SHTX_FFT_FAIL;
+                    const int cmax = R == 23 ? 17 : R == 9 ? 3 : R >= 10 ? 4 : 1;
+                    if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= P) SHTX_FFT_FAIL;
+                    prod *= R;
+                    if ((s == seam || s == d.conv - 1) && prod != P) SHTX_FFT_FAIL;
+                    if (s == seam) prod = R;
+                    if (s == d.conv - 1) prod = d.conv_p;
+                    continue;
+                }
+                const int kind = d.blue && s == seam ? kPassSeam
                                  : first   ? (dir ? kPassFromGrid : kPassFromFour)
                                  : last    ? (dir ? kPassToFour : kPassToGrid)
                                            : kPassLds;
@@ -1482,7 +1628,7 @@ bool check_fft(const Plan &p, int cap)
                 const int cmax = R == 23 ? 17 : R == 9 ? 3 : R >= 10 ? 4 : 1;
                 if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= d.L) SHTX_FFT_FAIL;
                 prod *= R;
-                if (s == seam) {
+                if (d.blue && s == seam) {
                     // ends the first FFT and begins the second
                     if (prod != d.L) SHTX_FFT_FAIL;
                     prod = R;
@@ -1506,7 +1652,7 @@ bool check_fft(const Plan &p, int cap)
         if (it.nf > d.fb) SHTX_FFT_FAIL;
         // a prime pass's tile shape has to cover the item's units
         const PassDesc &pd = p.passes[d.pass_off];
-        if (gp_radix(pd.R, sizeof(T) == 8) && !gp_shape_ok(it.shape, pd.R, it.nf * pd.nbf))
+        if (!d.conv && gp_radix(pd.R, sizeof(T) == 8) && !gp_shape_ok(it.shape, pd.R, it.nf * pd.nbf))
             SHTX_FFT_FAIL;
     }
     return true;

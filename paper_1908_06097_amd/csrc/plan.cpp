@@ -6,6 +6,7 @@
 // across time steps; here everything a transform needs (tables, twiddles,
 // work lists, the Fourier workspace) is allocated once per plan so that the
 // transform calls themselves never allocate.
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <complex>
@@ -212,6 +213,64 @@ PassPlan bluestein_passes(int L, bool r2c, bool dbl)
     return best;
 }
 
+// Passes of a prime pass by convolution: two FFTs of length P = p - 1 around a
+// seam, their first pass a gather and their last a scatter; no passes if P has
+// no such factors.  per: transforms a field, fields: a block.
+PassPlan conv_passes(int p, int per, int fields, bool dbl)
+{
+    constexpr double kPermute = 6;  // table reads and LDS conflicts of a permuted side
+    const int P = p - 1, cap = dbl ? kFftCapF64 : kFftCapF32;
+    PassPlan best;
+    auto fits = [&](int kind, int R) {
+        return fft_radix_ok(kind, dbl, R) && fields * per * (P / R) <= fft_rounds(cap, R) * kFftThreads;
+    };
+    auto cost = [&](int R, int Ns) { return idle_factor(fields * per * (P / R)) * pass_cost(R, Ns, P / R, true); };
+    for (int J = 24; J >= 2; --J) {
+        if (P % J || !fits(kPassSubSeam, J)) continue;
+        const double seam = cost(J, 2) + idle_factor(fields * per * (P / J)) * (butterfly_cost(J) + 8);
+        // the other factor in one to three passes, those of the second FFT
+        // after a product of J
+        PassPlan half[2];
+        for (int out = 0; out < 2; ++out) {
+            std::vector<int> cur;
+            auto go = [&](auto &&self, int left, int Ns, double c) -> void {
+                for (int R = 24; R >= 2; --R) {
+                    if (left % R) continue;
+                    const int kind = out ? (left == R ? kPassScatter : kPassSub) : (cur.empty() ? kPassGather : kPassSub);
+                    if (!fits(kind, R)) continue;
+                    const double cr = c + cost(R, Ns);
+                    if (cr >= half[out].cost) continue;
+                    cur.push_back(R);
+                    if (left == R) {
+                        half[out].cost = cr;
+                        half[out].rad = cur;
+                    } else if (cur.size() < 3) {
+                        self(self, left / R, Ns * R, cr);
+                    }
+                    cur.pop_back();
+                }
+            };
+            go(go, P / J, out ? J : 1, kPermute);
+        }
+        if (half[0].rad.empty() || half[1].rad.empty() || half[0].cost + half[1].cost + seam >= best.cost) continue;
+        best.cost = half[0].cost + half[1].cost + seam;
+        best.rad = half[0].rad;
+        best.seam = (int)best.rad.size();
+        best.rad.push_back(J);
+        best.rad.insert(best.rad.end(), half[1].rad.begin(), half[1].rad.end());
+    }
+    return best;
+}
+
+int primitive_root(int p)
+{
+    for (int g = 2;; ++g) {
+        int k = 1;
+        for (int64_t x = g; x != 1; x = x * g % p) ++k;
+        if (k == p - 1) return g;
+    }
+}
+
 // Both directions' passes of a Bluestein length, made once per length.
 struct BluePlan {
     PassPlan pass[2];
@@ -372,16 +431,21 @@ void free_plan(Plan &p)
 // timings of 64 equal rings of 320 to 5136 points, 411 fields, on MI355X
 // (double precision takes about twice as long throughout): a ring without
 // large primes 2.05 ps per grid point; a prime pass (p, nf fields per block) on
-// top of 2.4 by its units, 16 p cycles each; Bluestein 0.0160 L / h by its
-// passes' instructions per value (bluestein_passes).  It deals the rings to the
+// top of 2.4 by its units, 16 p cycles each; a prime pass by convolution 1.9
+// and 0.0098 by its passes' instructions per value (conv_passes); Bluestein
+// 0.0160 L / h by its passes' (bluestein_passes).  It deals the rings to the
 // XCDs, whose loads have to match: by L log2 L alone some XCDs held more of the
 // slow rings than others, and O640, 411 fields, took 2.66 instead of 2.29 ms,
-// O400, 137 fields, 296 instead of 280 us.  It also chooses between a prime
-// pass and Bluestein: 1604 points (p = 401) take 6.4 and 5.6 ps per point, 1556
-// (p = 389) 6.4 and 5.8.
-static double ring_cost(int h, int L, double blue, int p, int nf)
+// O400, 137 fields, 296 instead of 280 us.  It also chooses between the three,
+// ps per point as a general prime pass | by convolution | Bluestein: p = 61,
+// 2440 points, 2.8 | 3.3 | -; p = 89, 2136 points, 3.3 | 3.4 | -; p = 101, 2424
+// points, 3.6 | 3.2 | -; p = 151, 2416 points, 4.2 | 3.1 | -; p = 389, 1556
+// points, 6.4 | - | 5.8; p = 401, 1604 points, 6.4 | 3.65 | 5.7; p = 1009, 4036
+// points, - | 3.5 | 8.7; p = 2521, 5042 points, - | 4.4 | 7.9.
+static double ring_cost(int h, int L, double blue, int p, int nf, double conv = 0)
 {
     const double n = 2.0 * h;
+    if (conv > 0) return n * (1.9 + 0.0098 * conv);
     if (blue > 0) return n * 0.0160 * blue * L / h;
     if (!p) return n * 2.05;
     return n * 2.4 + 16.0 * p * gp_cost(gp_best_shape(p, nf * (h / p))) / nf / 0.614;
@@ -410,7 +474,9 @@ int fft_blocking(Plan &p, int cap)
                 const PassDesc &q = p.passes[(dir ? d.pass_off_r : d.pass_off) + s];
                 const int R = q.R;
                 int lim;
-                if (gp_radix(R, p.prec == SHTX_FP64)) {
+                if (s < d.conv) {
+                    lim = std::min(fft_rounds(maxcap, R) * kFftThreads / q.nbf, kFftThreads) / (d.h / d.conv_p);
+                } else if (gp_radix(R, p.prec == SHTX_FP64)) {
                     lim = gp_fields(R, d.h, d.fb);
                     extra = gp = R;
                     gp_nbf = q.nbf;
@@ -428,7 +494,7 @@ int fft_blocking(Plan &p, int cap)
             g.push_back(FftItem{j, f0, nf, gp ? gp_best_shape(gp, nf * gp_nbf) : 0});
         }
         fgroups.push_back(g);
-        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue ? d.blue_cost : 0.0, gp, d.fb));
+        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue ? d.blue_cost : 0.0, gp, d.fb, d.conv ? d.blue_cost : 0.0));
     }
     p.fft_lds_bytes = lds_elems * (int)celem;
     p.fft_lds_max = lds_elems;
@@ -547,9 +613,13 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         int L, blue, pass_off[2];  // c2r, r2c
         PassPlan pass[2];
         int64_t tw, post, chirp, bhat;
+        PassPlan conv;
+        int conv_p = 0;
+        int64_t conv_tw = 0, conv_perm = 0;
     };
     std::map<int, LenPlan> lens;
     std::map<int, BluePlan> blues;
+    std::map<int, std::array<int64_t, 3>> convs;  // by prime: W_P, spectrum, permutations
     std::map<int, int64_t> tws;  // first root of unity by length
     std::vector<long double> pool;  // interleaved re, im
     const long double pi = 3.141592653589793238462643383279502884L;
@@ -581,12 +651,20 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         // run as a general prime pass (first, at Ns = 1) instead of Bluestein
         // when one field's output units fit the block's waves and, above 191,
         // when ring_cost favours it
-        bool gp = rem > 1 && rem <= kGpMaxPrime && is_prime(rem) &&
+        const int fmost = std::max(1, std::min(F, cap / (h + 1)));
+        const bool prime = rem > 1 && is_prime(rem);
+        bool gp = prime && rem <= kGpMaxPrime &&
                   gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
-        if (gp && rem > 191 && Lb <= cap)
-            gp = ring_cost(h, h, 0, rem, gp_fields(rem, h, std::max(1, std::min(F, cap / (h + 1))))) <
-                 ring_cost(h, bl.second, bl.first, 0, 1);
-        if (rem == 1 || gp) {
+        const double bcost = Lb <= cap ? ring_cost(h, bl.second, bl.first, 0, 1) : 1e300;
+        const double gcost = gp ? ring_cost(h, h, 0, rem, gp_fields(rem, h, fmost)) : 1e300;
+        if (gp && rem > 191 && gcost >= bcost) gp = false;
+        // a prime pass by convolution takes the place of either where its
+        // passes cost less: from primes of about 97 on
+        if (prime && (gp || Lb <= cap)) {
+            lp.conv = conv_passes(rem, h / rem, fmost, dbl);
+            if (ring_cost(h, h, 0, 0, 1, lp.conv.cost) >= (gp ? gcost : bcost)) lp.conv = PassPlan();
+        }
+        if (rem == 1 || gp || !lp.conv.rad.empty()) {
             lp.L = h;
             lp.blue = 0;
         } else {
@@ -600,19 +678,26 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
             if (!lp.blue && q >= 11 && lp.L / q > kFftThreads) return SHTX_EUNSUPPORTED;
         for (int dir = 0; dir < 2; ++dir) {
             PassPlan &pp = lp.pass[dir];
-            pp = lp.blue ? blues[lp.L].pass[dir] : plan_passes(lp.L, gp ? rem : 1, dir == 1, dbl);
+            pp = lp.blue ? blues[lp.L].pass[dir] : plan_passes(lp.L, rem, dir == 1, dbl);
+            const int nconv = (int)lp.conv.rad.size(), P = nconv ? rem - 1 : 0;
+            if (nconv && !pp.rad.empty()) {
+                pp.rad.erase(pp.rad.begin());
+                pp.rad.insert(pp.rad.begin(), lp.conv.rad.begin(), lp.conv.rad.end());
+                pp.seam = lp.conv.seam;
+            }
             if (pp.rad.empty() || (int)pp.rad.size() > kMaxRadices) return SHTX_EUNSUPPORTED;
             lp.pass_off[dir] = (int)p.passes.size();
             for (int s = 0, Ns = 1; s < (int)pp.rad.size(); ++s) {
                 PassDesc q{};
+                const int len = s < nconv ? P : lp.L;
                 q.R = pp.rad[s];
                 q.Ns = Ns;
-                q.nbf = lp.L / q.R;
-                q.tstep = lp.L / (Ns * q.R);
+                q.nbf = len / q.R;
+                q.tstep = len / (Ns * q.R);
                 q.mg_nbf = div_magic(q.nbf);
                 q.mg_ns = div_magic(Ns);
                 p.passes.push_back(q);
-                Ns = s == pp.seam ? q.R : Ns * q.R;  // the seam begins the second FFT
+                Ns = s == pp.seam ? q.R : s == nconv - 1 ? rem : Ns * q.R;  // the seam begins the second FFT
             }
         }
         auto push = [&](long double re, long double im) {
@@ -644,6 +729,35 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         }
         lp.tw = tw;
         lp.chirp = lp.bhat = -1;
+        if (!lp.conv.rad.empty()) {
+            // roots of unity of P, (g^k, g^-k), and the spectrum over P of the
+            // filter W_p^(g^-k), shared between rings
+            const int pr = rem, P = pr - 1;
+            auto &cv = convs[pr];
+            if (!cv[0]) {
+                std::vector<int> g((size_t)P);
+                const int root0 = primitive_root(pr);
+                for (int k = 0, x = 1; k < P; ++k, x = (int)((int64_t)x * root0 % pr)) g[k] = x;
+                std::vector<cld> w((size_t)P), b((size_t)P);
+                cv[0] = (int64_t)pool.size() / 2;
+                for (int k = 0; k < P; ++k) {
+                    root(2.0L * pi * k / P);
+                    w[k] = {pool[pool.size() - 2], pool[pool.size() - 1]};
+                    const long double a = 2.0L * pi * g[(P - k) % P] / pr;
+                    b[k] = {cosl(a), -sinl(a)};
+                }
+                dft_ld(b.data(), P, w, P);
+                cv[1] = (int64_t)pool.size() / 2;
+                for (int k = 0; k < P; ++k) push(b[k].real() / P, b[k].imag() / P);
+                cv[2] = (int64_t)pool.size() / 2;
+                const long double bias = dbl ? 0x1p52L : 0x1p23L;
+                for (int k = 0; k < P; ++k) push(bias + g[k], bias + g[(P - k) % P]);
+            }
+            lp.bhat = cv[1];
+            lp.conv_tw = cv[0];
+            lp.conv_perm = cv[2];
+            lp.conv_p = pr;
+        }
         if (lp.blue) {
             lp.chirp = (int64_t)pool.size() / 2;
             for (int k = 0; k < h; ++k) {
@@ -682,7 +796,11 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         d.fuse_out_r = lp.pass[1].fuse_out;
         d.seam = lp.pass[0].seam;
         d.seam_r = lp.pass[1].seam;
-        d.blue_cost = lp.blue ? (float)blues[lp.L].cost : 0.f;
+        d.blue_cost = lp.blue ? (float)blues[lp.L].cost : lp.conv.rad.empty() ? 0.f : (float)lp.conv.cost;
+        d.conv = (int)lp.conv.rad.size();
+        d.conv_p = lp.conv_p;
+        d.conv_tw_off = lp.conv_tw;
+        d.conv_perm_off = lp.conv_perm;
         d.lbuf = std::max(d.L, d.h + 1);
         d.lbufp = d.lbuf;
         d.tw_off = lp.tw;

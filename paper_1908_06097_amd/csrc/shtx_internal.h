@@ -34,8 +34,21 @@ __host__ __device__ constexpr int fft_rounds(int cap, int R)
 // place; the r2c kernel's first pass, from the grid row; the c2r kernel's first
 // pass, from the Fourier rows with the merge step; the c2r kernel's last pass,
 // to the grid row; the r2c kernel's last pass, with the split step to the
-// Fourier rows; the seam between Bluestein's two FFTs, in LDS.
-enum FftPassKind { kPassLds = 0, kPassFromGrid = 1, kPassFromFour = 2, kPassToGrid = 3, kPassToFour = 4, kPassSeam = 5 };
+// Fourier rows; the seam between Bluestein's two FFTs, in LDS; and of a prime
+// pass by convolution, all in LDS, its first pass, those between, its seam and
+// its last pass.
+enum FftPassKind {
+    kPassLds = 0,
+    kPassFromGrid = 1,
+    kPassFromFour = 2,
+    kPassToGrid = 3,
+    kPassToFour = 4,
+    kPassSeam = 5,
+    kPassGather = 6,
+    kPassSub = 7,
+    kPassSubSeam = 8,
+    kPassScatter = 9
+};
 
 // Radices with a butterfly of each kind.  The Fourier-side passes hold a pair of
 // butterflies (j and its mirror) per thread, so their radices stop earlier;
@@ -51,6 +64,10 @@ __host__ __device__ constexpr bool fft_radix_ok(int kind, bool dbl, int R)
     case kPassToGrid: return R <= 10 || R == 12 || R == 16 || (!dbl && (R == 14 || R == 15 || R == 18 || R == 20));
     case kPassToFour: return R <= 6 || R == 8 || (!dbl && (R == 7 || R == 9));
     case kPassSeam: return R == 9 || R == 10 || (dbl ? R == 12 : R == 15 || R == 18);
+    case kPassGather: case kPassSub: return R <= 19 || R == 23;
+    case kPassScatter: return R <= 11 || (R >= 13 && R <= 17) || R == 19;
+    case kPassSubSeam:
+        return R == 4 || R == 6 || R == 8 || R == 9 || R == 10 || (R >= 14 && R <= 16) || (!dbl && (R == 12 || R == 18));
     }
     return false;
 }
@@ -159,11 +176,14 @@ struct RingDesc {
     int fuse_in, fuse_out;      // c2r: first pass merges, last pass writes the grid
     int fuse_in_r, fuse_out_r;  // r2c: first pass reads the grid, last pass splits
     int seam, seam_r;           // index of Bluestein's seam pass, c2r and r2c (-1: none)
-    float blue_cost;            // Bluestein: cost of its passes (host only)
+    float blue_cost;            // cost of Bluestein's or the convolution's passes (host only)
+    int conv, conv_p;           // a prime pass by convolution: its passes (0: none), its prime
+    int64_t conv_tw_off;        // W_{p-1}
+    int64_t conv_perm_off;      // (g^k, g^-k) mod p, g a primitive root, k < p - 1, each plus 2^23 (FP64: 2^52)
     int64_t tw_off;     // W_L[k] = exp(-2 pi i k / L), k < L
     int64_t post_off;   // exp(-2 pi i m / n), m <= h
     int64_t chirp_off;  // Bluestein chirp exp(-pi i k^2 / h), k < h
-    int64_t bhat_off;   // Bluestein filter spectrum / L, L entries
+    int64_t bhat_off;   // Bluestein filter spectrum / L, L entries; a convolution's / (p - 1), p - 1 entries
     int64_t grid_off;   // first point of the ring inside one grid field
     int64_t four_off;   // first complex of the ring's [m][nfld] block
     double w;           // Gauss weight

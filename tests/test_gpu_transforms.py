@@ -224,6 +224,30 @@ def test_bluestein_passes_parity(prec, F):
         plan.close()
 
 
+# Prime passes by convolution: every radix of their first, middle and last
+# passes and of the pass between their two FFTs, three to seven passes, primes
+# alone and before other radices, and lengths near the smallest and the largest
+# that take them; one field, and enough for a shorter last run.
+CONV_LENGTHS = {
+    "fp64": [4754, 628, 922, 1906, 3242, 6002, 6274, 482, 194, 5702, 5770, 254, 398, 3194, 202, 226, 262, 274, 394, 514,
+             5834, 16336],
+    "fp32": [5042, 1412, 7778, 758, 922, 4286, 6658, 302, 1142, 362, 274, 842, 1622, 194, 218, 262, 292, 356, 382, 386,
+             394, 662, 1538, 16336],
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("F", [1, 11])
+def test_prime_convolution_parity(prec, F):
+    shtx = _shtx()
+    for nlon in CONV_LENGTHS[prec]:
+        N = 20
+        _say(f"prime convolution nlon={nlon} F={F} {prec}")
+        plan = shtx.Plan(N, "full", 4, F, prec, nlon_full=nlon)
+        _check_all(plan, N, plan.ring_lengths(), 43, range(F), prec)
+        plan.close()
+
+
 # General prime passes in every tile shape of output units (row tiles of the
 # prime by column tiles of the block's butterflies): small primes with many
 # butterflies, large ones with two, and field counts that leave a block's last
