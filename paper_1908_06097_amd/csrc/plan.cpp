@@ -661,7 +661,13 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         // a prime pass by convolution takes the place of either where its
         // passes cost less: from primes of about 97 on
         if (prime && (gp || Lb <= cap)) {
+            // passes of radix 13, 14 and 15 run one round of butterflies: with
+            // them a block takes fewer fields than its LDS holds (2504 points,
+            // 411 fields, 6.0 -> 4.0 ps per point), unless that splits a call's
+            // few fields over two blocks (O1280, 3 fields, 108 -> 113 us)
             lp.conv = conv_passes(rem, h / rem, fmost, dbl);
+            if (lp.conv.rad.empty() && fmost < F && kFftThreads * 13 / h > 0)
+                lp.conv = conv_passes(rem, h / rem, std::min(fmost, kFftThreads * 13 / h), dbl);
             if (ring_cost(h, h, 0, 0, 1, lp.conv.cost) >= (gp ? gcost : bcost)) lp.conv = PassPlan();
         }
         if (rem == 1 || gp || !lp.conv.rad.empty()) {

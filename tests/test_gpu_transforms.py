@@ -227,12 +227,13 @@ def test_bluestein_passes_parity(prec, F):
 # Prime passes by convolution: every radix of their first, middle and last
 # passes and of the pass between their two FFTs, three to seven passes, primes
 # alone and before other radices, and lengths near the smallest and the largest
-# that take them; one field, and enough for a shorter last run.
+# that take them, and radix-13 passes that take fewer fields a block than fit the
+# LDS; one field, and enough for a shorter last run.
 CONV_LENGTHS = {
     "fp64": [4754, 628, 922, 1906, 3242, 6002, 6274, 482, 194, 5702, 5770, 254, 398, 3194, 202, 226, 262, 274, 394, 514,
-             5834, 16336],
+             5834, 1042, 2084, 16336],
     "fp32": [5042, 1412, 7778, 758, 922, 4286, 6658, 302, 1142, 362, 274, 842, 1622, 194, 218, 262, 292, 356, 382, 386,
-             394, 662, 1538, 16336],
+             394, 662, 1538, 1042, 2084, 16336],
 }
 
 
