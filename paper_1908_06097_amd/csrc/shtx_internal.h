@@ -83,8 +83,9 @@ __host__ __device__ constexpr bool blue_last_radix(int R, bool dbl)
 }
 
 // General prime pass: a ring whose half-length has one prime factor p above
-// the register radices, p <= kGpMaxPrime, runs it as the first pass on the
-// matrix cores, reading the p-th roots of unity from p LDS entries after the
+// the register radices, p <= kGpMaxPrime, may run it as the first pass on the
+// matrix cores (the plan chooses between it, a convolution and Bluestein),
+// reading the p-th roots of unity from p LDS entries after the
 // field slots.  Its outputs come in units of 16 rows t (t = 0 .. (p-1)/2) by
 // 16 columns (butterfly, real | imaginary part); each wave holds one tile of
 // NI x NJ of them, at most kGpUnits (more would push the FFT kernels past the

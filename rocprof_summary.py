@@ -47,16 +47,12 @@ def classify(name):
     if "k_uv_spec" in name:
         # the wind step, launched with the inverse GEMM it feeds
         return "legendre_inverse_gemm"
-    if "k_leg_mfma" in name or "k_leg_split" in name:
-        # the inverse-shaped instantiation has template argument INV = true
-        # (5th of k_leg_mfma<T, BM, BN, BK, INV, NW> and of
-        # k_leg_split<F16, BM, BN, BK, INV>)
+    if "k_leg_mfma" in name or "k_leg_split" in name or "k_leg_narrow" in name:
+        # the inverse-shaped instantiation has template argument INV = true,
+        # the last bool of each GEMM kernel's arguments
         args = re.search(r"<([^<>]*)>", name)
-        if args:
-            parts = [x.strip() for x in args.group(1).split(",")]
-            inv = len(parts) > 4 and parts[4] == "true"
-        else:
-            inv = name.endswith("Lb1EEEvNS0_8GemmArgsE") or "Lb1ELi8E" in name or "Lb1ELi4E" in name
+        bools = re.findall(r"\b(true|false)\b", args.group(1)) if args else re.findall(r"Lb([01])E", name)
+        inv = bool(bools) and bools[-1] in ("true", "1")
         return "legendre_inverse_gemm" if inv else "legendre_direct_gemm"
     if "k_fft_c2r" in name:
         return "ring_fft_c2r"
