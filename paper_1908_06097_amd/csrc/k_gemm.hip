@@ -589,16 +589,21 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 // FP32 and the split forms, on the half-precision matrix cores with FP32
 // accumulation.  Each operand is a sum of 16-bit pieces and a tile product is
 // the MFMAs of the piece pairs that matter, smallest first:
-//   SHTX_FP32    three bfloat16 pieces, 8 + 8 + 8 significand bits: every float
-//                exactly; the six products down to 2^-16 of the largest (what
-//                is dropped is below 2^-24 of it)
+//   SHTX_FP32    three bfloat16 pieces, 8 + 8 + 8 significand bits: a float
+//                exactly, if it is not below 2^-110, where pieces fall under
+//                bfloat16's smallest value; the six products down to 2^-16
+//                of the largest
 //   SHTX_BF16X3  bfloat16 hi + lo, three products (lo lo is dropped)
 //   SHTX_FP16X3  IEEE half hi + lo, three products
-// The table is stored in pieces, for the split forms scaled by 2^e_m per m; the
-// data operand is cut into pieces here, once per block and stage.  IEEE half
-// has a 5-bit exponent, so its data operand is also scaled per field by 2^E_f,
-// chosen from a bound on the field's largest value; bfloat16 has the FP32
-// exponent range and needs no data scale.  An infinite value gives NaN.
+// The table is stored in pieces, for the split forms scaled by 2^e_m per m, for
+// FP32 by 2^16 (its smallest entries in full); the data operand is cut into
+// pieces here, once per block and stage.  IEEE half has a 5-bit exponent, so
+// its data operand is also scaled per field by 2^E_f, chosen from a bound on
+// the field's largest value; bfloat16 has the FP32 exponent range and needs no
+// data scale.  A tile of the FP32 form that meets a smaller value than its
+// pieces hold, one that is not finite, or a sum beyond 2^112 runs again on the
+// single-precision matrix cores: only there do such values keep 24 bits.  In
+// the split forms an infinite value gives NaN.
 //
 // 32x32x16 MFMA: lane l supplies A[l%32][8(l/32)..+7] and B[8(l/32)..+7][l%32]
 // and holds D[8(v/4) + 4(l/32) + v%4][l%32], v = 0..15.  Both operands come in
@@ -629,6 +634,10 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // instructions need only 4-byte alignment)
 typedef float f32x4a8 __attribute__((ext_vector_type(4), aligned(8)));
 
+// From this magnitude on a float is the sum of three bfloat16 pieces: its last
+// bit is bfloat16's smallest value, 2^-133, or more.
+constexpr float kPiecesHold = 0x1p-110f;
+
 // Two floats -> packed pieces, most significant first.  Residuals must be taken
 // against the very bits that are stored.  Left to itself the compiler
 // re-derives hi for that subtraction from the product that produced x, by
@@ -637,9 +646,10 @@ typedef float f32x4a8 __attribute__((ext_vector_type(4), aligned(8)));
 // roundings disagree; hi + lo is then off by a unit of hi.  An empty asm
 // statement makes the stored bits opaque, so the residual is computed from
 // them.  The FP32 form cuts its leading piece instead of rounding it: values
-// near the largest float stay finite.
+// near the largest float stay finite.  `least` takes the smallest magnitude
+// seen (FP32 form).
 template <int FORM>
-__device__ inline void split_pair(float x0, float x1, unsigned *w)
+__device__ inline void split_pair(float x0, float x1, unsigned *w, float &least)
 {
     if constexpr (FORM == SHTX_FP16X3) {
         unsigned hb = __builtin_bit_cast(unsigned, f16x2{(_Float16)x0, (_Float16)x1});
@@ -650,6 +660,8 @@ __device__ inline void split_pair(float x0, float x1, unsigned *w)
     } else {
         float r0 = x0, r1 = x1;
         if constexpr (FORM == SHTX_FP32) {
+            // one instruction (fminf would first quiet its operands)
+            asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(x0), "v"(x1));
             const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
             *w++ = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
             r0 = x0 - __uint_as_float(b0 & 0xffff0000u);
@@ -657,11 +669,22 @@ __device__ inline void split_pair(float x0, float x1, unsigned *w)
         }
         unsigned hb = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
         asm("" : "+v"(hb));
+        r0 -= __uint_as_float(hb << 16);
+        r1 -= __uint_as_float(hb & 0xffff0000u);
         w[0] = hb;
-        w[1] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(r0 - __uint_as_float(hb << 16)),
-                                                   (__bf16)(r1 - __uint_as_float(hb & 0xffff0000u))});
+        w[1] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
     }
 }
+
+// 32x32x2 MFMA on floats: lane l supplies A[l%32][l/32] and B[l/32][l%32]; the
+// result is laid out as that of the 16-bit forms.
+__device__ inline f32x16 mfma32x32x2(float a, float b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Half t (0: low) of a word as the high half of a float's bits.
+__device__ inline float piece_float(unsigned w, int t) { return __uint_as_float(t ? w & 0xffff0000u : w << 16); }
 
 template <int FORM>
 __device__ inline f32x16 mfma_split(u32x4 a, u32x4 b, f32x16 c)
@@ -728,6 +751,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     constexpr int NSMEM = PA + PB > NSTAGE ? PA + PB : NSTAGE;
     constexpr int NA = NP * FI;  // units of A per thread
     __shared__ u32x4 smem[NSMEM];
+    __shared__ int wave_lost[4];
     u32x4 *As = smem, *Bs = smem + PA;
 
     const GemmItem it = a.items[xcd_remap(blockIdx.x, gridDim.x)];
@@ -809,7 +833,24 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
             }
         }
     };
-    auto store = [&]() __attribute__((always_inline)) {
+    uint64_t lost = 0;  // lanes that met a value which its pieces do not hold
+    auto note = [&](float x) __attribute__((always_inline)) {
+        lost |= __builtin_amdgcn_ballot_w64(x != 0.f && fabsf(x) < kPiecesHold);
+    };
+    // WHOLE: the data operand's floats uncut, high halves in the plane of the
+    // first piece and low halves in that of the second
+    auto store = [&](auto whole_c) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole_c)::value;
+        constexpr int NB = WHOLE ? 2 : NP;
+        float least = 1.f;
+        auto cut = [&](float x0, float x1, unsigned *w) __attribute__((always_inline)) {
+            if constexpr (WHOLE) {
+                w[0] = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+                w[1] = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x05040100u);
+            } else {
+                split_pair<FORM>(x0, x1, w, least);
+            }
+        };
 #pragma unroll
         for (int i = 0; i < NA; ++i) As[(wave + 4 * i) * 64 + lane] = ra[i];
         if (!bon) return;
@@ -823,14 +864,20 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                 quad_transpose(x, bri, bp);
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
-                    split_pair<FORM>(off ? 0.f : x[2 * t] * scale, off ? 0.f : x[2 * t + 1] * scale, w[2 * i + t]);
+                    cut(off ? 0.f : x[2 * t] * scale, off ? 0.f : x[2 * t + 1] * scale, w[2 * i + t]);
             }
 #pragma unroll
             for (int kc = 0; kc < 2; ++kc) {
                 u32x4 *dst = Bs + (2 * bp + kc) * UB + bri * URI + bf;
 #pragma unroll
-                for (int h = 0; h < NP; ++h)
+                for (int h = 0; h < NB; ++h)
                     dst[h * 4 * UB] = u32x4{w[4 * kc][h], w[4 * kc + 1][h], w[4 * kc + 2][h], w[4 * kc + 3][h]};
+            }
+            if (FORM == SHTX_FP32 && !WHOLE && __builtin_expect(__builtin_amdgcn_ballot_w64(least < kPiecesHold) != 0, 0)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) note(m == 0 && (t & 1) ? 0.f : rb[i][t]);
             }
         } else {
             // hemispheric fold: parity 0 takes q (north + south), parity 1 q (north - south)
@@ -845,24 +892,34 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                         const int q = 2 * i + t;
                         x[t] = (q1[q] * scale) * (p ? rn[q] - rs[q] : rn[q] + rs[q]);
                     }
-                    split_pair<FORM>(x[0], x[1], w[i]);
+                    cut(x[0], x[1], w[i]);
                 }
                 u32x4 *dst = Bs + (2 * p + kh) * UB + (tid & 1) * URI + bf;
 #pragma unroll
-                for (int h = 0; h < NP; ++h) dst[h * 4 * UB] = u32x4{w[0][h], w[1][h], w[2][h], w[3][h]};
+                for (int h = 0; h < NB; ++h) dst[h * 4 * UB] = u32x4{w[0][h], w[1][h], w[2][h], w[3][h]};
+            }
+            if (FORM == SHTX_FP32 && !WHOLE && __builtin_expect(__builtin_amdgcn_ballot_w64(least < kPiecesHold) != 0, 0)) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    note(q1[q] * (rn[q] + rs[q]));
+                    note(q1[q] * (rn[q] - rs[q]));
+                }
             }
         }
     };
 
     f32x16 acc[2][NI][2];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0.f;
+                    for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0.f;
+    };
+    clear();
 
     auto kloop = [&](auto ni_c) __attribute__((always_inline)) {
         constexpr int NA_I = decltype(ni_c)::value;  // row fragments in use
@@ -871,7 +928,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
         load(0);
         if (!INV) meta(BK);
         for (int s = 0; s < nstages; ++s) {
-            store();
+            store(std::false_type{});
             __syncthreads();
             if (s + 1 < nstages) load((s + 1) * BK);  // in flight during the MFMAs
             if (!INV) meta((s + 2) * BK);
@@ -916,11 +973,94 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     else
         kloop(std::integral_constant<int, 1>{});
 
+    // INV: the two parities' sums become the two hemispheres'
+    auto fold = [&]() __attribute__((always_inline)) {
+        if constexpr (!INV) return;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float x0 = acc[0][i][j][v], x1 = acc[1][i][j][v];
+                    acc[0][i][j][v] = x0 + x1;
+                    acc[1][i][j][v] = x0 - x1;
+                }
+    };
+    // A tile that met a value which is not the sum of its pieces (below 2^-110, or
+    // not finite), or whose sums left the range that the table's scale leaves,
+    // runs once more, as plain single-precision products on the FP32 matrix
+    // cores (the table's pieces are exact; 1/5 of the rate, but no ordinary
+    // field comes here).  All four waves go or none.
+    float unit = FORM == SHTX_FP32 ? 1.f / kF32TableScale : 1.f;
+    fold();
+    if constexpr (FORM == SHTX_FP32) {
+        // (an inverse tile's northern sums alone: they are finite only if both
+        // parities' are)
+#pragma unroll
+        for (int p = 0; p < (INV ? 1 : 2); ++p)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        lost |= __builtin_amdgcn_ballot_w64(!__builtin_isfinite(acc[p][i][j][v]));
+        if (lane == 0) wave_lost[wave] = lost != 0;
+        __syncthreads();
+        if (__builtin_expect(wave_lost[0] | wave_lost[1] | wave_lost[2] | wave_lost[3], 0)) {
+            unit = 1.f;
+            clear();
+            for (int s = 0; s < nstages; ++s) {
+                if (!INV) meta(s * BK);
+                load(s * BK);
+                store(std::true_type{});
+                __syncthreads();
+                const int kc = lane >> 5, ln = lane & 31;
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    u32x4 av[NI][NP], bv[2][2];
+#pragma unroll
+                    for (int h = 0; h < NP; ++h)
+#pragma unroll
+                        for (int i = 0; i < NI; ++i)
+                            av[i][h] = As[((2 * h + p) * 2 + kc) * UA + 32 * (WR * i + wr) + ln];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) bv[j][h] = Bs[((2 * h + p) * 2 + kc) * UB + j * URI + 32 * fj + ln];
+                    // kappa t of the lower half of the lanes with kappa 8 + t of the upper
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        float x[NI], y[2];
+#pragma unroll
+                        for (int i = 0; i < NI; ++i) {
+                            float z = piece_float(av[i][NP - 1][t / 2], t & 1);
+#pragma unroll
+                            for (int h = NP - 2; h >= 0; --h) z += piece_float(av[i][h][t / 2], t & 1);
+                            x[i] = z * (1.f / kF32TableScale);
+                        }
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            y[j] = __uint_as_float(__builtin_amdgcn_perm(bv[j][0][t / 2], bv[j][1][t / 2],
+                                                                         t & 1 ? 0x07060302u : 0x05040100u));
+#pragma unroll
+                        for (int i = 0; i < NI; ++i)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) acc[p][i][j] = mfma32x32x2(x[i], y[j], acc[p][i][j]);
+                    }
+                }
+                __syncthreads();
+            }
+            fold();
+        }
+    }
+
     auto frag_row = [&](int i, int v) { return 32 * (WR * i + wr) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
     // undoes the scales of the table block and of this lane's field
     int e = 0;
     if constexpr (FORM != SHTX_FP32) e = -(b.e + (F16 ? field_exp(a.fmax, min(f, a.nfld - 1), a.dbound) : 0));
-    auto unscale = [&](float x) { return FORM == SHTX_FP32 ? x : ldexpf(x, e); };
+    auto unscale = [&](float x) { return FORM == SHTX_FP32 ? x * unit : ldexpf(x, e); };
     if constexpr (INV) {
         // a lane holds its field's real and imaginary part of each row: runs of
         // 32 fields straight to both hemispheres' rows
@@ -935,9 +1075,8 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                 const int r = frag_row(i, v);
                 const RingPair o = orows[r];
                 if (row0 + r >= b.R || f >= a.nfld) continue;
-                const float x0 = acc[0][i][0][v], x1 = acc[1][i][0][v], y0 = acc[0][i][1][v], y1 = acc[1][i][1][v];
-                four[((int64_t)o.n + m) * a.nfld + f] = float2{unscale(x0 + x1), unscale(y0 + y1)};
-                four[((int64_t)o.s + m) * a.nfld + f] = float2{unscale(x0 - x1), unscale(y0 - y1)};
+                four[((int64_t)o.n + m) * a.nfld + f] = float2{unscale(acc[0][i][0][v]), unscale(acc[0][i][1][v])};
+                four[((int64_t)o.s + m) * a.nfld + f] = float2{unscale(acc[1][i][0][v]), unscale(acc[1][i][1][v])};
             }
     } else {
         // 32 fields at a time as [field][n], written as runs of n

@@ -250,7 +250,7 @@ __global__ void k_legendre_table(int trunc, const double *mu, const double *diag
         const int t = n - m, par = t & 1, k = t >> 1;
         const int64_t blk = 2 * (int64_t)b.Kp * b.Rp;  // entries of the block, and of each piece
         unsigned short w[NP];
-        if (INV_UNITS || DIR_UNITS) table_split<PREC>(v * scale, w);
+        if (INV_UNITS || DIR_UNITS) table_split<PREC>(v * (PREC == SHTX_FP32 ? (double)kF32TableScale : scale), w);
         if (INV_UNITS) {
             unsigned short *dst = (unsigned short *)tab_inv + NP * b.off;
 #pragma unroll

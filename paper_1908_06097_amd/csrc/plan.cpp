@@ -594,6 +594,7 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         b.K1 = (N - m + 1) / 2;
         b.Rp = (int)round_up(std::max(b.R, 1), kTablePad);
         b.Kp = (int)round_up(b.K0, kTablePad);
+        b.e = prec == SHTX_FP32 ? kF32TableExp : 0;  // the split forms' are set with the tables
         b.off = off;
         off += 2 * (int64_t)b.Kp * b.Rp;
         p.mb[m] = b;

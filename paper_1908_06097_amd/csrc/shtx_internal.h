@@ -152,7 +152,7 @@ struct MBlock {
     int j0;         // first such ring
     int K0, K1;     // number of n = m + p + 2k <= N for parity p = 0, 1
     int Rp, Kp;     // padded ring and parity-k extents
-    int e;          // power-of-two exponent applied to the stored split table
+    int e;          // power-of-two exponent applied to the stored table pieces
     int pad_;
     int64_t off;    // entries of the m blocks before this one (2 Kp Rp each)
 };
@@ -223,6 +223,10 @@ inline bool split_form(int prec) { return prec == SHTX_BF16X3 || prec == SHTX_FP
 // 16-bit pieces of a table entry in the half-precision matrix-core GEMM (FP32:
 // three bfloat16).
 __host__ __device__ constexpr int split_pieces(int prec) { return prec == SHTX_FP32 ? 3 : 2; }
+// Scale of a single-precision plan's table pieces: the last bit of the smallest
+// normal float, 2^-149, times 2^16 is bfloat16's smallest value.
+constexpr int kF32TableExp = 16;
+constexpr float kF32TableScale = 65536.f;
 
 struct Plan {
     int trunc = 0, grid = 0, nlat = 0, nlon_full = 0, nfld = 0, prec = 0;
