@@ -973,8 +973,9 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     else
         kloop(std::integral_constant<int, 1>{});
 
-    // INV: the two parities' sums become the two hemispheres'
-    auto fold = [&]() __attribute__((always_inline)) {
+    // INV: the two parities' sums become the two hemispheres' (FP32: without the
+    // table's scale, so that they are finite wherever those are)
+    auto fold = [&](float unit) __attribute__((always_inline)) {
         if constexpr (!INV) return;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -982,9 +983,10 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const float x0 = acc[0][i][j][v], x1 = acc[1][i][j][v];
-                    acc[0][i][j][v] = x0 + x1;
-                    acc[1][i][j][v] = x0 - x1;
+                    const float x0 = FORM == SHTX_FP32 ? unit * acc[0][i][j][v] : acc[0][i][j][v];
+                    const float x1 = acc[1][i][j][v];
+                    acc[0][i][j][v] = FORM == SHTX_FP32 ? fmaf(x1, unit, x0) : x0 + x1;
+                    acc[1][i][j][v] = FORM == SHTX_FP32 ? fmaf(x1, -unit, x0) : x0 - x1;
                 }
     };
     // A tile that met a value which is not the sum of its pieces (below 2^-110, or
@@ -993,7 +995,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     // cores (the table's pieces are exact; 1/5 of the rate, but no ordinary
     // field comes here).  All four waves go or none.
     float unit = FORM == SHTX_FP32 ? 1.f / kF32TableScale : 1.f;
-    fold();
+    fold(unit);
     if constexpr (FORM == SHTX_FP32) {
         // (an inverse tile's northern sums alone: they are finite only if both
         // parities' are)
@@ -1052,7 +1054,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                 }
                 __syncthreads();
             }
-            fold();
+            fold(unit);
         }
     }
 
@@ -1060,7 +1062,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     // undoes the scales of the table block and of this lane's field
     int e = 0;
     if constexpr (FORM != SHTX_FP32) e = -(b.e + (F16 ? field_exp(a.fmax, min(f, a.nfld - 1), a.dbound) : 0));
-    auto unscale = [&](float x) { return FORM == SHTX_FP32 ? x * unit : ldexpf(x, e); };
+    auto unscale = [&](float x) { return FORM != SHTX_FP32 ? ldexpf(x, e) : INV ? x : x * unit; };
     if constexpr (INV) {
         // a lane holds its field's real and imaginary part of each row: runs of
         // 32 fields straight to both hemispheres' rows

@@ -52,6 +52,26 @@ def test_amplitudes(shape):
         assert np.isfinite(got).all() and er.max() < TOL_RMS["fp32"], (name, worst)
 
 
+# Amplitudes around the one from which the scaled sums of a tile leave a float's
+# range, in steps fine enough for tiles in which only the difference of the two
+# parities' sums does.
+@pytest.mark.parametrize("shape", SHAPES)
+def test_largest_sums(shape):
+    shtx, o = _shtx(), _oracle()
+    n, nlat, nf = 15, 32, 20
+    plan = shtx.Plan(n, "octahedral", nlat, nf, "fp32")
+    plan.set_shapes(shape, shape, plan.info.fft_cap)
+    nlon = plan.ring_lengths()
+    _, w = o.gauss(nlat)
+    base = si.spectral_fields(n, 55, range(nf))
+    for k in range(8 * 104, 8 * 114):
+        amp = 2.0 ** (k / 8)
+        a = (base * amp).astype(np.complex64)
+        _, er = grid_errors(_np(plan.inv(_dev(a, plan.complex_dtype))) / amp,
+                            o.inv(n, nlon, a.astype(np.complex128)) / amp, nlon, w)
+        assert er.max() < TOL_RMS["fp32"], (shape, k / 8, er.max())
+
+
 # Wavenumbers whose table entries are near the smallest float on the rings away
 # from the equator, with inputs of 2^30 that bring the results back into range:
 # entry by entry, on the rings of a field of those wavenumbers, and in the
