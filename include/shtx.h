@@ -35,8 +35,8 @@
  * Precision forms (the Legendre arithmetic; the ring FFTs run in the grid
  * type): SHTX_FP64 plain double; SHTX_FP32 single precision with FP32
  * accumulation over the whole range of a float (on the half-precision matrix
- * cores each operand is its exact sum of three bfloat16, six products of which
- * count; where a value is below 2^-110 or not finite, or a sum is above 2^112,
+ * cores each operand is its exact sum of three bfloat16, and of the products of
+ * a pair's pieces six count: the rest is below 2^-24 of it; where a value is below 2^-110 or not finite, or a sum is above 2^112,
  * plain single-precision products); SHTX_BF16X3 split bfloat16 hi+lo operands
  * (three products, lo*lo dropped) with per-m power-of-two scaling of the
  * Legendre table and FP32 accumulation; SHTX_FP16X3 the same split with IEEE

@@ -592,7 +592,8 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 //   SHTX_FP32    three bfloat16 pieces, 8 + 8 + 8 significand bits: a float
 //                exactly, if it is not below 2^-110, where pieces fall under
 //                bfloat16's smallest value; the six products down to 2^-16
-//                of the largest
+//                of the largest (those left out come to 2^-24.0 of it at
+//                most, 2^-27 on average; FP32 rounds each sum to 2^-24)
 //   SHTX_BF16X3  bfloat16 hi + lo, three products (lo lo is dropped)
 //   SHTX_FP16X3  IEEE half hi + lo, three products
 // The table is stored in pieces, for the split forms scaled by 2^e_m per m, for
@@ -645,8 +646,10 @@ constexpr float kPiecesHold = 0x1p-110f;
 // half once) whose result differs from the stored hi wherever the two
 // roundings disagree; hi + lo is then off by a unit of hi.  An empty asm
 // statement makes the stored bits opaque, so the residual is computed from
-// them.  The FP32 form cuts its leading piece instead of rounding it: values
-// near the largest float stay finite.  `least` takes the smallest magnitude
+// them.  All pieces are rounded to nearest: with the FP32 form's leading one cut
+// instead, the products left out reached twice as much (2^-23 of a product).
+// A value near the largest float rounds to an infinite piece, and its sums to
+// NaN: the tile runs again.  `least` takes the smallest magnitude
 // seen (FP32 form).
 template <int FORM>
 __device__ inline void split_pair(float x0, float x1, unsigned *w, float &least)
@@ -659,20 +662,21 @@ __device__ inline void split_pair(float x0, float x1, unsigned *w, float &least)
         w[1] = __builtin_bit_cast(unsigned, f16x2{(_Float16)(x0 - (float)h[0]), (_Float16)(x1 - (float)h[1])});
     } else {
         float r0 = x0, r1 = x1;
+        // a piece of both, which leaves the rest in r0 and r1
+        auto piece = [&]() __attribute__((always_inline)) {
+            unsigned hb = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
+            asm("" : "+v"(hb));
+            r0 -= __uint_as_float(hb << 16);
+            r1 -= __uint_as_float(hb & 0xffff0000u);
+            return hb;
+        };
+        w[0] = piece();
         if constexpr (FORM == SHTX_FP32) {
             // one instruction (fminf would first quiet its operands)
             asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(x0), "v"(x1));
-            const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
-            *w++ = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-            r0 = x0 - __uint_as_float(b0 & 0xffff0000u);
-            r1 = x1 - __uint_as_float(b1 & 0xffff0000u);
+            w[1] = piece();
         }
-        unsigned hb = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
-        asm("" : "+v"(hb));
-        r0 -= __uint_as_float(hb << 16);
-        r1 -= __uint_as_float(hb & 0xffff0000u);
-        w[0] = hb;
-        w[1] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
+        w[split_pieces(FORM) - 1] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
     }
 }
 

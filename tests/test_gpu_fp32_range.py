@@ -10,7 +10,7 @@ import pytest
 
 import synth_inputs as si
 from error_metrics import grid_errors, spec_errors
-from test_gpu_transforms import TOL_RMS, _dev, _np, _oracle, _say, _shtx
+from test_gpu_transforms import TOL_RMS, _dev, _np, _oracle, _say, _shtx, _torch
 
 pytestmark = pytest.mark.gpu
 
@@ -128,3 +128,69 @@ def test_values_not_finite(shape):
     assert np.isnan(g[7]).any()
     rest = [f for f in range(F) if f not in (3, 5, 7)]
     np.testing.assert_allclose(g[rest], clean[rest], rtol=0, atol=1e-5 * np.abs(clean).max())
+
+
+# Every one of the six products of pieces counts: leaving one out costs 2.4e-6 to
+# 2.8e-6 RMS of a sum of random operands (numpy, K = 512, all pieces rounded to
+# nearest), and FP32 transforms of this size stay below 1e-6.
+TOL_SIX_PRODUCTS = 1.5e-6
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_all_products(shape):
+    o = _oracle()
+    for n, nf in ((N, F), (130, 65)):
+        plan = _shtx().Plan(n, "octahedral", 2 * (n + 1), nf, "fp32")
+        plan.set_shapes(shape, shape, plan.info.fft_cap)
+        nlon = plan.ring_lengths()
+        _, w = o.gauss(len(nlon))
+        a = si.spectral_fields(n, 59, range(nf)).astype(np.complex64)
+        y = np.stack([si.white_noise_grid(int(nlon.sum()), 900 + f) for f in range(nf)]).astype(np.float32)
+        a64, y64 = a.astype(np.complex128), y.astype(np.float64)
+        spec, grid = _dev(a, plan.complex_dtype), _dev(y, plan.real_dtype)
+        for name in ("inv", "dir_adj"):
+            _, er = grid_errors(_np(getattr(plan, name)(spec)), getattr(o, name)(n, nlon, a64), nlon, w)
+            _say(f"  {shape} T{n} {name} rms {er.max():.2e}")
+            assert er.max() < TOL_SIX_PRODUCTS
+        for name in ("dir", "inv_adj"):
+            _, er = spec_errors(_np(getattr(plan, name)(grid)), getattr(o, name)(n, nlon, y64), n)
+            _say(f"  {shape} T{n} {name} rms {er.max():.2e}")
+            assert er.max() < TOL_SIX_PRODUCTS
+
+
+def _nearest_bf16(x):
+    u = x.view(np.uint32).astype(np.uint64)
+    u = (u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000
+    return u.astype(np.uint32).view(np.float32)
+
+
+# The products left out stay below 2^-24 of a product, which takes pieces rounded
+# to nearest: a leading piece cut instead leaves out up to 2^-23.  One
+# coefficient a_1^0 in each field makes every value of F_0 one product; its
+# pieces, cut, are as large as pieces get.  The part of the results' error
+# that goes with what cutting leaves out (the slope of a regression on it, 1
+# for cut pieces; its standard error from roundings to 2^-24 is 0.03).
+@pytest.mark.parametrize("shape", SHAPES)
+def test_products_left_out(shape):
+    torch, o = _torch(), _oracle()
+    n, nlat, nl = 31, 256, 512
+    plan = _shtx().Plan(n, "full", nlat, F, "fp32", nlon_full=nl)
+    plan.set_shapes(shape, shape, plan.info.fft_cap)
+    mu, _ = plan.nodes()
+    p = o.legendre(n, 0, mu[:nlat // 2])[:, 1].astype(np.float32)  # P_1^0 on the northern rings
+
+    def pieces(x, first):
+        h = first(x)
+        m = _nearest_bf16(x - h)
+        return [v.astype(np.float64) for v in (h, m, x - h - m)]
+
+    x = (1 + 2.0 ** -7 - 2.0 ** -23 * (1 + np.arange(F))).astype(np.float32)
+    a = np.zeros((F, plan.nspec), np.complex64)
+    a[:, 1] = x
+    got = _np(plan.inv(torch.from_numpy(a).cuda())).astype(np.float64).reshape(F, nlat, nl)[:, :nlat // 2, 0]
+    exact = p.astype(np.float64)[None] * x.astype(np.float64)[:, None]
+    tab, cut = pieces(p, _nearest_bf16), pieces(x, lambda v: (v.view(np.uint32) & 0xFFFF0000).view(np.float32))
+    left = sum(tab[i][None] * cut[j][:, None] for i in range(3) for j in range(3 - i)) / exact - 1
+    slope = ((got / exact - 1) * left).sum() / (left * left).sum()
+    _say(f"  {shape} slope {slope:.3f}, error rms {np.sqrt(((got / exact - 1) ** 2).mean()):.2e}")
+    assert abs(slope) < 0.5
