@@ -811,13 +811,22 @@ __device__ inline void merge_pair(C2<T> &y0, C2<T> &y1, C2<T> pst)
     y1 = {A.x + t.y, A.y - t.x};
 }
 
+// Y_m / 2 of the adjoint of the direct transform, m > 0.  (Y_0 doubled and the
+// half in the last scale is one multiplication less, but overflows for F_0 from
+// half the largest value on.)
+template <typename T>
+__device__ inline C2<T> halved(C2<T> y)
+{
+    return {T(0.5) * y.x, T(0.5) * y.y};
+}
+
 // First pass of the c2r FFT (Ns = 1) with the merge step: a thread takes the
 // butterflies u and nbf - u of one field, whose inputs are each other's
 // mirrors (h - (u + r nbf) = (nbf - u) + (R - 1 - r) nbf), so that every
 // Fourier value is read once and merged in registers.  Consecutive lanes take
-// consecutive fields of a row (the runs in memory).  y0_fac: factor of Y_0.
+// consecutive fields of a row (the runs in memory).  adjoint: Y_m = F_m / c_m.
 template <typename T, int R>
-__device__ __attribute__((noinline)) void pass_from_four(FourSide<T> g, PassDesc pd, T y0_fac)
+__device__ __attribute__((noinline)) void pass_from_four(FourSide<T> g, PassDesc pd, bool adjoint)
 {
     constexpr int NB = R >= 8 ? 1 : 8 / R;
     constexpr unsigned CB = sizeof(C2<T>);
@@ -851,7 +860,14 @@ __device__ __attribute__((noinline)) void pass_from_four(FourSide<T> g, PassDesc
         for (int b = 0; b < NB; ++b) {
             const int u = uu[b];
             if (u < 0) continue;
-            if (u == 0) ya[b][0] = C2<T>{ya[b][0].x * y0_fac, T(0)};
+            if (u == 0) ya[b][0].y = T(0);
+            if (adjoint) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (u + r > 0) ya[b][r] = halved(ya[b][r]);
+                    yb[b][r] = halved(yb[b][r]);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r) merge_pair(ya[b][r], yb[b][R - 1 - r], ps[b][r]);
             dft_reg<T, R>(ya[b]);
@@ -1255,7 +1271,7 @@ __device__ inline bool grid_pairs(const RingDesc &d, int h, unsigned npts, const
 // issues the loads of kU elements before using any.
 template <typename T>
 __device__ inline void merge_to_lds(const RingDesc &d, const C2<T> *fourb, unsigned nfld, int nf, unsigned mg_nf,
-                                    const C2<T> *post, const C2<T> *chirp, T y0_fac)
+                                    const C2<T> *post, const C2<T> *chirp, bool adjoint)
 {
     LdsC2<T> *buf = lds_c2<T>();
     const int h = d.h, M = d.M, lbufp = d.lbufp;
@@ -1286,7 +1302,11 @@ __device__ inline void merge_to_lds(const RingDesc &d, const C2<T> *fourb, unsig
             const int m = mm[u];
             if (m < 0) continue;
             C2<T> y0 = ym[u], y1 = yh[u];
-            if (m == 0) y0 = {y0.x * y0_fac, T(0)};
+            if (m == 0) y0.y = T(0);
+            if (adjoint) {
+                if (m > 0) y0 = halved(y0);
+                y1 = halved(y1);
+            }
             merge_pair(y0, y1, pm[u]);
             if (d.blue) {
                 // the chirp at h - m is the chirp at m times (-1)^h (m > 0)
@@ -1326,18 +1346,17 @@ __global__ __launch_bounds__(kFftThreads, sizeof(T) == 4 ? 4 : 2) void k_fft_c2r
     const C2<T> *fourb = (const C2<T> *)a.in + d.four_off + f0;  // (m, f) at fourb[m nfld + f]
     T *gridb = (T *)a.out + (uint64_t)f0 * npts + d.grid_off;    // field f at gridb + f npts
     const unsigned mg_nf = div_magic(nf);
-    // the adjoint's Y_m = F_m / c_m: Y_0 doubled, the halves in the scale
-    const T y0_fac = a.adjoint ? T(2) : T(1);
-    const T scale = a.adjoint ? T(d.w / (4.0 * d.n)) : T(1);
+    const bool adjoint = a.adjoint != 0;
+    const T scale = adjoint ? T(d.w / (2.0 * d.n)) : T(1);
     const PassDesc *ps = a.passes + d.pass_off;
     if (d.fuse_in) {
         const FourSide<T> fs{lbufp, nf, h, M, nfld, mg_nf, (GlobalOut<T> *)fourb, (GlobalC2<T> *)post};
         const PassDesc pd = ps[0];
         radix_dispatch<kPassFromFour, sizeof(T) == 8>(pd.R, [&](auto r) __attribute__((always_inline)) {
-            pass_from_four<T, decltype(r)::value>(fs, pd, y0_fac);
+            pass_from_four<T, decltype(r)::value>(fs, pd, adjoint);
         });
     } else {
-        merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, y0_fac);
+        merge_to_lds<T>(d, fourb, nfld, nf, mg_nf, post, chirp, adjoint);
     }
     // forward DFT of length h; z = conj(DFT(u)): even samples Re z, odd samples Im z
     dft_passes<T, CAP>(d, ps, d.seam, d.fuse_in, d.nrad - d.fuse_out, nf, it.shape, tw);

@@ -72,6 +72,22 @@ def test_largest_sums(shape):
         assert er.max() < TOL_RMS["fp32"], (shape, k / 8, er.max())
 
 
+# A mean near the largest float: the adjoint of the direct transform scales it
+# down, and forms nothing larger on the way.
+@pytest.mark.parametrize("grid,nlat,nl", [("octahedral", 64, 0), ("full", 64, 122)])
+@pytest.mark.parametrize("nf", [1, F])
+def test_adjoint_of_largest_mean(grid, nlat, nl, nf):
+    shtx, o = _shtx(), _oracle()
+    n = 31
+    plan = shtx.Plan(n, grid, nlat, nf, "fp32", nlon_full=nl)
+    nlon = plan.ring_lengths()
+    a = np.zeros((nf, plan.nspec), np.complex64)
+    a[:, 0] = 3e38
+    got = _np(plan.dir_adj(_dev(a, plan.complex_dtype))).astype(np.float64)
+    ref = o.dir_adj(n, nlon, a.astype(np.complex128))
+    assert np.abs(got - ref).max() < 1e-5 * np.abs(ref).max()
+
+
 # Wavenumbers whose table entries are near the smallest float on the rings away
 # from the equator, with inputs of 2^30 that bring the results back into range:
 # entry by entry, on the rings of a field of those wavenumbers, and in the
