@@ -341,7 +341,7 @@ int shtx_plan_legendre(shtx_plan h, int m, double *out)
     const shtx::MBlock &b = p.mb[m];
     if (!out) return b.R;
     int K = p.trunc - m + 1;
-    const int np = shtx::table_pieces(p, false);
+    const shtx::TableLayout lay = shtx::table_layout(p, false);
     const size_t el = shtx::table_entry_bytes(p, false), cnt = 2 * (size_t)b.Rp * b.Kp;
     std::vector<unsigned char> tab(cnt * el);
     hipError_t e = hipMemcpy(tab.data(), (const char *)p.d_tab_dir + b.off * el, cnt * el, hipMemcpyDeviceToHost);
@@ -353,11 +353,15 @@ int shtx_plan_legendre(shtx_plan h, int m, double *out)
     };
     auto val = [&](int par, int r, int k) -> double {
         const size_t idx = ((size_t)par * b.Rp + r) * b.Kp + k;
-        if (!np) return p.prec == SHTX_FP64 ? reinterpret_cast<const double *>(tab.data())[idx]
+        if (lay == shtx::kTabPlain)
+            return p.prec == SHTX_FP64 ? reinterpret_cast<const double *>(tab.data())[idx]
                                             : reinterpret_cast<const float *>(tab.data())[idx];
+        const size_t unit = ((size_t)(r / 8) * b.Kp + k) * 8 + r % 8, plane = (size_t)b.Rp * b.Kp;
+        if (lay == shtx::kTabUnits)
+            return std::ldexp((double)reinterpret_cast<const float *>(tab.data())[par * plane + unit], -b.e);
         double v = 0.0;
-        for (int h = np - 1; h >= 0; --h)
-            v += piece((((size_t)(2 * h + par) * (b.Rp / 8) + r / 8) * b.Kp + k) * 8 + r % 8);
+        for (int h = shtx::split_pieces(p.prec) - 1; h >= 0; --h)
+            v += piece((size_t)(2 * h + par) * plane + unit);
         return std::ldexp(v, -b.e);
     };
     for (int r = 0; r < b.R; ++r)

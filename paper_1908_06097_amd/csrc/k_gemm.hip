@@ -418,7 +418,6 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
     const int row0 = it.tr * BM, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4, ncol = 2 * a.nfld;
-    const int col0 = it.tc * 16 * FN, f0 = it.tc * 8 * FN;
     const int64_t pstride = (int64_t)b.Kp * b.Rp;
     const int lda_g = INV ? b.Rp : b.Kp;
     const T *A0 = (const T *)a.tab + b.off + (int64_t)lk * lda_g + row0 + VEC * lr;
@@ -466,7 +465,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
                 const int nrel = 2 * (4 * s + lk);
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
-                    const int f = f0 + NF * j + (lr & (NF - 1));
+                    const int f = NF * j + (lr & (NF - 1));
                     const Vec2<T> *src = (const Vec2<T> *)a.in + (int64_t)f * a.nspec + sb + nrel;
                     Vec2<T> z0 = {T(0), T(0)}, z1 = {T(0), T(0)};
                     if (f < a.nfld && m + nrel + 1 <= a.trunc) {
@@ -491,7 +490,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             } else {
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
-                    const int c = col0 + 16 * j + lr;
+                    const int c = 16 * j + lr;
                     bv[u][0][j] = T(0);
                     bv[u][1][j] = T(0);
                     if (ro[u].n >= 0 && c < ncol) {
@@ -534,7 +533,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 #pragma unroll
         for (int q = 0; q < 2 * NP; ++q) {
             const int hs = q & 1, j = q >> 1;
-            if (f0 + NF * j >= a.nfld) break;
+            if (NF * j >= a.nfld) break;
             if (q) __syncthreads();
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -553,7 +552,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             __syncthreads();
 #pragma unroll
             for (int i = tid; i < BM * NF; i += 64 * NW) {
-                const int r = i / NF, fl = i % NF, f = f0 + NF * j + fl;
+                const int r = i / NF, fl = i % NF, f = NF * j + fl;
                 if (row0 + r >= b.R || f >= a.nfld) continue;
                 const RingPair o = a.ring_pair[b.j0 + row0 + r];
                 ((Vec2<T> *)a.out)[((int64_t)(hs ? o.s : o.n) + m) * a.nfld + f] =
@@ -564,7 +563,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
         // the waves' sums, 16 columns at a time: runs of n of one field
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            if (col0 + 16 * j >= ncol) break;
+            if (16 * j >= ncol) break;
             if (j) __syncthreads();
 #pragma unroll
             for (int p = 0; p < 2; ++p)
@@ -575,7 +574,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
             __syncthreads();
 #pragma unroll
             for (int i = tid; i < 2 * BM * 8; i += 64 * NW) {
-                const int fl = i / (2 * BM), nr = i % (2 * BM), f = f0 + 8 * j + fl, nrel = 2 * row0 + nr;
+                const int fl = i / (2 * BM), nr = i % (2 * BM), f = 8 * j + fl, nrel = 2 * row0 + nr;
                 if (f >= a.nfld || m + nrel > a.trunc) continue;
                 const T x = sum(nr & 1, nr >> 1, 2 * fl);
                 const T y = m == 0 ? T(0) : sum(nr & 1, nr >> 1, 2 * fl + 1);
@@ -596,12 +595,12 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 //                most, 2^-27 on average; FP32 rounds each sum to 2^-24)
 //   SHTX_BF16X3  bfloat16 hi + lo, three products (lo lo is dropped)
 //   SHTX_FP16X3  IEEE half hi + lo, three products
-// The table is stored in pieces, for the split forms scaled by 2^e_m per m, for
-// FP32 by 2^16 (its smallest entries in full); the data operand is cut into
-// pieces here, once per block and stage.  IEEE half has a 5-bit exponent, so
-// its data operand is also scaled per field by 2^E_f, chosen from a bound on
-// the field's largest value; bfloat16 has the FP32 exponent range and needs no
-// data scale.  A tile of the FP32 form that meets a smaller value than its
+// The split forms' table is stored in pieces, scaled by 2^e_m per m; FP32's as
+// floats, scaled by 2^16 (its smallest entries have whole pieces), which are cut
+// here like the data operand, once per block and stage.  IEEE half has a 5-bit
+// exponent, so its data operand is also scaled per field by 2^E_f, chosen from
+// a bound on the field's largest value; bfloat16 has the FP32 exponent range
+// and needs no data scale.  A tile of the FP32 form that meets a smaller value than its
 // pieces hold, one that is not finite, or a sum beyond 2^112 runs again on the
 // single-precision matrix cores: only there do such values keep 24 bits.  In
 // the split forms an infinite value gives NaN.
@@ -609,9 +608,10 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 // 32x32x16 MFMA: lane l supplies A[l%32][8(l/32)..+7] and B[8(l/32)..+7][l%32]
 // and holds D[8(v/4) + 4(l/32) + v%4][l%32], v = 0..15.  Both operands come in
 // units of 16 bytes, 8 consecutive kappa of one row: the table is laid out in
-// memory as planes [piece][parity][kappa / 8][row] of units, so a stage's
-// loads and LDS writes are runs of units (no transposition, no bank
-// conflicts), and LDS holds one 16-deep stage in the same order.
+// memory as planes [piece][parity][kappa / 8][row] of units (FP32: of 32-byte
+// units without pieces), so a stage's loads and LDS writes are runs of units
+// (no transposition, no bank conflicts), and LDS holds one 16-deep stage in
+// the same order.
 //
 // A block covers 64 FI rows and 32 FJ fields (64 FJ columns), both parities, in
 // four waves of 32 fields (real and imaginary parts: two column fragments) and
@@ -619,9 +619,12 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 // in flight over the MFMAs.
 //
 // O1280, 411 fields, against the kernels before (16x16x4 FP32 MFMA; split
-// operands re-staged by field): FP32 inverse 13.4 -> 9.8 ms, direct 13.6 -> 11.1;
-// BF16x3 8.3 -> 6.9 and 8.8 -> 7.8; T399, 137 fields, FP32 244 -> 177 and 285 ->
-// 227 us.  Of the FP32 inverse's 9.8 ms, found by leaving out one part at a
+// operands re-staged by field): FP32 inverse 13.4 -> 9.95 ms, direct 13.6 -> 11.6;
+// BF16x3 8.3 -> 6.9 and 8.8 -> 7.8; T399, 137 fields, FP32 244 -> 175 and 285 ->
+// 232 us; T2799 on 4200 x 8400 points, 120 fields, 35.8 -> 24.6 and 37.5 -> 29.4 ms.
+// (With the data cut instead of rounded to its first piece, no look for values
+// that pieces do not hold and the FP32 table in pieces: 9.7 and 10.95.)  Of the
+// FP32 inverse's 9.8 ms then, found by leaving out one part at a
 // time: MFMAs 2.7, operand loads 2.7, conversion and LDS stores 1.4, output and
 // block start 2.3 (8.1 GB written); the parts add up instead of overlapping
 // although two blocks share a CU, at a clock that falls to 2.0 GHz.
@@ -742,6 +745,7 @@ __device__ inline void quad_transpose(float *x, bool odd, bool upper)
 template <int FORM, int FI, int FJ, bool INV>
 __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArgs a)
 {
+    constexpr bool CUT = FORM == SHTX_FP32;  // table units of floats, cut on their way to LDS
     constexpr bool F16 = FORM == SHTX_FP16X3;
     constexpr int NP = split_pieces(FORM), BM = 64 * FI, BN = 64 * FJ, NF = 32 * FJ, BK = 16;
     constexpr int WR = 4 / FJ, NI = BM / (32 * WR);  // waves over the rows, row fragments per wave
@@ -753,7 +757,8 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     // values of 32 fields
     constexpr int NSTAGE = INV ? 0 : 32 * (2 * BM + 1) / 2;
     constexpr int NSMEM = PA + PB > NSTAGE ? PA + PB : NSTAGE;
-    constexpr int NA = NP * FI;  // units of A per thread
+    constexpr int NTP = CUT ? 2 : NP;  // 16-byte loads of a table unit: halves or pieces
+    constexpr int NA = NTP * FI;       // and of a stage's units, per thread
     __shared__ u32x4 smem[NSMEM];
     __shared__ int wave_lost[4];
     u32x4 *As = smem, *Bs = smem + PA;
@@ -770,8 +775,8 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     // the m block's table through a buffer descriptor: a unit's plane and row
     // are a scalar offset, the only vector address is the lane
     const int rows = INV ? b.Rp : b.Kp, chunks = (INV ? b.Kp : b.Rp) / 8;
-    const int64_t tab_units = (int64_t)NP * 2 * chunks * rows;
-    const auto tab = __builtin_amdgcn_make_buffer_rsrc((void *)((const u32x4 *)a.tab + b.off / 8 * NP), 0,
+    const int64_t tab_units = (int64_t)NTP * 2 * chunks * rows;
+    const auto tab = __builtin_amdgcn_make_buffer_rsrc((void *)((const u32x4 *)a.tab + b.off / 8 * NTP), 0,
                                                        (int)(tab_units * 16), 0x00027000);
     // This thread's share of B.  INV: a quad of lanes takes the 16 kappa of one
     // field, reading 64 contiguous bytes at a time, and transposes them so that
@@ -804,10 +809,11 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             // wave-loads of 64 rows: (plane, row half)
-            const int q = wave + 4 * i, half = q % FI, kc = q / FI & 1, pp = q / (2 * FI);
-            ra[i] = __builtin_bit_cast(
-                u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                           tab, 16 * lane, 16 * ((pp * chunks + kk / 8 + kc) * rows + row0 + 64 * half), 0));
+            const int q = wave + 4 * (CUT ? i / 2 : i), half = q % FI, kc = q / FI & 1, pp = q / (2 * FI);
+            const int unit = (pp * chunks + kk / 8 + kc) * rows + row0 + 64 * half;
+            ra[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  tab, CUT ? 32 * lane : 16 * lane,
+                                                  CUT ? 32 * unit + 16 * (i & 1) : 16 * unit, 0));
         }
         if (!bon) return;
         if constexpr (INV) {
@@ -855,8 +861,23 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                 split_pair<FORM>(x0, x1, w, least);
             }
         };
+        if constexpr (CUT) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) As[(wave + 4 * i) * 64 + lane] = ra[i];
+            for (int i = 0; i < FI; ++i) {
+                unsigned w[4][NP];
+                float any = 1.f;  // the scale leaves no entry that pieces would not hold
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    split_pair<FORM>(__uint_as_float(ra[2 * i + t / 2][2 * (t & 1)]),
+                                     __uint_as_float(ra[2 * i + t / 2][2 * (t & 1) + 1]), w[t], any);
+#pragma unroll
+                for (int h = 0; h < NP; ++h)
+                    As[h * 4 * UA + (wave + 4 * i) * 64 + lane] = u32x4{w[0][h], w[1][h], w[2][h], w[3][h]};
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) As[(wave + 4 * i) * 64 + lane] = ra[i];
+        }
         if (!bon) return;
         if constexpr (INV) {
             // kappa 4 i + q of lane q -> kappa 4 i .. + 3 of lane q's value
@@ -996,8 +1017,8 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     // A tile that met a value which is not the sum of its pieces (below 2^-110, or
     // not finite), or whose sums left the range that the table's scale leaves,
     // runs once more, as plain single-precision products on the FP32 matrix
-    // cores (the table's pieces are exact; 1/5 of the rate, but no ordinary
-    // field comes here).  All four waves go or none.
+    // cores (the table's entries are the sums of their pieces; 1/5 of the rate,
+    // but no ordinary field comes here).  All four waves go or none.
     float unit = FORM == SHTX_FP32 ? 1.f / kF32TableScale : 1.f;
     fold(unit);
     if constexpr (FORM == SHTX_FP32) {
@@ -1307,13 +1328,9 @@ bool gemm_tile_supported(int prec, int bm, int bn)
 // 150 / 206 at 16 fields but 360 / 280 at 24, direct 152 / 252 at 16 and 247 /
 // 319 at 32 (its operand loads are fewer), FP64 227 / 240 at 8 and 393 / 308
 // at 12.
-int gemm_narrow(int prec, int nfld, bool inverse, int64_t tab_elems)
+int gemm_narrow(int prec, int nfld, bool inverse)
 {
     const int ncol = 2 * nfld;
-    // any field count, 16 fields at a time, where the three pieces of both
-    // layouts (12 bytes an entry, against 8 for plain values) would take more
-    // than a third of the memory (truncations above about 2700)
-    if (prec == SHTX_FP32 && ncol > 32 && 12 * tab_elems > (int64_t)96 << 30) return 2;
     if (ncol <= 16 && (prec == SHTX_FP32 || prec == SHTX_FP64)) return 1;
     if (ncol <= 32 && prec == SHTX_FP32) return 2;
     if (ncol <= 64 && prec == SHTX_FP32 && !inverse) return 4;
@@ -1327,7 +1344,8 @@ bool gemm_shapes_ok(const Plan &p)
         return false;
     // each direction's list is for its tiles, or for the few-fields kernel's
     auto dir_ok = [&](const std::vector<GemmItem> &items, bool inverse, int narrow, int bm, int bn) {
-        return narrow ? check_work_list(p, items, inverse, kNarrowRows, 16 * narrow, 4)
+        // (one column tile holds all of that kernel's columns)
+        return narrow ? 2 * p.nfld <= 16 * narrow && check_work_list(p, items, inverse, kNarrowRows, 16 * narrow, 4)
                       : check_work_list(p, items, inverse, bm, bn, bk);
     };
     return (p.inv_items.empty() || dir_ok(p.inv_items, true, p.inv_narrow, p.inv_bm, p.inv_bn)) &&

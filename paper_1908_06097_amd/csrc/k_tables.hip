@@ -206,14 +206,13 @@ __device__ inline void table_split(double v, unsigned short *w)
 
 // Column recurrence over n for one (m, ring).  MODE 0: per-m max |P̄| only (the
 // split forms' exponents).  MODE 1: store, in the forms of the plan's
-// precision: plain values of type T as tab_inv = [p][k][r] and tab_dir =
-// [p][r][k] (k = (n - m - p) / 2), or with INV_UNITS / DIR_UNITS 16-bit pieces
-// [piece][p][k / 8][r][k % 8] and [piece][p][r / 8][k][r % 8].  The split forms'
+// precision (k = (n - m - p) / 2), laid out as INV_LAY and DIR_LAY say
+// (TableLayout), units scaled by kF32TableScale.  The split forms'
 // pieces are scaled by 2^e_m: BF16x3 puts the block's largest entry in [1/2, 1);
 // FP16x3 in [2^13, 2^14) (half's 5-bit exponent: entries that small relative
 // to the block's largest lose their lo half to the subnormal range, a loss
 // relative to that largest entry of at most 2^-38).
-template <int PREC, int MODE, bool INV_UNITS, bool DIR_UNITS>
+template <int PREC, int MODE, TableLayout INV_LAY, TableLayout DIR_LAY>
 __global__ void k_legendre_table(int trunc, const double *mu, const double *diag, const int *diag_e, MBlock *mbs,
                                  unsigned long long *mmax, void *tab_inv, void *tab_dir)
 {
@@ -234,7 +233,7 @@ __global__ void k_legendre_table(int trunc, const double *mu, const double *diag
     if (r >= b.R) return;
     const int j = b.j0 + r;
     const double x = mu[j];
-    double scale = 1.0;
+    double scale = PREC == SHTX_FP32 ? (double)kF32TableScale : 1.0;
     if (SCALED) {
         double mx = __longlong_as_double((long long)mmax[m]);
         int E = 0;
@@ -250,20 +249,25 @@ __global__ void k_legendre_table(int trunc, const double *mu, const double *diag
         const int t = n - m, par = t & 1, k = t >> 1;
         const int64_t blk = 2 * (int64_t)b.Kp * b.Rp;  // entries of the block, and of each piece
         unsigned short w[NP];
-        if (INV_UNITS || DIR_UNITS) table_split<PREC>(v * (PREC == SHTX_FP32 ? (double)kF32TableScale : scale), w);
-        if (INV_UNITS) {
+        const double vs = v * scale;
+        if (INV_LAY == kTabPieces || DIR_LAY == kTabPieces) table_split<PREC>(vs, w);
+        const int64_t ui = (((int64_t)par * (b.Kp / 8) + k / 8) * b.Rp + r) * 8 + k % 8;
+        const int64_t ud = (((int64_t)par * (b.Rp / 8) + r / 8) * b.Kp + k) * 8 + r % 8;
+        if (INV_LAY == kTabPieces) {
             unsigned short *dst = (unsigned short *)tab_inv + NP * b.off;
 #pragma unroll
-            for (int h = 0; h < NP; ++h)
-                dst[h * blk + (((int64_t)par * (b.Kp / 8) + k / 8) * b.Rp + r) * 8 + k % 8] = w[h];
+            for (int h = 0; h < NP; ++h) dst[h * blk + ui] = w[h];
+        } else if (INV_LAY == kTabUnits) {
+            ((T *)tab_inv)[b.off + ui] = (T)vs;
         } else {
             ((T *)tab_inv)[b.off + ((int64_t)par * b.Kp + k) * b.Rp + r] = (T)v;
         }
-        if (DIR_UNITS) {
+        if (DIR_LAY == kTabPieces) {
             unsigned short *dst = (unsigned short *)tab_dir + NP * b.off;
 #pragma unroll
-            for (int h = 0; h < NP; ++h)
-                dst[h * blk + (((int64_t)par * (b.Rp / 8) + r / 8) * b.Kp + k) * 8 + r % 8] = w[h];
+            for (int h = 0; h < NP; ++h) dst[h * blk + ud] = w[h];
+        } else if (DIR_LAY == kTabUnits) {
+            ((T *)tab_dir)[b.off + ud] = (T)vs;
         } else {
             ((T *)tab_dir)[b.off + ((int64_t)par * b.Rp + r) * b.Kp + k] = (T)v;
         }
@@ -325,22 +329,23 @@ hipError_t launch_legendre_tables(Plan &p, hipStream_t s)
         kern<<<grid, 128, 0, s>>>(N, p.d_mu, p.d_diag, p.d_diag_e, p.d_mb, p.d_mmax, p.d_tab_inv, p.d_tab_dir);
     };
     if (split_form(p.prec)) {
-        store(k_legendre_table<SHTX_FP64, 0, false, false>);
+        store(k_legendre_table<SHTX_FP64, 0, kTabPlain, kTabPlain>);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (p.prec == SHTX_FP64)
-        store(k_legendre_table<SHTX_FP64, 1, false, false>);
-    else if (p.prec == SHTX_BF16X3)
-        store(k_legendre_table<SHTX_BF16X3, 1, true, true>);
-    else if (p.prec == SHTX_FP16X3)
-        store(k_legendre_table<SHTX_FP16X3, 1, true, true>);
-    else if (p.inv_narrow && p.dir_narrow)
-        store(k_legendre_table<SHTX_FP32, 1, false, false>);
-    else if (p.dir_narrow)
-        store(k_legendre_table<SHTX_FP32, 1, true, false>);
-    else
-        store(k_legendre_table<SHTX_FP32, 1, true, true>);
-    return hipGetLastError();
+    const TableLayout li = table_layout(p, true), ld = table_layout(p, false);
+#define SHTX_TABLE(PREC, LI, LD)                             \
+    if (p.prec == PREC && li == LI && ld == LD) {            \
+        store(k_legendre_table<PREC, 1, LI, LD>);            \
+        return hipGetLastError();                            \
+    }
+    SHTX_TABLE(SHTX_FP64, kTabPlain, kTabPlain)
+    SHTX_TABLE(SHTX_BF16X3, kTabPieces, kTabPieces)
+    SHTX_TABLE(SHTX_FP16X3, kTabPieces, kTabPieces)
+    SHTX_TABLE(SHTX_FP32, kTabPlain, kTabPlain)
+    SHTX_TABLE(SHTX_FP32, kTabUnits, kTabPlain)
+    SHTX_TABLE(SHTX_FP32, kTabUnits, kTabUnits)
+#undef SHTX_TABLE
+    return hipErrorInvalidValue;
 }
 
 }  // namespace shtx

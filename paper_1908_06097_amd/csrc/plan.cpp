@@ -603,8 +603,8 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
     p.tab_elems = off;
     p.legendre_flops = flops;
 
-    p.inv_narrow = gemm_narrow(prec, F, true, off);
-    p.dir_narrow = gemm_narrow(prec, F, false, off);
+    p.inv_narrow = gemm_narrow(prec, F, true);
+    p.dir_narrow = gemm_narrow(prec, F, false);
     p.table_bytes = (table_entry_bytes(p, true) + table_entry_bytes(p, false)) * p.tab_elems;
 
     // ---- ring FFT plans and twiddle pool --------------------------------------

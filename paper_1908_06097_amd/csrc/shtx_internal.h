@@ -152,7 +152,7 @@ struct MBlock {
     int j0;         // first such ring
     int K0, K1;     // number of n = m + p + 2k <= N for parity p = 0, 1
     int Rp, Kp;     // padded ring and parity-k extents
-    int e;          // power-of-two exponent applied to the stored table pieces
+    int e;          // power-of-two exponent applied to the stored pieces or units
     int pad_;
     int64_t off;    // entries of the m blocks before this one (2 Kp Rp each)
 };
@@ -220,10 +220,10 @@ constexpr int kKinds = 5;
 
 // The split-precision forms: hi + lo halves of bfloat16 or IEEE half.
 inline bool split_form(int prec) { return prec == SHTX_BF16X3 || prec == SHTX_FP16X3; }
-// 16-bit pieces of a table entry in the half-precision matrix-core GEMM (FP32:
-// three bfloat16).
+// 16-bit pieces of an operand in the half-precision matrix-core GEMM (FP32: three
+// bfloat16).
 __host__ __device__ constexpr int split_pieces(int prec) { return prec == SHTX_FP32 ? 3 : 2; }
-// Scale of a single-precision plan's table pieces: the last bit of the smallest
+// Scale of a single-precision plan's table units: the last bit of the smallest
 // normal float, 2^-149, times 2^16 is bfloat16's smallest value.
 constexpr int kF32TableExp = 16;
 constexpr float kF32TableScale = 65536.f;
@@ -261,10 +261,7 @@ struct Plan {
     double *d_mu = nullptr, *d_w = nullptr;  // nlat
     double *d_diag = nullptr;                // [NL][N+1] sectoral seeds q (plan time only) ...
     int *d_diag_e = nullptr;                 // ... and their exponents E: P̄_m^m = q 2^E
-    // Legendre tables of the inverse- and the direct-shaped GEMM, per m block:
-    // plain values [p][k][r] and [p][r][k] where a kernel of the plan's own
-    // precision reads them (FP64, few fields), else 16-bit pieces
-    // [piece][p][k / 8][r][k % 8] and [piece][p][r / 8][k][r % 8].
+    // Legendre tables of the inverse- and the direct-shaped GEMM (TableLayout).
     void *d_tab_inv = nullptr, *d_tab_dir = nullptr;
     unsigned long long *d_mmax = nullptr;                  // per-m max |P̄| bits (plan time)
     MBlock *d_mb = nullptr;
@@ -346,16 +343,26 @@ void gemm_tiles(int prec, int trunc, int nfld, int *inv_bm, int *inv_bn, int *di
 bool gemm_tile_supported(int prec, int bm, int bn);
 // Few fields: column fragments of the kernel that serves them, whatever the
 // tile shapes are (0: the tiled kernels do), and its row tile.
-int gemm_narrow(int prec, int nfld, bool inverse, int64_t tab_elems);
-// 16-bit pieces of a plan's table entries in one direction, 0: plain values.
-inline int table_pieces(const Plan &p, bool inverse)
+int gemm_narrow(int prec, int nfld, bool inverse);
+// How a direction's table is laid out, per m block (inverse | direct):
+//   kTabPlain   values of the plan's precision [p][k][r] | [p][r][k], where a
+//               kernel of that precision reads them (FP64, few fields)
+//   kTabPieces  the split forms: 16-bit pieces [piece][p][k / 8][r][k % 8] |
+//               [piece][p][r / 8][k][r % 8]
+//   kTabUnits   single precision: floats, times kF32TableScale, in the same order,
+//               [p][k / 8][r][k % 8] | [p][r / 8][k][r % 8]; the GEMM cuts them
+//               into pieces (stored in pieces they take half as much memory
+//               again and gain 2 to 4 % of the direct GEMM, T1279 11.3 against
+//               11.6 ms, and nothing of the inverse)
+enum TableLayout { kTabPlain, kTabPieces, kTabUnits };
+inline TableLayout table_layout(const Plan &p, bool inverse)
 {
-    return p.prec == SHTX_FP64 || (inverse ? p.inv_narrow : p.dir_narrow) ? 0 : split_pieces(p.prec);
+    if (p.prec == SHTX_FP64 || (inverse ? p.inv_narrow : p.dir_narrow)) return kTabPlain;
+    return p.prec == SHTX_FP32 ? kTabUnits : kTabPieces;
 }
 inline size_t table_entry_bytes(const Plan &p, bool inverse)
 {
-    const int np = table_pieces(p, inverse);
-    return np ? 2 * np : p.prec == SHTX_FP64 ? 8 : 4;
+    return table_layout(p, inverse) == kTabPieces ? 2 * split_pieces(p.prec) : p.prec == SHTX_FP64 ? 8 : 4;
 }
 constexpr int kNarrowRows = 64;
 // Candidate shapes the autotuner times (count returned, shapes in bm[], bn[]).
