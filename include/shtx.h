@@ -142,7 +142,7 @@ int shtx_plan_check(int trunc, int grid, int nlat, int nlon_full, int nfld, int 
  * SHTX_EUNSUPPORTED; fft_cap out of range is SHTX_EINVAL.  Plans of few fields
  * (FP32: up to 16, the direct-shaped launch up to 32; FP64: up to 8) run a
  * kernel of their own, which has no tile shapes: theirs are kept and reported
- * but change nothing. */
+ * but change nothing, and autotuning does not time them. */
 int shtx_plan_check_shapes(int trunc, int grid, int nlat, int nlon_full, int nfld, int prec, int inv_bm,
                            int inv_bn, int dir_bm, int dir_bn, int fft_cap, shtx_info *out);
 

@@ -156,10 +156,21 @@ int autotune_plan(Plan &p, hipStream_t s)
         int cbm[8], cbn[8];
         const int nc = gemm_tile_candidates(p.prec, cbm, cbn, 8);
         double bi = 1e300, bd = 1e300;
+        // a direction of few fields runs a kernel without tile shapes: it keeps
+        // the default ones, untimed
+        if (p.inv_narrow) {
+            best.inv_bm = p.inv_bm;
+            best.inv_bn = p.inv_bn;
+        }
+        if (p.dir_narrow) {
+            best.dir_bm = p.dir_bm;
+            best.dir_bn = p.dir_bn;
+        }
+        const bool tiled = !p.inv_narrow || !p.dir_narrow;
         // inverse-shaped and direct-shaped launches are tuned independently;
         // the candidates are timed twice, in forward then reverse order, and
         // each keeps its faster median (clock drift favours neither end)
-        for (int cc = 0; cc < 2 * nc && rc == SHTX_OK; ++cc) {
+        for (int cc = 0; tiled && cc < 2 * nc && rc == SHTX_OK; ++cc) {
             const int c = cc < nc ? cc : 2 * nc - 1 - cc;
             int arc = apply_shapes(p, cbm[c], cbn[c], cbm[c], cbn[c], p.fft_cap);
             if (arc == SHTX_EINVAL || arc == SHTX_EUNSUPPORTED) continue;
@@ -167,8 +178,11 @@ int autotune_plan(Plan &p, hipStream_t s)
                 fail(arc);
                 break;
             }
-            double ti = time_ms(s, ea, eb, reps, [&] { return launch_gemm_inverse(p, spec, p.d_four, p.d_fmax, s); });
-            double td = time_ms(s, ea, eb, reps, [&] { return launch_gemm_direct(p, p.d_four, spec, false, p.d_fmax, s); });
+            double ti = -1.0, td = -1.0;
+            if (!p.inv_narrow)
+                ti = time_ms(s, ea, eb, reps, [&] { return launch_gemm_inverse(p, spec, p.d_four, p.d_fmax, s); });
+            if (!p.dir_narrow)
+                td = time_ms(s, ea, eb, reps, [&] { return launch_gemm_direct(p, p.d_four, spec, false, p.d_fmax, s); });
             if (std::getenv("SHTX_DEBUG"))
                 std::fprintf(stderr, "shtx tune: GEMM %dx%d inverse %.3f ms direct %.3f ms\n", cbm[c], cbn[c], ti, td);
             if (ti >= 0 && ti < bi) {

@@ -79,3 +79,24 @@ def test_autotune_and_cache(tmp_path):
         assert len(cache.read_text().strip().splitlines()) == 1
     finally:
         del os.environ["SHTX_TUNE_CACHE"]
+
+
+# Directions of few fields have no tile shapes: nothing is timed for them, and
+# they keep the default ones (8 FP32 fields in both directions, 20 in the
+# direct one, 8 FP64 fields in both).
+@pytest.mark.parametrize("prec,F,inv,dirn", [("fp32", 8, False, False), ("fp32", 20, True, False),
+                                             ("fp32", 40, True, True), ("fp64", 8, False, False)])
+def test_autotune_times_only_tiled_directions(tmp_path, monkeypatch, prec, F, inv, dirn):
+    shtx = _shtx()
+    cache = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("SHTX_TUNE_CACHE", str(cache))
+    ref = shtx.Plan(63, "octahedral", 128, F, prec)
+    tuned = shtx.Plan(63, "octahedral", 128, F, prec, autotune=True)
+    rec = json.loads(cache.read_text())
+    assert (rec["inv_ms"] > 0) == inv and (rec["dir_ms"] > 0) == dirn and rec["fft_ms"] > 0
+    for timed, field in ((inv, "inv_tile"), (dirn, "dir_tile")):
+        t = tuple(getattr(tuned.info, field))
+        assert t in SHAPES[prec] and (timed or t == tuple(getattr(ref.info, field)))
+    _check_all(tuned, 63, tuned.ring_lengths(), 31, range(F), prec)
+    again = shtx.Plan(63, "octahedral", 128, F, prec, autotune=True)
+    assert again.info.tuned == 2 and tuple(again.info.inv_tile) == tuple(tuned.info.inv_tile)
