@@ -53,18 +53,20 @@ enum FftPassKind {
 // Radices with a butterfly of each kind.  The Fourier-side passes hold a pair of
 // butterflies (j and its mirror) per thread, so their radices stop earlier;
 // FP64 values take twice the registers.  The sets end where the butterfly would
-// spill at the two blocks (FP64: one) per CU that the LDS allows.
+// spill at the two blocks (FP64: one) per CU that the LDS allows, and hold no
+// radix that no ring's cheapest passes have.
 __host__ __device__ constexpr bool fft_radix_ok(int kind, bool dbl, int R)
 {
     if (R < 2) return false;
     switch (kind) {
     case kPassLds: return R <= 13 || R == 16 || R == 17 || (!dbl && (R == 18 || R == 19 || R == 23));
-    case kPassFromGrid: return R <= 13 || R == 16 || (!dbl && (R == 15 || R == 17 || R == 18));
-    case kPassFromFour: return R <= (dbl ? 9 : 10);
+    case kPassFromGrid: return (R <= 13 && R > (dbl ? 2 : 1)) || R == 16 || (!dbl && (R == 15 || R == 17 || R == 18));
+    case kPassFromFour: return dbl ? R > 2 && R <= 9 : R <= 10;
     case kPassToGrid: return R <= 10 || R == 12 || R == 16 || (!dbl && (R == 14 || R == 15 || R == 18 || R == 20));
     case kPassToFour: return R <= 6 || R == 8 || (!dbl && (R == 7 || R == 9));
     case kPassSeam: return R == 9 || R == 10 || (dbl ? R == 12 : R == 15 || R == 18);
-    case kPassGather: case kPassSub: return R <= 19 || R == 23;
+    case kPassGather: return (R > 2 && R <= 19) || R == 23;
+    case kPassSub: return R <= 19 || R == 23;
     case kPassScatter: return R <= 11 || (R >= 13 && R <= 17) || R == 19;
     case kPassSubSeam:
         return R == 4 || R == 6 || R == 8 || R == 9 || R == 10 || (R >= 14 && R <= 16) || (!dbl && (R == 12 || R == 18));

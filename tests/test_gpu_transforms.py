@@ -168,6 +168,9 @@ def test_transform_parity(prec, shape):
 # primes, a small prime with a large smooth cofactor, and odd half lengths
 # (h = 211, a single prime butterfly; h = 1021, Bluestein), where the chirp at
 # h - m is minus the chirp at m.
+# (Which kind a length takes moves with the plan's cost model, here and in the
+# ring tests below: that every kernel is reached is test_ring_kernels.py's
+# part, which asks the planner.)
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("nlon", [844, 1604, 2452, 3596, 4084, 5180, 422, 2042])
 def test_ring_kinds_parity(prec, nlon):
@@ -268,6 +271,8 @@ def test_prime_pass_shapes_parity(prec, F):
 # Legendre GEMM column tiling: 128 columns exactly (64 fields), a last tile at
 # most half used (70 fields: covered by the 64-column tail launch) and one
 # more than half used (100 fields: no tail).
+# (A last tile at most half used is a 128- or 64-column tile like the others; the
+# tail launch is gone.)
 @pytest.mark.parametrize("F", [64, 70, 100])
 def test_gemm_column_tiles_fp32(F):
     shtx = _shtx()
