@@ -148,7 +148,6 @@ __host__ __device__ constexpr int pfa_factor(int R)
     return R == 6 || R == 10 || R == 14 || R == 18 ? 2
            : R == 12 || R == 20                   ? 4
            : R == 15                              ? 3
-           : R == 24                              ? 8
                                                   : 0;
 }
 
@@ -321,7 +320,7 @@ __device__ inline PassDesc uniform(PassDesc d)
 
 // The table reads behind the twiddle powers of one butterfly: w = W[t1]
 // (w = exp(-2 pi i k / (Ns R))) and, for radix 9, w^3, for the radices from
-// 10 to 24, w^4.
+// 10 to 20, w^4.
 template <int R>
 constexpr int twiddle_step2() { return R == 9 ? 3 : R >= 10 && R != 23 ? 4 : 0; }
 
@@ -346,7 +345,6 @@ __device__ inline void twiddle_powers(C2<T> *tw, C2<T> w1, C2<T> w2nd)
         tw[8] = cmul(w2nd, w2nd);
         if constexpr (R > 12) tw[12] = cmul(w2nd, tw[8]);
         if constexpr (R > 16) tw[16] = cmul(tw[8], tw[8]);
-        if constexpr (R > 20) tw[20] = cmul(tw[16], w2nd);
 #pragma unroll
         for (int a = 4; a < R; a += 4)
 #pragma unroll
@@ -1005,7 +1003,7 @@ __device__ inline void str(unsigned a, T v)
 struct GpGeom {
     int p, H, mt, nb, nbf;
     unsigned mg_nbf;
-    int buf_off, lbufp, ksteps;
+    int lbufp, ksteps;
     unsigned rb, rstr, rspan, rstep, lb;
     int lr, lk;
 };
@@ -1037,7 +1035,7 @@ __device__ __attribute__((always_inline)) inline void gp_run(const GpGeom &g, in
         const int c = 16 * (g0 + j) + g.lr;
         const int b = min(c >> 1, g.nb - 1);
         const int f = udiv(b, g.mg_nbf), jj = b - f * g.nbf;
-        const unsigned slot = g.lb + (unsigned)(g.buf_off + f * g.lbufp + jj) * CB + (unsigned)(c & 1) * RB;
+        const unsigned slot = g.lb + (unsigned)(f * g.lbufp + jj) * CB + (unsigned)(c & 1) * RB;
         ar[j] = slot + (unsigned)(1 + g.lk) * g.nbf * CB;
         am[j] = slot + (unsigned)(g.p - 1 - g.lk) * g.nbf * CB;
         x0[j] = lda<T>(slot);
@@ -1114,7 +1112,7 @@ __device__ __attribute__((noinline)) void gp_pass(int lbufp, int nf, PassDesc pd
     V4 accp[NI][NJ], accq[NI][NJ];
     T x0[NJ];
     // 2. the wave's row tiles i0 .. and column tiles g0 ..
-    const GpGeom gm{p, H, mt, nb, nbf, pd.mg_nbf, 0, lbufp, ksteps, rb, rstr, rspan, rstep, lb, lr, lk};
+    const GpGeom gm{p, H, mt, nb, nbf, pd.mg_nbf, lbufp, ksteps, rb, rstr, rspan, rstep, lb, lr, lk};
     const int mi = (mt + NI - 1) / NI, i0 = wave % mi * NI, g0 = wave / mi * NJ;
     if (g0 < ct) gp_run<T, NI, NJ>(gm, i0, g0, accp, accq, x0);
     __syncthreads();
@@ -1188,7 +1186,6 @@ __device__ inline void radix_dispatch(int R, Fn fn)
         SHTX_RADIX(19)
         SHTX_RADIX(20)
         SHTX_RADIX(23)
-        SHTX_RADIX(24)
     }
 #undef SHTX_RADIX
 }
@@ -1643,7 +1640,7 @@ bool check_fft(const Plan &p, int cap)
                 if (pd.Ns != prod || pd.nbf * R != d.L || pd.tstep * prod * R != d.L) SHTX_FFT_FAIL;
                 if (pd.mg_nbf != div_magic(pd.nbf) || pd.mg_ns != div_magic(pd.Ns)) SHTX_FFT_FAIL;
                 // twiddle reads W[c k tstep], k < Ns: c = 1, and 3 for radix 9, 4 for
-                // 10 to 24, 17 for the streamed radix 23
+                // 10 to 20, 17 for the streamed radix 23
                 const int cmax = R == 23 ? 17 : R == 9 ? 3 : R >= 10 ? 4 : 1;
                 if (prod > 1 && (int64_t)cmax * (prod - 1) * pd.tstep >= d.L) SHTX_FFT_FAIL;
                 prod *= R;

@@ -159,8 +159,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leg_mfma(GemmArgs a)
 #pragma unroll
         for (int v = 0; v < NM; ++v) {
             int r = kk + (tid + v * NT) / (BN / 2);
-            // with 64 fields per tile a wave's ring is uniform: scalar loads
-            if constexpr (BN / 2 == 64) r = __builtin_amdgcn_readfirstlane(r);
             RingPair o = {-1, -1};
             T w = T(0);
             if (r < b.R) {
@@ -307,18 +305,14 @@ __global__ __launch_bounds__(64 * NW, 2) void k_leg_mfma(GemmArgs a)
             __syncthreads();
         }
     };
-    static_assert(FM >= 1 && FM <= 4, "one to four row fragments per wave");
+    static_assert(FM == 1 || FM == 2, "one or two row fragments per wave");
     // the inverse's ragged rows are few (2 % of its MFMAs against 6 % in the
     // direct): whole waves only, which keeps its registers within the two
     // blocks per CU
     if (nfa == FM || (INV && nfa > 0))
         kloop(std::integral_constant<int, FM>{});
-    else if (!INV && FM >= 4 && nfa == 3)
-        kloop(std::integral_constant<int, (FM >= 4 ? 3 : 0)>{});
-    else if (!INV && FM >= 3 && nfa == 2)
-        kloop(std::integral_constant<int, (FM >= 3 ? 2 : 0)>{});
-    else if (!INV && FM >= 2 && nfa == 1)
-        kloop(std::integral_constant<int, (FM >= 2 ? 1 : 0)>{});
+    else if (!INV && nfa == 1)
+        kloop(std::integral_constant<int, 1>{});
     else
         kloop(std::integral_constant<int, 0>{});
 

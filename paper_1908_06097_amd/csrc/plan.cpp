@@ -69,7 +69,6 @@ double butterfly_cost(int R)
     case 18: return 2 + butterfly_cost(9);
     case 12: case 20: return 4 + butterfly_cost(R / 4);
     case 15: return butterfly_cost(3) + butterfly_cost(5);
-    case 24: return butterfly_cost(8) + butterfly_cost(3);
     }
     const double H = (R - 1) / 2;  // odd primes, inputs paired
     return (4 * H * H + 10 * H) / R;
@@ -135,7 +134,7 @@ PassPlan order_passes(int L, int Ns0, int Ns1, int kin, int kout, int fields, bo
         const int left = Ns1 / Ns;
         // no pass costs less than 7 log2(R), 8 of them its writes and 8 its twiddles
         if (cost + std::max(10.0, 7.0 * std::log2(left) - (Ns == 1 ? 16 : 8)) >= best.cost) return;
-        for (int R = 24; R >= 2; --R) {
+        for (int R = kTopRadix; R >= 2; --R) {
             if (left % R) continue;
             const int nbf = L / R;
             const bool last = left == R;
@@ -193,7 +192,7 @@ PassPlan bluestein_passes(int L, bool r2c, bool dbl)
 {
     PassPlan best;
     const int cap = dbl ? kFftCapF64 : kFftCapF32, fields = std::max(1, cap / L);
-    for (int J = 24; J >= 2; --J) {
+    for (int J = kTopRadix; J >= 2; --J) {
         if (L % J || L == J || !fft_radix_ok(kPassSeam, dbl, J) || L / J > fft_rounds(cap, J) * kFftThreads) continue;
         const double seam = idle_factor(L / J * fields) * (pass_cost(J, 2, L / J, true) + butterfly_cost(J) + 8 +
                                                            3 * (write_conflicts(J, 1, L / J) - 1));
@@ -225,7 +224,7 @@ PassPlan conv_passes(int p, int per, int fields, bool dbl)
         return fft_radix_ok(kind, dbl, R) && fields * per * (P / R) <= fft_rounds(cap, R) * kFftThreads;
     };
     auto cost = [&](int R, int Ns) { return idle_factor(fields * per * (P / R)) * pass_cost(R, Ns, P / R, true); };
-    for (int J = 24; J >= 2; --J) {
+    for (int J = kTopRadix; J >= 2; --J) {
         if (P % J || !fits(kPassSubSeam, J)) continue;
         const double seam = cost(J, 2) + idle_factor(fields * per * (P / J)) * (butterfly_cost(J) + 8);
         // the other factor in one to three passes, those of the second FFT
@@ -234,7 +233,7 @@ PassPlan conv_passes(int p, int per, int fields, bool dbl)
         for (int out = 0; out < 2; ++out) {
             std::vector<int> cur;
             auto go = [&](auto &&self, int left, int Ns, double c) -> void {
-                for (int R = 24; R >= 2; --R) {
+                for (int R = kTopRadix; R >= 2; --R) {
                     if (left % R) continue;
                     const int kind = out ? (left == R ? kPassScatter : kPassSub) : (cur.empty() ? kPassGather : kPassSub);
                     if (!fits(kind, R)) continue;

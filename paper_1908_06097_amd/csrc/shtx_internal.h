@@ -50,6 +50,8 @@ enum FftPassKind {
     kPassScatter = 9
 };
 
+constexpr int kTopRadix = 23;  // of any kind
+
 // Radices with a butterfly of each kind.  The Fourier-side passes hold a pair of
 // butterflies (j and its mirror) per thread, so their radices stop earlier;
 // FP64 values take twice the registers.  The sets end where the butterfly would
@@ -146,7 +148,7 @@ inline int gp_fields(int p, int h, int fb)
 }
 constexpr int kMaxRadices = 12;
 // Primes above the register butterflies run as general prime passes.
-__host__ __device__ constexpr bool gp_radix(int R, bool dbl) { return R > 24 || (dbl && (R == 19 || R == 23)); }
+__host__ __device__ constexpr bool gp_radix(int R, bool dbl) { return R > kTopRadix || (dbl && (R == 19 || R == 23)); }
 
 // One m block of the Legendre tables.
 struct MBlock {
