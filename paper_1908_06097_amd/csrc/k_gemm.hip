@@ -793,7 +793,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     RingPair mp = {0, 0};
     float mq = 0.f, q1[8];
     auto meta = [&](int kk) __attribute__((always_inline)) {
-        // past the last ring: repeated (with weight 0 when taken); nothing here
+        // past the last ring: repeated (the table's padding is zero); nothing here
         // may wait for these loads, which would wait for the operands' too
         const int j = b.j0 + min(kk + 8 * kh + (lane & 7), b.R - 1);
         mp = a.ring_pair[j];
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
                 rn[q] = (four + 2 * ((int64_t)on + m) * a.nfld)[c];
                 rs[q] = (four + 2 * ((int64_t)os + m) * a.nfld)[c];
                 const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mq), q));
-                q1[q] = kk + 8 * kh + q >= b.R ? 0.f : a.adjoint ? 1.f : w;
+                q1[q] = a.adjoint ? 1.f : w;
             }
         }
     };
@@ -1016,8 +1016,9 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
     float unit = FORM == SHTX_FP32 ? 1.f / kF32TableScale : 1.f;
     fold(unit);
     if constexpr (FORM == SHTX_FP32) {
-        // (an inverse tile's northern sums alone: they are finite only if both
-        // parities' are)
+        // the sum of all is finite only if each is (an inverse tile's northern
+        // sums alone: they are finite only if both parities' are)
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < (INV ? 1 : 2); ++p)
 #pragma unroll
@@ -1025,8 +1026,8 @@ __global__ __launch_bounds__(256, FI * FJ == 4 ? 2 : 3) void k_leg_split(GemmArg
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        lost |= __builtin_amdgcn_ballot_w64(!__builtin_isfinite(acc[p][i][j][v]));
+                    for (int v = 0; v < 16; ++v) sum[v & 3] += acc[p][i][j][v];
+        lost |= __builtin_amdgcn_ballot_w64(!__builtin_isfinite((sum[0] + sum[1]) + (sum[2] + sum[3])));
         if (lane == 0) wave_lost[wave] = lost != 0;
         __syncthreads();
         if (__builtin_expect(wave_lost[0] | wave_lost[1] | wave_lost[2] | wave_lost[3], 0)) {
