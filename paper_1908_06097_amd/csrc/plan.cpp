@@ -426,29 +426,77 @@ void free_plan(Plan &p)
         }                                                \
     } while (0)
 
-// Time of one field of a ring in picoseconds, fitted to single-precision
-// timings of 64 equal rings of 320 to 5136 points, 411 fields, on MI355X
-// (double precision takes about twice as long throughout): a ring without
-// large primes 2.05 ps per grid point; a prime pass (p, nf fields per block) on
-// top of 2.4 by its units, 16 p cycles each; a prime pass by convolution 1.9
-// and 0.0098 by its passes' instructions per value (conv_passes); Bluestein
-// 0.0160 L / h by its passes' (bluestein_passes).  It deals the rings to the
-// XCDs, whose loads have to match: by L log2 L alone some XCDs held more of the
-// slow rings than others, and O640, 411 fields, took 2.66 instead of 2.29 ms,
-// O400, 137 fields, 296 instead of 280 us.  It also chooses between the three,
-// ps per point as a general prime pass | by convolution | Bluestein: p = 61,
-// 2440 points, 2.8 | 3.3 | -; p = 89, 2136 points, 3.3 | 3.4 | -; p = 101, 2424
-// points, 3.6 | 3.2 | -; p = 151, 2416 points, 4.2 | 3.1 | -; p = 389, 1556
-// points, 6.4 | - | 5.8; p = 401, 1604 points, 6.4 | 3.65 | 5.7; p = 1009, 4036
-// points, - | 3.5 | 8.7; p = 2521, 5042 points, - | 4.4 | 7.9.
-static double ring_cost(int h, int L, double blue, int p, int nf, double conv = 0)
+namespace {
+
+// How a ring's FFT runs: without large primes, with a general prime pass, with a
+// prime pass by convolution, by Bluestein.
+enum RingKind { kRingPlain, kRingPrime, kRingConv, kRingBlue };
+
+// Time of one block of nf fields of a ring of half-length h, in nanoseconds with
+// the CUs full of such blocks: so much for the block (its descriptors, first
+// loads, last stores), for each pass (barriers and the loads it begins with;
+// `passes` without a general prime pass), for each value, and for the work of
+// the kind's own: a prime pass's cycles (16 p for each unit of a wave),
+// instructions per value of a convolution's or Bluestein's passes.  Fitted to
+// 10 494 timings on MI355X (random lengths of 20 to 16 382 points, 1 to 411
+// fields, every kind that a length can take; 6 to 11 % RMS).  A block of few
+// values is mostly its passes, of which a convolution and Bluestein have more:
+// by throughput alone, as 411 fields have it, some rings of few fields ran up
+// to half as long again (us, general prime pass | convolution | Bluestein, both
+// directions, 512 rings; FP64 244 points, 2 fields, 24.4 | 36.8 | 38.6; FP32 122
+// points, 3 fields, 17.6 | 24.1 | 21.9; but FP32 2416 points, 411 fields, 4.2 |
+// 3.1 | - ps per point).  With it the choice costs 0.2 % against the fastest of
+// the three on average over the timed rings, 2.5 % before.
+double block_time(bool dbl, RingKind kind, int h, double passes, int nf, double work)
 {
-    const double n = 2.0 * h;
-    if (conv > 0) return n * (1.9 + 0.0098 * conv);
-    if (blue > 0) return n * 0.0160 * blue * L / h;
-    if (!p) return n * 2.05;
-    return n * 2.4 + 16.0 * p * gp_cost(gp_best_shape(p, nf * (h / p))) / nf / 0.614;
+    static const double t[2][4][4] = {{{2800, 280, 1.23, 0}, {3000, 830, 1.24, 1.0}, {3700, 560, 1.37, 0.0059},
+                                       {6000, 290, 1.44, 0.0055}},
+                                      {{3200, 280, 1.23, 0}, {3200, 710, 1.46, 0.91}, {3400, 590, 1.27, 0.0073},
+                                       {4600, 600, 1.97, 0.0039}}};
+    const double *c = t[dbl][kind];
+    return c[0] + c[1] * passes + c[2] * h * nf + c[3] * work;
 }
+
+// Of F fields, fb a block (the last block takes what is left).
+template <class Fn>
+double fields_time(int F, int fb, Fn block)
+{
+    return F / fb * block(fb) + (F % fb ? block(F % fb) : 0.0);
+}
+
+double prime_block_time(bool dbl, int p, int h, double passes, int nf)
+{
+    return block_time(dbl, kRingPrime, h, passes, nf, 16.0 * p * gp_cost(gp_best_shape(p, nf * (h / p))));
+}
+
+// By what a ring's ways of running are compared: the time of nlat such rings on
+// the chip's block slots (two a CU, FP64 one), one block's at least.
+template <class Fn>
+double ring_time(bool dbl, int nlat, int F, int fb, Fn block)
+{
+    return std::max(block(std::min(F, fb)), fields_time(F, fb, block) * nlat / (dbl ? 256 : 512));
+}
+
+// Fields per block (at most fb) of a ring with a general prime pass, among the
+// counts whose units fit one tile per wave: the least time.  Small plans, with
+// slots to spare, take fewer than the most that fit (c2r, against the least time
+// of the blocks' sum: T75, 45 fields on a full grid 16.2 -> 11.0 us, T117, 59 fields on
+// O118 20.6 -> 18.7).  0 if not even one field's fit.
+int prime_fields(bool dbl, int nlat, int p, int h, double passes, int F, int fb)
+{
+    int best = 0;
+    double least = 0;
+    for (int nf = 1; nf <= fb && gp_best_shape(p, nf * (h / p)); ++nf) {
+        const double t = ring_time(dbl, nlat, F, nf, [&](int k) { return prime_block_time(dbl, p, h, passes, k); });
+        if (!best || t < least) {
+            best = nf;
+            least = t;
+        }
+    }
+    return best;
+}
+
+}  // namespace
 
 // FFT blocking: fields per block (at most `cap` complex values of LDS per
 // block), the XCD-segmented work list and the dynamic LDS size.
@@ -467,6 +515,8 @@ int fft_blocking(Plan &p, int cap)
         // a general prime pass takes one tile of output units per wave, a
         // pass in LDS its rounds of kFftThreads butterflies
         int extra = 0, gp = 0, gp_nbf = 0;
+        const bool dbl = p.prec == SHTX_FP64;
+        const double passes = 0.5 * (d.nrad + d.nrad_r);
         for (int dir = 0; dir < 2; ++dir) {
             const int nrad = dir ? d.nrad_r : d.nrad;
             for (int s = 0; s < nrad; ++s) {
@@ -475,8 +525,8 @@ int fft_blocking(Plan &p, int cap)
                 int lim;
                 if (s < d.conv) {
                     lim = std::min(fft_rounds(maxcap, R) * kFftThreads / q.nbf, kFftThreads) / (d.h / d.conv_p);
-                } else if (gp_radix(R, p.prec == SHTX_FP64)) {
-                    lim = gp_fields(R, d.h, d.fb);
+                } else if (gp_radix(R, dbl)) {
+                    lim = prime_fields(dbl, p.nlat, R, d.h, passes - 1, F, d.fb);
                     extra = gp = R;
                     gp_nbf = q.nbf;
                 } else {
@@ -493,7 +543,12 @@ int fft_blocking(Plan &p, int cap)
             g.push_back(FftItem{j, f0, nf, gp ? gp_best_shape(gp, nf * gp_nbf) : 0});
         }
         fgroups.push_back(g);
-        fcost.push_back((double)F * ring_cost(d.h, d.L, d.blue ? d.blue_cost : 0.0, gp, d.fb, d.conv ? d.blue_cost : 0.0));
+        fcost.push_back(fields_time(F, d.fb, [&](int nf) {
+            return gp       ? prime_block_time(dbl, gp, d.h, passes - 1, nf)
+                   : d.conv ? block_time(dbl, kRingConv, d.h, passes, nf, (double)nf * d.h * d.blue_cost)
+                   : d.blue ? block_time(dbl, kRingBlue, d.h, passes, nf, (double)nf * d.L * d.blue_cost)
+                            : block_time(dbl, kRingPlain, d.h, passes, nf, 0.0);
+        }));
     }
     p.fft_lds_bytes = lds_elems * (int)celem;
     p.fft_lds_max = lds_elems;
@@ -647,28 +702,53 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         if (Lb > cap) Lb = smallest(2 * h - 1, true);
         std::pair<double, int> bl = {1e300, 0};  // cost of a field, length
         if (rem > 1 && Lb <= cap) bl = bluestein_length(2 * h - 1, cap, dbl, blues);
-        // one prime factor above the register radices, up to kGpMaxPrime, is
-        // run as a general prime pass (first, at Ns = 1) instead of Bluestein
-        // when one field's output units fit the block's waves and, above 191,
-        // when ring_cost favours it
+        // one prime factor above the register radices runs as the first pass, as
+        // a general prime pass (up to kGpMaxPrime, where one field's output units
+        // fit the block's waves) or by convolution, or the whole length by
+        // Bluestein: what takes the least time for the plan's fields
         const int fmost = std::max(1, std::min(F, cap / (h + 1)));
         const bool prime = rem > 1 && is_prime(rem);
-        bool gp = prime && rem <= kGpMaxPrime &&
-                  gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
-        const double bcost = Lb <= cap ? ring_cost(h, bl.second, bl.first, 0, 1) : 1e300;
-        const double gcost = gp ? ring_cost(h, h, 0, rem, gp_fields(rem, h, fmost)) : 1e300;
-        if (gp && rem > 191 && gcost >= bcost) gp = false;
-        // a prime pass by convolution takes the place of either where its
-        // passes cost less: from primes of about 97 on
-        if (prime && (gp || Lb <= cap)) {
+        const bool can_gp = prime && rem <= kGpMaxPrime &&
+                            gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
+        bool gp = can_gp;
+        double least = 1e300;
+        if (prime && (can_gp || Lb <= cap)) {
+            // the other passes, alike for the first two
+            double rest = 0;
+            for (int dir = 0; dir < 2; ++dir) rest += 0.5 * (plan_passes(h, rem, dir == 1, dbl).rad.size() - 1);
+            if (can_gp)
+                least = ring_time(dbl, nlat, F, prime_fields(dbl, nlat, rem, h, rest, F, fmost),
+                                  [&](int nf) { return prime_block_time(dbl, rem, h, rest, nf); });
             // passes of radix 13, 14 and 15 run one round of butterflies: with
             // them a block takes fewer fields than its LDS holds (2504 points,
             // 411 fields, 6.0 -> 4.0 ps per point), unless that splits a call's
             // few fields over two blocks (O1280, 3 fields, 108 -> 113 us)
-            lp.conv = conv_passes(rem, h / rem, fmost, dbl);
-            if (lp.conv.rad.empty() && fmost < F && kFftThreads * 13 / h > 0)
-                lp.conv = conv_passes(rem, h / rem, std::min(fmost, kFftThreads * 13 / h), dbl);
-            if (ring_cost(h, h, 0, 0, 1, lp.conv.cost) >= (gp ? gcost : bcost)) lp.conv = PassPlan();
+            int nf = fmost;
+            lp.conv = conv_passes(rem, h / rem, nf, dbl);
+            if (lp.conv.rad.empty() && fmost < F && kFftThreads * 13 / h > 0) {
+                nf = std::min(fmost, kFftThreads * 13 / h);
+                lp.conv = conv_passes(rem, h / rem, nf, dbl);
+            }
+            if (!lp.conv.rad.empty()) {
+                nf = std::min(nf, std::max(1, kFftThreads / (h / rem)));
+                const double t = ring_time(dbl, nlat, F, nf, [&](int k) {
+                    return block_time(dbl, kRingConv, h, rest + lp.conv.rad.size(), k, (double)k * h * lp.conv.cost);
+                });
+                if (t >= least) lp.conv = PassPlan();
+                least = std::min(least, t);
+            }
+        }
+        if (prime && Lb <= cap && bl.second) {
+            const BluePlan &b = blues[bl.second];
+            const double passes = 0.5 * (b.pass[0].rad.size() + b.pass[1].rad.size());
+            const int nf = std::max(1, std::min(F, cap / std::max(bl.second, h + 1)));
+            const double t = ring_time(dbl, nlat, F, nf, [&](int k) {
+                return block_time(dbl, kRingBlue, h, passes, k, (double)k * bl.second * bl.first);
+            });
+            if (t < least) {
+                gp = false;
+                lp.conv = PassPlan();
+            }
         }
         if (rem == 1 || gp || !lp.conv.rad.empty()) {
             lp.L = h;

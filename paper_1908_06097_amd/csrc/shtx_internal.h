@@ -67,7 +67,7 @@ __host__ __device__ constexpr bool fft_radix_ok(int kind, bool dbl, int R)
     case kPassToGrid: return R <= 10 || R == 12 || R == 16 || (!dbl && (R == 14 || R == 15 || R == 18 || R == 20));
     case kPassToFour: return R <= 6 || R == 8 || (!dbl && (R == 7 || R == 9));
     case kPassSeam: return R == 9 || R == 10 || (dbl ? R == 12 : R == 15 || R == 18);
-    case kPassGather: return (R > 2 && R <= 19) || R == 23;
+    case kPassGather: return R == 3 || (R > 4 && R <= 19) || R == 23;
     case kPassSub: return R <= 19 || R == 23;
     case kPassScatter: return R <= 11 || (R >= 13 && R <= 17) || R == 19;
     case kPassSubSeam:
@@ -125,25 +125,6 @@ inline int gp_best_shape(int p, int nb)
         best = gp_shape(NI, NJ);
     SHTX_GP_SHAPES(SHTX_GP)
 #undef SHTX_GP
-    return best;
-}
-// Fields per block (at most fb) of a ring of half-length h with a prime pass:
-// the fewest cycles per field of the pass (16 p for each unit of a wave) and
-// of what a block costs whatever its fields (0.7 h: shorter runs in the
-// Fourier rows).  0 if not even one field's units fit.
-inline int gp_fields(int p, int h, int fb)
-{
-    int best = 0;
-    double cost = 0;
-    for (int nf = 1; nf <= fb; ++nf) {
-        const int shape = gp_best_shape(p, nf * (h / p));
-        if (!shape) break;
-        const double c = (16.0 * p * gp_cost(shape) + 0.7 * h) / nf;
-        if (!best || c < cost) {
-            best = nf;
-            cost = c;
-        }
-    }
     return best;
 }
 constexpr int kMaxRadices = 12;

@@ -1,6 +1,6 @@
 // Ring-FFT plans of the built library, for the host test of what the GPU tests
-// reach: for every "precision nlon nfld cap" on standard input (precision 0
-// FP64, 1 FP32; cap 0: the default blocking) the plan of a full grid of such
+// reach: for every "precision nlon nfld cap nlat" on standard input (precision 0
+// FP64, 1 FP32; cap 0: the default blocking) the plan of a full grid of nlat such
 // rings, as words on one line: kind:radix of every pass of both directions
 // (kinds as FftPassKind; B before a pass of Bluestein's that is joined to the
 // grid), gp:p of a general prime pass and shape:NIxNJ of its work items; or
@@ -85,11 +85,11 @@ int main(int argc, char **argv)
         print(kernels(false));
         return 0;
     }
-    int prec, nlon, nfld, cap;
-    while (std::scanf("%d %d %d %d", &prec, &nlon, &nfld, &cap) == 4) {
+    int prec, nlon, nfld, cap, nlat;
+    while (std::scanf("%d %d %d %d %d", &prec, &nlon, &nfld, &cap, &nlat) == 5) {
         Plan p;
         const int trunc = nlon > 40 ? 20 : (nlon - 1) / 2;
-        if (plan_layout(p, trunc, SHTX_GRID_FULL, 4, nlon, nfld, prec, 0) != SHTX_OK ||
+        if (plan_layout(p, trunc, SHTX_GRID_FULL, nlat, nlon, nfld, prec, 0) != SHTX_OK ||
             (cap && fft_blocking(p, cap) != SHTX_OK) || !fft_shapes_ok(p)) {
             std::printf("refused\n");
             continue;
