@@ -793,7 +793,9 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         auto root = [&](long double a) {  // exp(-i a)
             long double si, co;
             sincosl(a, &si, &co);
-            push(co, -si);
+            // exact at the quarter turns, where cosl(pi / 2) is 1e-20: values that
+            // cancel would keep a residue of that times the others
+            push(std::fabs(co) < 1e-18L ? 0.0L : co, std::fabs(si) < 1e-18L ? 0.0L : -si);
         };
         lp.post = (int64_t)pool.size() / 2;
         for (int m = 0; m <= h; ++m) root(2.0L * pi * m / n);

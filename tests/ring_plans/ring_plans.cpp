@@ -3,9 +3,10 @@
 // FP64, 1 FP32; cap 0: the default blocking) the plan of a full grid of nlat such
 // rings, as words on one line: kind:radix of every pass of both directions
 // (kinds as FftPassKind; B before a pass of Bluestein's that is joined to the
-// grid), gp:p of a general prime pass and shape:NIxNJ of its work items; or
-// "refused".  With an argument "kernels" instead: the passes and shapes that
+// grid), gp:p of a general prime pass and shape:NIxNJ of its work items, residue
+// if a root of unity is next to 0 but not 0; or "refused".  With an argument "kernels" instead: the passes and shapes that
 // have a kernel.  No GPU.
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <set>
@@ -50,6 +51,10 @@ std::set<std::string> kernels(bool dbl)
 
 void ring_words(const Plan &p, const RingDesc &d, std::set<std::string> &out)
 {
+    for (int64_t i = 2 * d.post_off; i < 2 * (d.post_off + d.h + 1); ++i)
+        if (p.twid_host[i] != 0 && std::fabs(p.twid_host[i]) < 1e-17) out.insert("residue");
+    for (int64_t i = 2 * d.tw_off; i < 2 * (d.tw_off + d.L); ++i)
+        if (p.twid_host[i] != 0 && std::fabs(p.twid_host[i]) < 1e-17) out.insert("residue");
     for (int dir = 0; dir < 2; ++dir) {
         const int off = dir ? d.pass_off_r : d.pass_off, n = dir ? d.nrad_r : d.nrad;
         const int fin = dir ? d.fuse_in_r : d.fuse_in, fout = dir ? d.fuse_out_r : d.fuse_out;

@@ -56,6 +56,14 @@ def test_every_kernel_has_a_ring(prec):
     assert sorted(kernels - {w for p in plans for w in p.split()}) == []
 
 
+# Roots of unity at quarter turns are exact zeros and ones: cosl(pi / 2) is 1e-20,
+# and what should cancel would leave that much of the other values.
+def test_quarter_turns_are_exact():
+    lengths = [24, 64, 244, 488, 1604, 2416, 4996, 5120]
+    plans = _ring_plans(input="\n".join(f"{c} {n} 3 0 4" for n in lengths for c in (0, 1))).splitlines()
+    assert len(plans) == 2 * len(lengths) and not any("residue" in p for p in plans)
+
+
 # Few values a block take the kind with the fewest passes, many the one with the
 # least work (the faster of the two by 15 to 50 % in each case).
 @pytest.mark.parametrize("prec,nlon,nf,want", [
