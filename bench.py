@@ -38,7 +38,11 @@ PEAK = {  # MI355X published dense peaks
     "bf16_TF": 2500.0,
     "fp16_TF": 2500.0,
 }
-PEAK_TF = {"fp64": PEAK["fp64_TF"], "fp32": PEAK["fp32_TF"], "bf16x3": PEAK["bf16_TF"], "fp16x3": PEAK["fp16_TF"]}
+# matrix-core unit of each form's Legendre GEMM, products there of one useful one, and the probe of
+# the unit's rate (FP32 multiplies three bfloat16 pieces; few fields run on the FP32 unit itself)
+GEMM_UNIT = {"fp64": ("fp64_TF", 1, "mfma_f64_TF"), "fp32": ("bf16_TF", 6, "mfma_bf16_TF"),
+             "bf16x3": ("bf16_TF", 3, "mfma_bf16_TF"), "fp16x3": ("fp16_TF", 3, "mfma_f16_TF")}
+FEW_FIELDS_FP32 = {"legendre_inverse_gemm": 16, "legendre_direct_gemm": 32}
 DTYPE = {"fp64": "f64", "fp32": "f32", "bf16x3": "bf16x3", "fp16x3": "fp16x3"}
 KERNELS = ["legendre_inverse_gemm", "legendre_direct_gemm", "ring_fft_c2r", "ring_fft_r2c"]
 
@@ -216,16 +220,25 @@ def tiles_of(plan):
             "chosen_by": ["default", "autotuner", "tune cache"][int(i.tuned)]}
 
 
+def gemm_unit(prec, nfld, kernel):
+    """Matrix-core unit (key of PEAK), products per useful one and probe of a Legendre GEMM."""
+    if prec == "fp32" and nfld <= FEW_FIELDS_FP32[kernel]:
+        return "fp32_TF", 1, "mfma_f32_TF"
+    return GEMM_UNIT[prec]
+
+
 def roofline_for(res, prec):
     plan = res["plan"]
     nbytes = kernel_bytes(plan, prec)
     flops = res["legendre_flops"]
-    peak_tf = PEAK_TF[prec]
     out = {}
     for k, t in res["kernel_ms"].items():
         if k.startswith("legendre"):
             ach = flops / (t * 1e-3) / 1e12
+            unit, products, _ = gemm_unit(prec, plan.info.nfld, k)
+            peak_tf = PEAK[unit] / products
             out[k] = {"bound": "mfma", "achieved": ach, "peak": peak_tf, "unit": "TFLOP/s",
+                      "peak_unit": unit[:-3] + " matrix cores", "products": products,
                       "frac": ach / peak_tf, "ms": t, "hbm_GBps": nbytes[k] / (t * 1e-3) / 1e9,
                       "hbm_frac": nbytes[k] / (t * 1e-3) / 1e9 / PEAK["hbm_GBps"],
                       "algorithmic_bytes": nbytes[k], "algorithmic_flops": flops}
@@ -343,10 +356,6 @@ def form_summary(res, prec, wl):
             "fft_hbm_frac": {k: rf[k]["frac"] for k in rf if k.startswith("ring")}}
 
 
-# the probe whose measured rate stands beside each form's published MFMA peak
-PEAK_PROBE = {"fp64": "mfma_f64_TF", "fp32": "mfma_f32_TF", "bf16x3": "mfma_bf16_TF", "fp16x3": "mfma_f16_TF"}
-
-
 def measure_peaks(torch, shtx):
     """Rates this GPU sustains (shtx_probe_peak): matrix-core loops per
     precision, the non-packed FP32 vector-ALU rate, and a 1 GiB HBM copy and
@@ -400,6 +409,8 @@ def main():
     d = roof[dom]
     roofline = {"bound": d["bound"], "achieved": d["achieved"], "peak": d["peak"], "unit": d["unit"],
                 "frac": d["frac"], "traffic": traffic_for(dom, wl.name, args.prec), "kernel": dom}
+    if d["bound"] == "mfma":
+        roofline.update(peak_unit=d["peak_unit"], products=d["products"])
     line = {
         "metric": "inv+dir SH transform fields/s",
         "value": res["fields_per_s"],
@@ -468,10 +479,13 @@ def main():
         say("peak probes")
         peaks = measure_peaks(torch, shtx)
         line["peaks_measured"] = peaks
-        key = {"TFLOP/s": PEAK_PROBE[args.prec], "GB/s": "hbm_copy_GB_s"}[roofline["unit"]]
+        key, products = "hbm_copy_GB_s", 1
+        if roofline["bound"] == "mfma":
+            _, products, key = gemm_unit(args.prec, wl.nfld, dom)
         if peaks.get(key):
-            line["roofline_vs_measured"] = {"peak": peaks[key], "probe": key,
-                                            "frac": roofline["achieved"] / peaks[key]}
+            peak = peaks[key] / products
+            line["roofline_vs_measured"] = {"peak": peak, "probe": key, "products": products,
+                                            "frac": roofline["achieved"] / peak}
     print(json.dumps(line), flush=True)
 
 
