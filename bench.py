@@ -53,7 +53,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--workload", default="tco1279_o1280")
-    ap.add_argument("--prec", default="fp32", choices=sorted(PEAK_TF))
+    ap.add_argument("--prec", default="fp32", choices=sorted(GEMM_UNIT))
     ap.add_argument("--forms", default="fp64,bf16x3,fp16x3",
                     help="extra precision forms timed beside the headline (comma list, or none)")
     ap.add_argument("--form-steps", type=int, default=5)
