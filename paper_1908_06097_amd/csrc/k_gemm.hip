@@ -613,11 +613,11 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_leg_narrow(GemmArgs a)
 // in flight over the MFMAs.
 //
 // O1280, 411 fields, against the kernels before (16x16x4 FP32 MFMA; split
-// operands re-staged by field): FP32 inverse 13.4 -> 9.95 ms, direct 13.6 -> 11.6;
-// BF16x3 8.3 -> 6.9 and 8.8 -> 7.8; T399, 137 fields, FP32 244 -> 175 and 285 ->
-// 232 us; T2799 on 4200 x 8400 points, 120 fields, 35.8 -> 24.6 and 37.5 -> 29.4 ms.
+// operands re-staged by field): FP32 inverse 13.4 -> 9.95 ms, direct 13.6 -> 11.3;
+// BF16x3 8.3 -> 6.9 and 8.8 -> 7.6; T399, 137 fields, FP32 244 -> 176 and 285 ->
+// 224 us; T2799 on 4200 x 8400 points, 120 fields, 35.8 -> 25.0 and 37.5 -> 28.7 ms.
 // (With the data cut instead of rounded to its first piece, no look for values
-// that pieces do not hold and the FP32 table in pieces: 9.7 and 10.95.)  Of the
+// that pieces do not hold and the FP32 table in pieces: 9.7 and 11.0.)  Of the
 // FP32 inverse's 9.8 ms then, found by leaving out one part at a
 // time: MFMAs 2.7, operand loads 2.7, conversion and LDS stores 1.4, output and
 // block start 2.3 (8.1 GB written); the parts add up instead of overlapping
@@ -1319,10 +1319,11 @@ bool gemm_tile_supported(int prec, int bm, int bn)
 // Column fragments of the few-fields kernel for a plan and direction, 0 where
 // the tiled kernels serve it.  The lines lie where the accumulators (32 FN
 // registers in FP32, 64 FN in FP64) leave too few waves to cover the table's
-// latency: T639 on O640, microseconds against the tiled kernel, FP32 inverse
-// 150 / 206 at 16 fields but 360 / 280 at 24, direct 152 / 252 at 16 and 247 /
-// 319 at 32 (its operand loads are fewer), FP64 227 / 240 at 8 and 393 / 308
-// at 12.
+// latency.  Microseconds against the tiled kernel: FP32 inverse, 16 fields,
+// T63 8.2 / 9.2, T127 10.5 / 13.4, T255 22.6 / 23.2, T639 156 / 137, T1279 948 /
+// 875 (the tiled one gains from 400 on), direct T127 10.7 / 20.9, T639 159 / 266, 32
+// fields 262 / 287 (its operand loads are fewer); FP64 T639 8 fields 231 / 247 and
+// 242 / 286, but 12 fields 393 / 310.
 int gemm_narrow(int prec, int nfld, bool inverse)
 {
     const int ncol = 2 * nfld;

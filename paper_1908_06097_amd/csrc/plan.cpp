@@ -314,13 +314,13 @@ hipError_t upload(T **dst, const std::vector<T> &src)
 
 // Default tiles.  128 x 128 but where rows or columns would mostly be padding;
 // measured on octahedral grids, microseconds at 128 x 128 / 64 x 128 / 128 x 64:
-//   few rows a wavenumber: FP32 inverse T213 37 fields 26 / 21 / 21, T639 40
-//   fields 236 / 230; BF16x3 inverse T213 20 / 18, T639 411 fields 1131 / 1266;
-//   direct FP32 T255 411 fields 184 / 169, T639 1577 / 1640, BF16x3 T399 137
-//   fields 192 / 175, T639 518 / 541;
-//   columns: FP32 inverse T639 137 fields (274 columns in 384 or 320) 575 / 572
-//   / 524, T1279 4094 / 4502 / 3725, but 411 fields (822 in 896 or 832) 9830 /
-//   - / 10160.
+//   few rows a wavenumber: FP32 inverse T213 37 fields 28 / 22 / 23, T639 40
+//   fields 225 / 228; BF16x3 inverse T213 20 / 17, T639 411 fields 1120 / 1270;
+//   direct FP32 T255 411 fields 190 / 177, T639 1684 / 1824, BF16x3 T399 137
+//   fields 188 / 174, T639 411 fields 1173 / 1316;
+//   columns: FP32 inverse T639 137 fields (274 columns in 384 or 320) 599 / 629
+//   / 544, T1279 4096 / 4553 / 3856, but 411 fields (822 in 896 or 832) 10043 /
+//   11427 / 10561.
 void gemm_tiles(int prec, int trunc, int nfld, int *inv_bm, int *inv_bn, int *dir_bm, int *dir_bn)
 {
     if (prec == SHTX_FP64) {

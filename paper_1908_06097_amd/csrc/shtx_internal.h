@@ -337,8 +337,8 @@ int gemm_narrow(int prec, int nfld, bool inverse);
 //   kTabUnits   single precision: floats, times kF32TableScale, in the same order,
 //               [p][k / 8][r][k % 8] | [p][r / 8][k][r % 8]; the GEMM cuts them
 //               into pieces (stored in pieces they take half as much memory
-//               again and gain 2 to 4 % of the direct GEMM, T1279 11.3 against
-//               11.6 ms, and nothing of the inverse)
+//               again and gain 2 to 4 % of the direct GEMM and nothing of the
+//               inverse, T1279 11.3 against 11.6 ms and 9.9 each)
 enum TableLayout { kTabPlain, kTabPieces, kTabUnits };
 inline TableLayout table_layout(const Plan &p, bool inverse)
 {
