@@ -712,10 +712,13 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
                             gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
         bool gp = can_gp;
         double least = 1e300;
+        PassPlan first[2];  // a prime pass and the others, alike for the first two ways
         if (prime && (can_gp || Lb <= cap)) {
-            // the other passes, alike for the first two
             double rest = 0;
-            for (int dir = 0; dir < 2; ++dir) rest += 0.5 * (plan_passes(h, rem, dir == 1, dbl).rad.size() - 1);
+            for (int dir = 0; dir < 2; ++dir) {
+                first[dir] = plan_passes(h, rem, dir == 1, dbl);
+                rest += 0.5 * (first[dir].rad.size() - 1);
+            }
             if (can_gp)
                 least = ring_time(dbl, nlat, F, prime_fields(dbl, nlat, rem, h, rest, F, fmost),
                                   [&](int nf) { return prime_block_time(dbl, rem, h, rest, nf); });
@@ -764,7 +767,7 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
             if (!lp.blue && q >= 11 && lp.L / q > kFftThreads) return SHTX_EUNSUPPORTED;
         for (int dir = 0; dir < 2; ++dir) {
             PassPlan &pp = lp.pass[dir];
-            pp = lp.blue ? blues[lp.L].pass[dir] : plan_passes(lp.L, rem, dir == 1, dbl);
+            pp = lp.blue ? blues[lp.L].pass[dir] : rem > 1 ? first[dir] : plan_passes(lp.L, 1, dir == 1, dbl);
             const int nconv = (int)lp.conv.rad.size(), P = nconv ? rem - 1 : 0;
             if (nconv && !pp.rad.empty()) {
                 pp.rad.erase(pp.rad.begin());
