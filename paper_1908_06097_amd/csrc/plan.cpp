@@ -508,6 +508,7 @@ int fft_blocking(Plan &p, int cap)
     int lds_elems = 0;
     std::vector<std::vector<FftItem>> fgroups;
     std::vector<double> fcost;
+    std::map<std::pair<int, int>, int> prime_lim;  // by ring length and fields
     for (int j = 0; j < p.nlat; ++j) {
         RingDesc &d = p.rings[j];
         if (d.lbuf > maxcap) return SHTX_EUNSUPPORTED;
@@ -526,7 +527,9 @@ int fft_blocking(Plan &p, int cap)
                 if (s < d.conv) {
                     lim = std::min(fft_rounds(maxcap, R) * kFftThreads / q.nbf, kFftThreads) / (d.h / d.conv_p);
                 } else if (gp_radix(R, dbl)) {
-                    lim = prime_fields(dbl, p.nlat, R, d.h, passes - 1, F, d.fb);
+                    int &nf = prime_lim[{d.n, d.fb}];
+                    if (!nf) nf = prime_fields(dbl, p.nlat, R, d.h, passes - 1, F, d.fb);
+                    lim = nf;
                     extra = gp = R;
                     gp_nbf = q.nbf;
                 } else {
