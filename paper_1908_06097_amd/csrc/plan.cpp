@@ -713,50 +713,62 @@ int plan_layout(Plan &p, int trunc, int grid, int nlat, int nlon_full, int nfld,
         const bool prime = rem > 1 && is_prime(rem);
         const bool can_gp = prime && rem <= kGpMaxPrime &&
                             gp_row_tiles(rem) * gp_col_tiles(h / rem) <= kGpFieldUnits && gp_best_shape(rem, h / rem);
-        bool gp = can_gp;
-        double least = 1e300;
+        RingKind kind = rem == 1 ? kRingPlain : kRingBlue;
         PassPlan first[2];  // a prime pass and the others, alike for the first two ways
         if (prime && (can_gp || Lb <= cap)) {
-            double rest = 0;
-            for (int dir = 0; dir < 2; ++dir) {
-                first[dir] = plan_passes(h, rem, dir == 1, dbl);
-                rest += 0.5 * (first[dir].rad.size() - 1);
-            }
-            if (can_gp)
-                least = ring_time(dbl, nlat, F, prime_fields(dbl, nlat, rem, h, rest, F, fmost),
-                                  [&](int nf) { return prime_block_time(dbl, rem, h, rest, nf); });
             // passes of radix 13, 14 and 15 run one round of butterflies: with
             // them a block takes fewer fields than its LDS holds (2504 points,
             // 411 fields, 6.0 -> 4.0 ps per point), unless that splits a call's
             // few fields over two blocks (O1280, 3 fields, 108 -> 113 us)
-            int nf = fmost;
-            lp.conv = conv_passes(rem, h / rem, nf, dbl);
+            int conv_nf = fmost;
+            lp.conv = conv_passes(rem, h / rem, conv_nf, dbl);
             if (lp.conv.rad.empty() && fmost < F && kFftThreads * 13 / h > 0) {
-                nf = std::min(fmost, kFftThreads * 13 / h);
-                lp.conv = conv_passes(rem, h / rem, nf, dbl);
+                conv_nf = std::min(fmost, kFftThreads * 13 / h);
+                lp.conv = conv_passes(rem, h / rem, conv_nf, dbl);
             }
-            if (!lp.conv.rad.empty()) {
-                nf = std::min(nf, std::max(1, kFftThreads / (h / rem)));
-                const double t = ring_time(dbl, nlat, F, nf, [&](int k) {
-                    return block_time(dbl, kRingConv, h, rest + lp.conv.rad.size(), k, (double)k * h * lp.conv.cost);
-                });
-                if (t >= least) lp.conv = PassPlan();
-                least = std::min(least, t);
+            conv_nf = std::min(conv_nf, std::max(1, kFftThreads / (h / rem)));
+            // with `rest` passes after the prime one
+            auto fastest = [&](double rest) {
+                RingKind best = kRingBlue;
+                double least = 1e300;
+                auto take = [&](RingKind k, double t) {
+                    if (t < least) {
+                        best = k;
+                        least = t;
+                    }
+                };
+                if (can_gp)
+                    take(kRingPrime, ring_time(dbl, nlat, F, prime_fields(dbl, nlat, rem, h, rest, F, fmost),
+                                               [&](int nf) { return prime_block_time(dbl, rem, h, rest, nf); }));
+                if (!lp.conv.rad.empty())
+                    take(kRingConv, ring_time(dbl, nlat, F, conv_nf, [&](int nf) {
+                             return block_time(dbl, kRingConv, h, rest + lp.conv.rad.size(), nf,
+                                               (double)nf * h * lp.conv.cost);
+                         }));
+                if (Lb <= cap && bl.second) {
+                    const BluePlan &b = blues[bl.second];
+                    const double passes = 0.5 * (b.pass[0].rad.size() + b.pass[1].rad.size());
+                    take(kRingBlue,
+                         ring_time(dbl, nlat, F, std::max(1, std::min(F, cap / std::max(bl.second, h + 1))), [&](int nf) {
+                             return block_time(dbl, kRingBlue, h, passes, nf, (double)nf * bl.second * bl.first);
+                         }));
+                }
+                return best;
+            };
+            // the search for the other passes only where Bluestein does not win
+            // without them
+            kind = fastest(0);
+            if (kind != kRingBlue) {
+                double rest = 0;
+                for (int dir = 0; dir < 2; ++dir) {
+                    first[dir] = plan_passes(h, rem, dir == 1, dbl);
+                    rest += 0.5 * (first[dir].rad.size() - 1);
+                }
+                kind = fastest(rest);
             }
+            if (kind != kRingConv) lp.conv = PassPlan();
         }
-        if (prime && Lb <= cap && bl.second) {
-            const BluePlan &b = blues[bl.second];
-            const double passes = 0.5 * (b.pass[0].rad.size() + b.pass[1].rad.size());
-            const int nf = std::max(1, std::min(F, cap / std::max(bl.second, h + 1)));
-            const double t = ring_time(dbl, nlat, F, nf, [&](int k) {
-                return block_time(dbl, kRingBlue, h, passes, k, (double)k * bl.second * bl.first);
-            });
-            if (t < least) {
-                gp = false;
-                lp.conv = PassPlan();
-            }
-        }
-        if (rem == 1 || gp || !lp.conv.rad.empty()) {
+        if (kind != kRingBlue) {
             lp.L = h;
             lp.blue = 0;
         } else {
